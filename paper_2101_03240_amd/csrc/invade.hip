@@ -41,6 +41,7 @@
 #include <vector>
 
 #include "ibip_internal.h"
+#include "tree.h"
 
 namespace ibip {
 
@@ -60,22 +61,6 @@ __device__ inline uint32_t isqrt_u32(uint32_t a) {
     while (q * q > a) q--;
     while ((q + 1) * (q + 1) <= a) q++;
     return (uint32_t)q;
-}
-
-// Key words: bits 0..23 hold the rank of dt2 among the distinct pore values
-// (0 on solid); bit 24 + d is set when the face neighbour in direction d
-// (0 -x, 1 +x, 2 -y, 3 +y, 4 -z, 5 +z) lies inside the image; bit 31 marks
-// a voxel claimed as a candidate. A claim thus returns, with the rank, what a
-// later step needs to claim the voxel's own neighbours without dividing its
-// index into coordinates.
-constexpr uint32_t kClaim = 0x80000000u;
-constexpr uint32_t kRankMask = 0x00FFFFFFu;
-constexpr int kNbShift = 24;
-
-// in-image neighbour bits of the voxel at (x, y, z)
-__device__ inline uint32_t nb_bits(uint32_t x, uint32_t y, uint32_t z, int X, int Y, int Z) {
-    return (x > 0 ? 1u : 0u) | (x + 1 < (uint32_t)X ? 2u : 0u) | (y > 0 ? 4u : 0u) |
-           (y + 1 < (uint32_t)Y ? 8u : 0u) | (z > 0 ? 16u : 0u) | (z + 1 < (uint32_t)Z ? 32u : 0u);
 }
 
 // number of set bits of m in the lanes below this one
@@ -145,8 +130,9 @@ __global__ void k_present(const uint32_t* hist, uint32_t* present, int64_t V) {
 // has room for kMaxRanks; beyond that its loop rejects the image).
 __global__ void k_rank_tables(const uint32_t* cnt_scanned, const uint32_t* present_scanned,
                               const uint32_t* hist_raw_flag, int64_t V, uint32_t* val, uint32_t* off,
-                              uint32_t* head, uint32_t* tail, uint32_t rcap) {
+                              uint32_t* head, uint32_t* tail, uint32_t rcap, const LoopState* st) {
     int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v == 0 && st->R <= rcap) off[st->R + 1] = st->n_pore;  // the end of the last slice
     if (v >= V || v == 0 || !hist_raw_flag[v]) return;
     uint32_t r = present_scanned[v] + 1;
     if (r > rcap + 1) return;  // too many ranks: the loop rejects the image
@@ -1759,9 +1745,11 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     uint32_t* tmp32 = (uint32_t*)ensure(ctx, B_TMP1, sizeof(uint32_t) * n);
     uint32_t* partials = (uint32_t*)ensure(ctx, B_SCAN, sizeof(uint32_t) * (V / 1000 + n / 1000 + 64));
     uint8_t* misc = (uint8_t*)ensure(ctx, B_MISC, 4096);
-    LoopState* h_st = (LoopState*)pinned(ctx, 4096);
+    // pinned: the loop state, and the slice offsets (at most kMaxRanks + 2)
+    LoopState* h_st = (LoopState*)pinned(ctx, 4096 + sizeof(uint32_t) * (kMaxRanks + 2));
     if (!key || !state || !bucket || !hist || !g16 || !tmp32 || !partials || !misc || !h_st)
         return fail(ctx, IBIP_ENOMEM, "invade: scratch allocation failed");
+    uint32_t* h_off = (uint32_t*)((uint8_t*)h_st + 4096);
     LoopState* st = (LoopState*)misc;
     uint32_t* solid_flag = &st->solid_seen;
     uint32_t* dummy_total = (uint32_t*)(misc + 1024);
@@ -1809,38 +1797,114 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     if ((rc = hip_check(ctx, hipMemsetAsync(head, 0, sizeof(uint32_t) * (R + 2), s), "memset")) != IBIP_OK) return rc;
     if ((rc = hip_check(ctx, hipMemsetAsync(tail, 0, sizeof(uint32_t) * (R + 2), s), "memset")) != IBIP_OK) return rc;
     hipLaunchKernelGGL(k_rank_tables, dim3(blocks(V)), dim3(256), 0, s, hist, present, flags, V, val, off, head, tail,
-                       R);
-    hipLaunchKernelGGL(k_convert, dim3(blocks(n)), dim3(256), 0, s, image, key, present, n, (uint32_t)(V - 1), state,
-                       seq, d.X, d.Y, d.Z, make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y), R);
+                       R, st);
+    // The component tree takes every call that it can: not a resumption, and
+    // not one stopped after so few steps that the step loop ends first.
+    const bool tree = n_pore > 0 && !big && !resume_cs && !(opts && opts->max_steps > 0 && opts->max_steps < kTreeMinSteps);
+    TreeArgs ta{};
+    if (tree) {
+        if (!ctx->copy_ev &&
+            (rc = hip_check(ctx, hipEventCreateWithFlags(&ctx->copy_ev, hipEventDisableTiming), "event")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, hipMemcpyAsync(h_off, off, sizeof(uint32_t) * (R + 2), hipMemcpyDeviceToHost, s),
+                            "copy")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, hipEventRecord(ctx->copy_ev, s), "event")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, launch_tree_convert(image, key, present, d, (uint32_t)(V - 1),
+                                                     (uint32_t*)state, tmp32,
+                                                     (uint32_t*)seq, tail, bucket, R, s), "convert")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, hipEventSynchronize(ctx->copy_ev), "sync")) != IBIP_OK) return rc;
+        uint32_t lcap = 0;
+        for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
+        ta = TreeArgs{};
+        ta.key = key;
+        ta.list = bucket;
+        ta.off = off;
+        ta.uf = tmp32;
+        ta.top = (uint32_t*)seq;
+        ta.idx = (uint32_t*)state;
+        ta.gu = full;
+        ta.nodes = M;
+        ta.ncap = (uint32_t)(n_pore / 6);
+        ta.M = M;
+        ta.pcap = (uint32_t)(n_pore / 8 + 4096);
+        ta.ecap = (uint32_t)(n_pore / 16 + 4096);
+        ta.lcap = lcap;
+        ta.xcap = lcap + 4096;
+        ta.R = R;
+        ta.sx = d.Y * d.Z;
+        ta.sy = d.Z;
+        ta.n = (uint32_t)n;
+        ta.n_pore = (uint32_t)n_pore;
+        ta.max_steps = opts ? (uint32_t)std::min<int64_t>(opts->max_steps, n_pore) : 0u;
+        uint32_t* w = (uint32_t*)ensure(ctx, B_TREE, tree_words(ta) * sizeof(uint32_t));
+        if (!w) return fail(ctx, IBIP_ENOMEM, "invade: scratch allocation failed");
+        tree_carve(ta, w);
+    } else {
+        hipLaunchKernelGGL(k_convert, dim3(blocks(n)), dim3(256), 0, s, image, key, present, n, (uint32_t)(V - 1), state,
+                           seq, d.X, d.Y, d.Z, make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y), R);
+    }
     if (resume_cs) {
         if (k_done > n_pore) return fail(ctx, IBIP_EINVAL, "invade_resume: more steps done than pore voxels");
         hipLaunchKernelGGL(k_resume_seed, dim3(blocks(n)), dim3(256), 0, s, inlets, resume_cs, k_done, key, state, M,
                            d.X, d.Y, d.Z, tail, bucket, (ctx->readings & IBIP_READ_MASK_INLETS) != 0, &st->pad2);
-    } else {
+    } else if (!tree) {
         hipLaunchKernelGGL(k_seed, dim3(blocks(n)), dim3(256), 0, s, inlets, key, d.X, d.Y, d.Z, tail, bucket,
                            (ctx->readings & IBIP_READ_MASK_INLETS) != 0, R);
     }
     tm.mark(2, s);
-    // loop control
-    h_st->k = 1 + (uint32_t)(resume_cs ? k_done : 0);
-    h_st->status = LS_RUN;
-    h_st->max_steps = opts ? opts->max_steps : 0;
-    {
-        // k, status and max_steps only; the rest stays as computed on the device
-        LoopState init = *h_st;
-        if ((rc = hip_check(ctx, hipMemcpyAsync(&st->k, &init.k, sizeof(uint32_t) * 2, hipMemcpyHostToDevice, s),
-                            "copy")) != IBIP_OK)
+    bool treed = false;  // the tree gave the centres
+    if (tree) {
+        tm.mark(3, s);
+        if ((rc = hip_check(ctx, hipMemsetAsync(ta.ctl, 0, sizeof(TreeCtl), s), "memset")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, launch_tree(ta, h_off, inlets, d, (ctx->readings & IBIP_READ_MASK_INLETS) != 0, seq, s),
+                            "tree")) != IBIP_OK)
             return rc;
-        if ((rc = hip_check(ctx, hipMemcpyAsync(&st->max_steps, &init.max_steps, sizeof(int64_t),
-                                                hipMemcpyHostToDevice, s), "copy")) != IBIP_OK)
-            return rc;
-        if (resume_cs &&
-            (rc = hip_check(ctx, hipMemcpyAsync(&h_st->pad2, &st->pad2, sizeof(uint32_t), hipMemcpyDeviceToHost, s),
-                            "copy")) != IBIP_OK)
+        tm.mark(4, s);
+        TreeCtl* h_ctl = (TreeCtl*)((uint8_t*)h_st + 2048);
+        if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, sizeof(TreeCtl), hipMemcpyDeviceToHost, s), "copy")) !=
+            IBIP_OK)
             return rc;
         if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
-        if (resume_cs && h_st->pad2)
-            return fail(ctx, IBIP_EINVAL, "invade_resume: the checkpoint has a step outside 1..k_done or a centre on solid");
+        treed = !h_ctl->abort;
+        if (treed) {
+            h_st->k = h_ctl->K + 1;
+            h_st->popped = 0;
+            for (uint32_t c : h_ctl->popped) h_st->popped += c;
+            if (tm.on) {
+                ctx->timing.loop_kernel_ms += tm.ms(3, 4);
+                ctx->timing.loop_launches++;
+            }
+        } else {
+            // more peaks, events or rounds than there is room for: the step loop
+            if ((rc = hip_check(ctx, launch_tree_undo(ta, seq, head, tail, s), "undo")) != IBIP_OK) return rc;
+            hipLaunchKernelGGL(k_seed, dim3(blocks(n)), dim3(256), 0, s, inlets, key, d.X, d.Y, d.Z, tail, bucket,
+                               (ctx->readings & IBIP_READ_MASK_INLETS) != 0, R);
+        }
+    }
+    if (!treed) {
+        // loop control
+        h_st->k = 1 + (uint32_t)(resume_cs ? k_done : 0);
+        h_st->status = LS_RUN;
+        h_st->max_steps = opts ? opts->max_steps : 0;
+        {
+            // k, status and max_steps only; the rest stays as computed on the device
+            LoopState init = *h_st;
+            if ((rc = hip_check(ctx, hipMemcpyAsync(&st->k, &init.k, sizeof(uint32_t) * 2, hipMemcpyHostToDevice, s),
+                                "copy")) != IBIP_OK)
+                return rc;
+            if ((rc = hip_check(ctx, hipMemcpyAsync(&st->max_steps, &init.max_steps, sizeof(int64_t),
+                                                    hipMemcpyHostToDevice, s), "copy")) != IBIP_OK)
+                return rc;
+            if (resume_cs &&
+                (rc = hip_check(ctx, hipMemcpyAsync(&h_st->pad2, &st->pad2, sizeof(uint32_t), hipMemcpyDeviceToHost, s),
+                                "copy")) != IBIP_OK)
+                return rc;
+            if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+            if (resume_cs && h_st->pad2)
+                return fail(ctx, IBIP_EINVAL, "invade_resume: the checkpoint has a step outside 1..k_done or a centre on solid");
+        }
     }
     LoopArgs la{st,     head, tail, val, bucket, state, key, M, d.X, d.Y, d.Z, kWideRound, kSmallRound,
                 make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y)};
@@ -1894,10 +1958,12 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     } pjoin;
     int p = 0;
     bool wide_ran = false;  // the wide launch read this round ran a wide step
-    tm.mark(loop_ev(p, 0), s);
-    launch_loop();
-    tm.mark(loop_ev(p, 1), s);
-    for (;;) {
+    if (!treed) {
+        tm.mark(loop_ev(p, 0), s);
+        launch_loop();
+        tm.mark(loop_ev(p, 1), s);
+    }
+    while (!treed) {
         if ((rc = hip_check(ctx, hipGetLastError(), "loop launch")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, hipMemcpyAsync(h_st, st, sizeof(LoopState), hipMemcpyDeviceToHost, s), "copy")) !=
             IBIP_OK)
@@ -1958,8 +2024,8 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         wide_ran = true;
         p ^= 1;
     }
-    if (h_st->err) return fail(ctx, IBIP_EDEVICE, "invade: step loop exceeded the pore count");
-    const int64_t K = (int64_t)h_st->k - 1;
+    if (!treed && h_st->err) return fail(ctx, IBIP_EDEVICE, "invade: step loop exceeded the pore count");
+    const int64_t K = (int64_t)h_st->k - 1, popped = h_st->popped;
     tm.mark(7, s);
     if (K > 0) hipLaunchKernelGGL(k_rank_to_value, dim3(blocks(K)), dim3(256), 0, s, M, K, val);
     // a5: the steps not inserted yet, after the passes on the second stream
@@ -2007,7 +2073,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         T.paint_ms += tm.ms(7, 8);
         T.steps_ms += tm.ms(8, 9);
         T.steps += K;
-        T.popped += h_st->popped + wide_centres;
+        T.popped += popped + wide_centres;
     }
     ctx->last_K = K;
     ctx->last_n_pore = n_pore;
@@ -2116,7 +2182,7 @@ hipError_t job_setup(const JobBufs& j, LoopState* st, const uint8_t* image, cons
     if ((e = launch_scan_u32(present, V, j.partials, &st->R, s)) != hipSuccess) return e;
     // a job's tables hold kMaxRanks ranks; its loop rejects an image with more
     hipLaunchKernelGGL(k_rank_tables, dim3(blocks(V)), dim3(256), 0, s, j.hist, present, flags, V, j.val, j.off,
-                       j.head, j.tail, (uint32_t)kMaxRanks);
+                       j.head, j.tail, (uint32_t)kMaxRanks, st);
     hipLaunchKernelGGL(k_convert, dim3(blocks(n)), dim3(256), 0, s, image, j.key, present, n, (uint32_t)(V - 1),
                        j.state, seq, d.X, d.Y, d.Z, make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y),
                        (uint32_t)kMaxRanks);

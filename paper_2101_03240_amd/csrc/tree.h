@@ -1,0 +1,141 @@
+// The invasion by levels of the component tree (tree.hip): data layout shared
+// by the single-image path, the batch and the server.
+#pragma once
+
+#include "ibip_internal.h"
+
+namespace ibip {
+
+// Key words: bits 0..23 hold the rank of dt2 among the distinct pore values
+// (0 on solid); bit 24 + d is set when the face neighbour in direction d
+// (0 -x, 1 +x, 2 -y, 3 +y, 4 -z, 5 +z) lies inside the image; bit 31 marks
+// a voxel claimed as a candidate. A claim thus returns, with the rank, what a
+// later step needs to claim the voxel's own neighbours without dividing its
+// index into coordinates.
+constexpr uint32_t kClaim = 0x80000000u;
+constexpr uint32_t kRankMask = 0x00FFFFFFu;
+constexpr int kNbShift = 24;
+
+// in-image neighbour bits of the voxel at (x, y, z)
+__device__ inline uint32_t nb_bits(uint32_t x, uint32_t y, uint32_t z, int X, int Y, int Z) {
+    return (x > 0 ? 1u : 0u) | (x + 1 < (uint32_t)X ? 2u : 0u) | (y > 0 ? 4u : 0u) |
+           (y + 1 < (uint32_t)Y ? 8u : 0u) | (z > 0 ? 16u : 0u) | (z + 1 < (uint32_t)Z ? 32u : 0u);
+}
+
+// Rounds after the first that a level of many voxels runs over the whole GPU,
+// at most.
+constexpr int kTreePulls = 6;
+
+// Counters of one tree, zeroed before its first kernel.
+struct TreeCtl {
+    uint32_t nmerge;  // merged peaks (their ids are 0..nmerge-1)
+    uint32_t nroot;   // peaks never merged (ids nmerge..nmerge+nroot-1)
+    uint32_t nev;     // events, the root event 0 included
+    uint32_t nblk;    // blocks of events
+    uint32_t ucnt[kTreePulls + 2];  // voxels that round r of the current level left
+    uint32_t xcnt[2]; // candidates claimed at the current level; the two in turn
+    uint32_t abort;   // a capacity was exceeded: the step loop runs instead
+    uint32_t K;       // steps, after the step limit
+    uint32_t popped[kCountSlots];  // centres, by block
+};
+
+struct TreeArgs {
+    TreeCtl* ctl;
+    const uint32_t* key;
+    const uint32_t* list;  // pore voxels by rank: rank r at off[r] .. off[r + 1]
+    const uint32_t* off;
+    uint32_t* uf;          // N: union-find over voxels
+    uint32_t* top;         // N: the peak that labels a voxel's component at its own level
+    uint32_t* idx;         // N: a voxel's place in the list (kTreeNone on solid), the step in the end
+    // per place of the list
+    uint4* rec;            // two each: the neighbours, the top, the voxel (see TreeRec)
+    uint32_t* dist;        // the round within the level, then the event; kTreeClaimed before
+    uint32_t* gu;          // the thread of the voxel's component at its level
+    // per peak (pcap entries)
+    uint2* cpm;            // (merge level, parent peak); level 0: never merged
+    uint32_t *plo, *mark, *grp, *er, *head, *lcnt, *E;
+    // per event (ecap entries; an event is also the thread that it starts):
+    // (level, round) of its last event, first event of its current block, last
+    // block; per block of events: thread, first event, events, level, the
+    // thread's block before it
+    uint32_t *gm, *gbase, *lastb, *bg, *bbase, *bcnt, *blev, *bprev;
+    uint2 *rank0, *rank1;  // 2 ecap each: list ranking of the events' tour (next, steps)
+    uint32_t* blkoff;      // R + 2: first block of each level
+    // lists of one level: places that a round left (two in turn), places
+    // popped, and candidates in components entered (three words each)
+    uint32_t *U, *U2, *F, *X;
+    uint32_t* nodes;       // next pointers, six per waiting voxel
+    uint32_t* M;           // rank of each step (out)
+    uint32_t pcap, ecap, lcap, xcap, ncap;
+    uint32_t R;
+    uint32_t kb;           // bits of a round in the (level, round) codes
+    int32_t sx, sy;        // strides along x and y
+    uint32_t n, n_pore;
+    uint32_t max_steps;    // 0: no limit
+};
+constexpr uint32_t kTreeNone = 0xFFFFFFFFu;
+constexpr uint32_t kTreeClaimed = 0x80000000u;
+
+constexpr int kPeakWords = 9;   // words per peak: cpm 2, plo, mark, grp, er, head, lcnt, E
+constexpr int kEventWords = 16;  // words per event: gm .. bprev, and the two rank arrays
+constexpr int kLevelWords = 3;  // words per voxel of the largest level: U, U2, F
+constexpr int kPoreWords = 9;   // words per pore voxel: rec 8, dist
+// words of scratch for the caps of `a` (control words included)
+inline size_t tree_words(const TreeArgs& a) {
+    return (sizeof(TreeCtl) + 255) / 256 * 64 + (size_t)a.pcap * kPeakWords + (size_t)a.ecap * kEventWords +
+           (a.R + 2) + (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3 + (size_t)a.n_pore * kPoreWords + 2;
+}
+// lays the control words, peaks, events and lists out in w, and sets a.kb
+inline void tree_carve(TreeArgs& a, uint32_t* w) {
+    a.ctl = (TreeCtl*)w;
+    w += (sizeof(TreeCtl) + 255) / 256 * 64;
+    a.rec = (uint4*)w;
+    w += 8 * (size_t)a.n_pore;
+    a.dist = w;
+    w += (a.n_pore + 1u) / 2 * 2;
+    a.cpm = (uint2*)w;
+    w += 2 * (size_t)a.pcap;
+    a.rank0 = (uint2*)w;
+    w += 4 * (size_t)a.ecap;
+    a.rank1 = (uint2*)w;
+    w += 4 * (size_t)a.ecap;
+    for (uint32_t** p : {&a.plo, &a.mark, &a.grp, &a.er, &a.head, &a.lcnt, &a.E}) {
+        *p = w;
+        w += a.pcap;
+    }
+    for (uint32_t** p : {&a.gm, &a.gbase, &a.lastb, &a.bg, &a.bbase, &a.bcnt, &a.blev, &a.bprev}) {
+        *p = w;
+        w += a.ecap;
+    }
+    a.blkoff = w;
+    w += a.R + 2;
+    for (uint32_t** p : {&a.U, &a.U2, &a.F}) {
+        *p = w;
+        w += a.lcap;
+    }
+    a.X = w;
+    uint32_t levels = 0;
+    while ((a.R >> levels) != 0) levels++;
+    a.kb = 32 - levels;
+}
+// Calls stopped after fewer steps run the step loop.
+constexpr int64_t kTreeMinSteps = 1024;
+// Levels of at most this many voxels run in one workgroup (joins, searches).
+constexpr uint32_t kTreeSmallJoin = 256;
+constexpr uint32_t kTreeSmall = 2048;
+
+// key (ranks and neighbour bits from dt2), uf and top of every voxel, then the
+// pore voxels sorted by rank into list (cursors: the slice offsets), idx the inverse
+hipError_t launch_tree_convert(const uint8_t* image, uint32_t* key, const uint32_t* present_scanned, ibip_dims d,
+                               uint32_t vlimit, uint32_t* idx, uint32_t* uf, uint32_t* top, uint32_t* cursor,
+                               uint32_t* list, uint32_t R, hipStream_t s);
+// The whole invasion of one image: component tree, levels, step numbers.
+// off_host: the slice offsets (R + 2 entries). Leaves the step of each centre
+// in the memory of a.idx (0 elsewhere), a.M = ranks per step, ctl->K = steps
+// (or ctl->abort), and seq (the memory of a.top) = INT_MAX on pore, -1 on solid.
+hipError_t launch_tree(const TreeArgs& a, const uint32_t* off_host, const uint8_t* inlets, ibip_dims d, bool mask,
+                       int32_t* seq, hipStream_t s);
+// state (the memory of a.idx), seq and the slices as the step loop starts from
+hipError_t launch_tree_undo(const TreeArgs& a, int32_t* seq, uint32_t* head, uint32_t* tail, hipStream_t s);
+
+}  // namespace ibip
