@@ -108,10 +108,10 @@ ibip_status ibip_ctx_set_readings(ibip_ctx* ctx, uint32_t flags);
    size class by the package's autotuner; results never depend on them).
    edt_tile_y  z columns per LDS tile of the EDT's pass y: 32 or 64 (0: 32)
    edt_tile_x  z columns per LDS tile of the EDT's pass x: 16 or 32 (0: 32)
-   batch_wide  a batch job's step with more centres than this leaves the job's
-               workgroup: the step runs over the whole GPU and the job's loop
-               resumes in its own launch (0: never for ibip_invade_batch, 8192
-               for the server's jobs; negative: never).
+   batch_wide  where a job runs the step loop, a step with more centres than
+               this leaves the job's workgroup: the step runs over the whole GPU
+               and the job's loop resumes in its own launch (0: never for
+               ibip_invade_batch, 8192 for the server's jobs; negative: never).
    Errors: EINVAL (a tile width not listed). NULL restores the defaults. */
 typedef struct {
     int32_t edt_tile_y;
@@ -225,19 +225,22 @@ ibip_status ibip_invade_resume(ibip_ctx* ctx, const uint8_t* image, const uint8_
 /*
  * ibip_invade_batch -- ibip_invade (Section 2.1) over many images of uneven
  * size in one call, with the same results as one ibip_invade per image.
- * Each job names its own device buffers, dims and step limit; per-job setup
- * runs concurrently, the step loops of all jobs run in ONE launch (one
- * workgroup per job, largest first) and the call synchronises once between
- * the loops and the post-processing.
+ * Each job names its own device buffers, dims and step limit. The images share
+ * one component tree (in groups of up to 2^29 voxels, the smaller ones padded
+ * to the rows and planes of the largest), whose levels are searched for all of
+ * them together; a batch whose jobs all stop after fewer than 1,024 steps runs
+ * their step loops in one launch instead, one workgroup per job. A job's seq
+ * also holds intermediate values while the call runs.
  * Per job: status receives the job's ibip_status (OK, ENOSOLID, ECAPACITY,
  * EDEVICE) and n_steps its K. M (uint32) and sat (double) are optional DEVICE
  * outputs of the per-step squared radius and saturation, each with capacity
  * for at least as many entries as the image has pore voxels.
- * A job whose image has more than 8192 distinct distance values in its pore
- * space (more than a job's rank tables hold) runs after the batched launch,
- * alone, through the path of ibip_invade on the context's stream (same
- * results); that call replaces the context's per-step arrays, so
- * ibip_get_steps afterwards reports EINVAL until the next ibip_invade.
+ * Jobs that the batched paths cannot take (more than 8192 distinct distance
+ * values in the pore space of a group, or more peaks or steps than its tree
+ * has room for) run afterwards, alone, through the path of ibip_invade on the
+ * context's stream (same results); that call replaces the context's per-step
+ * arrays, so ibip_get_steps afterwards reports EINVAL until the next
+ * ibip_invade.
  * Returns IBIP_OK when every job succeeded, else the first failing job's code.
  */
 typedef struct {

@@ -1657,9 +1657,8 @@ __global__ void k_rank_to_value(uint32_t* M, int64_t K, const uint32_t* val) {
 // Each block finalises a contiguous chunk of kCntChunk voxels. With `copies`
 // given, the per-step counts of painted voxels go to copy blockIdx % ncopies
 // (copy c at copies + c * K), summed per block in LDS first.
-__global__ __launch_bounds__(256) void k_finalise(int32_t* seq, int32_t* state_io, bool map_state, int64_t n,
-                                                  const uint32_t* M, uint32_t* rad2, uint32_t* copies, int64_t K,
-                                                  int ncopies) {
+__global__ __launch_bounds__(256) void k_finalise(int32_t* seq, int64_t n, const uint32_t* M, uint32_t* rad2,
+                                                  uint32_t* copies, int64_t K, int ncopies) {
     __shared__ CountTable tab;
     const bool counting = copies != nullptr;
     if (counting) count_table_clear(tab);
@@ -1674,8 +1673,6 @@ __global__ __launch_bounds__(256) void k_finalise(int32_t* seq, int32_t* state_i
             s = seq[v];
             if (s == INT_MAX) { s = 0; seq[v] = 0; }
             if (rad2) rad2[v] = s > 0 ? M[s - 1] : 0u;
-            const int32_t t = state_io[v];
-            if (map_state && t < 0) state_io[v] = 0;
         }
         if (counting) count_table_add(tab, have && s > 0, s, copy);
     }
@@ -1709,19 +1706,18 @@ inline unsigned blocks(int64_t n, int t = 256) { return (unsigned)((n + t - 1) /
 // k_finalise over n voxels. With counts given (K > 0), counts[0..K) receives
 // the number of voxels of each step; `spare` holds the copies when there is
 // more than one (kCntCopies * K words, see count_copies).
-hipError_t launch_finalise(int32_t* seq, int32_t* state, int64_t n, const uint32_t* M, uint32_t* rad2,
-                           uint32_t* counts, uint32_t* spare, int64_t K, hipStream_t s) {
+hipError_t launch_finalise(int32_t* seq, int64_t n, const uint32_t* M, uint32_t* rad2, uint32_t* counts,
+                           uint32_t* spare, int64_t K, hipStream_t s) {
     const unsigned g = (unsigned)((n + kCntChunk - 1) / kCntChunk);
     if (!counts || K <= 0) {
-        hipLaunchKernelGGL(k_finalise, dim3(g), dim3(256), 0, s, seq, state, true, n, M, rad2, (uint32_t*)nullptr,
-                           (int64_t)0, 1);
+        hipLaunchKernelGGL(k_finalise, dim3(g), dim3(256), 0, s, seq, n, M, rad2, (uint32_t*)nullptr, (int64_t)0, 1);
         return hipGetLastError();
     }
     const int S = count_copies(K, n);
     uint32_t* dst = S > 1 ? spare : counts;
     hipError_t e = hipMemsetAsync(dst, 0, sizeof(uint32_t) * (size_t)S * (size_t)K, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finalise, dim3(g), dim3(256), 0, s, seq, state, true, n, M, rad2, dst, K, S);
+    hipLaunchKernelGGL(k_finalise, dim3(g), dim3(256), 0, s, seq, n, M, rad2, dst, K, S);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return S > 1 ? launch_sum_copies(spare, S, K, counts, s) : hipSuccess;
 }
@@ -1810,14 +1806,6 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
                             "copy")) != IBIP_OK)
             return rc;
         if ((rc = hip_check(ctx, hipEventRecord(ctx->copy_ev, s), "event")) != IBIP_OK) return rc;
-        if ((rc = hip_check(ctx, launch_tree_convert(image, key, present, d, (uint32_t)(V - 1),
-                                                     (uint32_t*)state, tmp32,
-                                                     (uint32_t*)seq, tail, bucket, R, s), "convert")) != IBIP_OK)
-            return rc;
-        if ((rc = hip_check(ctx, hipEventSynchronize(ctx->copy_ev), "sync")) != IBIP_OK) return rc;
-        uint32_t lcap = 0;
-        for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
-        ta = TreeArgs{};
         ta.key = key;
         ta.list = bucket;
         ta.off = off;
@@ -1826,18 +1814,19 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         ta.idx = (uint32_t*)state;
         ta.gu = full;
         ta.nodes = M;
-        ta.ncap = (uint32_t)(n_pore / 6);
         ta.M = M;
-        ta.pcap = (uint32_t)(n_pore / 8 + 4096);
-        ta.ecap = (uint32_t)(n_pore / 16 + 4096);
-        ta.lcap = lcap;
-        ta.xcap = lcap + 4096;
         ta.R = R;
         ta.sx = d.Y * d.Z;
         ta.sy = d.Z;
         ta.n = (uint32_t)n;
-        ta.n_pore = (uint32_t)n_pore;
-        ta.max_steps = opts ? (uint32_t)std::min<int64_t>(opts->max_steps, n_pore) : 0u;
+        if ((rc = hip_check(ctx, launch_tree_convert(ta, 0, image, key, key, present, d, (uint32_t)(V - 1), s),
+                            "convert")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, launch_tree_sort(ta, tail, bucket, s), "sort")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, hipEventSynchronize(ctx->copy_ev), "sync")) != IBIP_OK) return rc;
+        uint32_t lcap = 0;
+        for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
+        tree_caps(ta, (uint32_t)n_pore, 1, lcap);
         uint32_t* w = (uint32_t*)ensure(ctx, B_TREE, tree_words(ta) * sizeof(uint32_t));
         if (!w) return fail(ctx, IBIP_ENOMEM, "invade: scratch allocation failed");
         tree_carve(ta, w);
@@ -1857,19 +1846,26 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     bool treed = false;  // the tree gave the centres
     if (tree) {
         tm.mark(3, s);
-        if ((rc = hip_check(ctx, hipMemsetAsync(ta.ctl, 0, sizeof(TreeCtl), s), "memset")) != IBIP_OK) return rc;
-        if ((rc = hip_check(ctx, launch_tree(ta, h_off, inlets, d, (ctx->readings & IBIP_READ_MASK_INLETS) != 0, seq, s),
-                            "tree")) != IBIP_OK)
-            return rc;
-        tm.mark(4, s);
+        // the control words and the image's entry (there and back)
         TreeCtl* h_ctl = (TreeCtl*)((uint8_t*)h_st + 2048);
-        if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, sizeof(TreeCtl), hipMemcpyDeviceToHost, s), "copy")) !=
-            IBIP_OK)
+        TreeJob* h_job = (TreeJob*)(h_ctl + 1);
+        *h_ctl = TreeCtl{};
+        *h_job = TreeJob{0, 0, opts ? (uint32_t)std::min<int64_t>(opts->max_steps, n_pore) : 0u, 0};
+        const size_t head_bytes = sizeof(TreeCtl) + sizeof(TreeJob);
+        static_assert(sizeof(TreeCtl) + sizeof(TreeJob) <= 2048, "the tree's head fits beside the loop state");
+        const bool mask = (ctx->readings & IBIP_READ_MASK_INLETS) != 0;
+        if ((rc = hip_check(ctx, hipMemcpyAsync(ta.ctl, h_ctl, head_bytes, hipMemcpyHostToDevice, s), "copy")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, launch_tree_build(ta, h_off, s), "tree")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, launch_tree_seed(ta, 0, inlets, d, mask, s), "tree")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, launch_tree_levels(ta, h_off, seq, s), "tree")) != IBIP_OK) return rc;
+        tm.mark(4, s);
+        if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
             return rc;
         if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
         treed = !h_ctl->abort;
         if (treed) {
-            h_st->k = h_ctl->K + 1;
+            h_st->k = h_job->K + 1;
             h_st->popped = 0;
             for (uint32_t c : h_ctl->popped) h_st->popped += c;
             if (tm.on) {
@@ -2047,7 +2043,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     uint32_t* counts = (uint32_t*)ensure(ctx, B_TMP2, sizeof(uint32_t) * (2 * (K + 1) + ncopy));
     partials = (uint32_t*)ensure(ctx, B_SCAN, sizeof(uint32_t) * (V / 1000 + n / 1000 + 64));
     if (!n_new || !sat || !pc || !counts || !partials) return fail(ctx, IBIP_ENOMEM, "invade: scratch allocation failed");
-    if ((rc = hip_check(ctx, launch_finalise(seq, state, n, M, rad2, counts, counts + 2 * (K + 1), K, s),
+    if ((rc = hip_check(ctx, launch_finalise(seq, n, M, rad2, counts, counts + 2 * (K + 1), K, s),
                         "finalise")) != IBIP_OK)
         return rc;
     if (K > 0) {
@@ -2203,7 +2199,7 @@ hipError_t job_post(const JobBufs& j, LoopState* st, ibip_dims d, int64_t K, int
     // the job's counts region holds 2 (n + 1) words: counts, their scan and,
     // when used, the copies (at most n words, and then 2 K <= n)
     uint32_t* counts = j.counts;
-    if ((e = launch_finalise(seq, j.state, n, j.M, rad2, counts, counts ? counts + 2 * (K + 1) : nullptr,
+    if ((e = launch_finalise(seq, n, j.M, rad2, counts, counts ? counts + 2 * (K + 1) : nullptr,
                              counts ? K : 0, s)) != hipSuccess)
         return e;
     if (K > 0 && M_out)
@@ -2238,7 +2234,7 @@ hipError_t job_post_devk(const JobBufs& j, LoopState* st, ibip_dims d, int32_t* 
                  make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y)};
     hipLaunchKernelGGL(k_paint_shell, dim3(blocks(n)), dim3(256), 0, s, pa);
     hipLaunchKernelGGL(k_paint_full, dim3(std::min<int64_t>(blocks(n), 2048)), dim3(256), 0, s, pa);
-    return launch_finalise(seq, j.state, n, j.M, rad2, nullptr, nullptr, 0, s);
+    return launch_finalise(seq, n, j.M, rad2, nullptr, nullptr, 0, s);
 }
 
 hipError_t launch_loop_jobs(const void* d_args, int32_t n, hipStream_t s) {
@@ -2282,7 +2278,287 @@ void fill_loop_args(void* out, const JobBufs& j, LoopState* st, ibip_dims d, uin
     *(LoopArgs*)out = job_loop_args(j, st, d, wide);
 }
 
-ibip_status run_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
+// ---------------------------------------------------------------------------
+// A batch by the component tree: the images share one tree (TreeJob).
+// ---------------------------------------------------------------------------
+// Voxels of one common array; a larger batch is taken in several groups.
+constexpr int64_t kGroupVoxels = (int64_t)1 << 29;
+
+struct Group {
+    std::vector<int32_t> job;  // indices into the caller's jobs
+    int32_t Y = 0, Z = 0;      // of the common array: rows and planes of the largest, rounded up to 8
+    int64_t planes = 0;
+    static int32_t up8(int32_t v) { return (v + 7) / 8 * 8; }
+    int64_t voxels_with(ibip_dims d) const {
+        return (planes + d.X) * std::max(Y, up8(d.Y)) * (int64_t)std::max(Z, up8(d.Z));
+    }
+    void add(int32_t q, ibip_dims d) {
+        job.push_back(q);
+        planes += d.X;
+        Y = std::max(Y, up8(d.Y));
+        Z = std::max(Z, up8(d.Z));
+    }
+    int64_t voxels() const { return planes * Y * (int64_t)Z; }
+};
+
+// The image's part of the common array (its voxels, CY x CZ planes) to its own
+// layout: seq (still INT_MAX where nothing was painted) and, if wanted, the steps.
+static __global__ __launch_bounds__(256) void k_crop(const int32_t* __restrict__ seq_c,
+                                                     const uint32_t* __restrict__ step_c, int64_t n, FastDiv divZ,
+                                                     FastDiv divY, int CY, int CZ, int32_t* seq, int32_t* centre_step) {
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v >= n) return;
+    const uint32_t t = fdiv((uint32_t)v, divZ), x = fdiv(t, divY), y = t - x * divY.d, z = (uint32_t)v - t * divZ.d;
+    const int64_t c = ((int64_t)x * CY + y) * CZ + z;
+    seq[v] = seq_c[c];
+    if (centre_step) centre_step[v] = (int32_t)step_c[c];
+}
+
+// One group. Jobs whose results it cannot give (too many ranks or peaks for
+// the tree) are left in `alone`.
+static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g, std::vector<int32_t>& alone) {
+    hipStream_t s = ctx->stream;
+    const int32_t m = (int32_t)g.job.size();
+    const int S = kBatchStreams;
+    const int64_t nc = g.voxels();
+    auto dims = [&](int32_t j) { return jobs[g.job[j]].dims; };
+    int64_t V = 0;
+    std::vector<uint32_t> vox(m);
+    for (int64_t j = 0, x = 0; j < m; j++) {
+        V = std::max(V, value_range(dims((int32_t)j)));
+        vox[j] = (uint32_t)(x * g.Y * g.Z);
+        x += dims((int32_t)j).X;
+    }
+    ibip_status rc;
+    if ((rc = batch_streams(ctx)) != IBIP_OK) return rc;
+    // scratch that does not depend on the pore count
+    const size_t words[] = {(size_t)nc, (size_t)nc, (size_t)nc, (size_t)nc, 3 * (size_t)V, (size_t)V / 1000 + 64,
+                            kMaxRanks + 2, kMaxRanks + 2, kMaxRanks + 2, kMaxRanks + 2,
+                            sizeof(LoopState) / 4 * ((size_t)m + 1)};
+    size_t total = 0;
+    for (size_t w : words) total += align256(4 * w);
+    uint8_t* base = (uint8_t*)ensure(ctx, B_BATCH, total);
+    const size_t st_bytes = sizeof(LoopState) * ((size_t)m + 1), off_bytes = sizeof(uint32_t) * (kMaxRanks + 2);
+    uint8_t* h = (uint8_t*)pinned(ctx, std::max<size_t>(4096, align256(st_bytes) + align256(off_bytes) +
+                                                                  tree_head_bytes((uint32_t)m)));
+    if (!base || !h) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
+    size_t wi = 0;
+    auto take = [&]() {
+        uint32_t* p = (uint32_t*)base;
+        base += align256(4 * words[wi++]);
+        return p;
+    };
+    uint32_t *key = take(), *uf = take(), *top = take(), *idx = take(), *hist = take(), *partials = take(),
+             *val = take(), *off = take(), *head = take(), *tail = take();
+    LoopState* st = (LoopState*)take();
+    LoopState* all = st + m;  // ranks and pore voxels of the whole group
+    LoopState* h_st = (LoopState*)h;
+    uint32_t* h_off = (uint32_t*)(h + align256(st_bytes));
+    TreeCtl* h_ctl = (TreeCtl*)(h + align256(st_bytes) + align256(off_bytes));
+    TreeJob* h_job = (TreeJob*)(h_ctl + 1);
+    uint32_t *present = hist + V, *flags = hist + 2 * V;
+    // on every batch stream after the caller's stream, and back
+    auto fork = [&]() -> ibip_status {
+        ibip_status r;
+        if ((r = hip_check(ctx, hipEventRecord(ctx->bev[S], s), "event")) != IBIP_OK) return r;
+        for (int i = 0; i < S; i++)
+            if ((r = hip_check(ctx, hipStreamWaitEvent(ctx->bstream[i], ctx->bev[S], 0), "wait")) != IBIP_OK) return r;
+        return IBIP_OK;
+    };
+    auto join = [&]() -> ibip_status {
+        ibip_status r;
+        for (int i = 0; i < S; i++) {
+            if ((r = hip_check(ctx, hipEventRecord(ctx->bev[i], ctx->bstream[i]), "event")) != IBIP_OK) return r;
+            if ((r = hip_check(ctx, hipStreamWaitEvent(s, ctx->bev[i], 0), "wait")) != IBIP_OK) return r;
+        }
+        return IBIP_OK;
+    };
+    // an early return leaves nothing running on buffers that the next call reuses
+    struct Drain {
+        ibip_ctx* c;
+        ~Drain() {
+            for (hipStream_t b : c->bstream) (void)hipStreamSynchronize(b);
+        }
+    } drain{ctx};
+    // distances (into the caller's seq, free until the end; the passes' own
+    // arrays in the parts of uf and idx) and the common histogram
+    if ((rc = hip_check(ctx, fill_u32((uint32_t*)st, st_bytes / 4, 0u, s), "fill")) != IBIP_OK) return rc;
+    if ((rc = hip_check(ctx, fill_u32(hist, V, 0u, s), "fill")) != IBIP_OK) return rc;
+    if ((rc = fork()) != IBIP_OK) return rc;
+    const EdtTiles tiles = edt_tiles(ctx->tuning);
+    for (int32_t j = 0; j < m; j++) {
+        const ibip_job& jb = jobs[g.job[j]];
+        hipStream_t bs = ctx->bstream[j % S];
+        uint32_t* dt2 = (uint32_t*)jb.seq;
+        if ((rc = hip_check(ctx, launch_edt(jb.image, nullptr, 0, 0, jb.dims, (uint16_t*)(idx + vox[j]), uf + vox[j],
+                                            dt2, &st[j].solid_seen, bs, nullptr, nullptr, tiles), "edt")) != IBIP_OK)
+            return rc;
+        const int64_t n = nvox(jb.dims);
+        hipLaunchKernelGGL(k_hist, dim3(std::min<int64_t>(blocks(n), kHistBlocks)), dim3(256), 0, bs, dt2, n,
+                           (uint32_t)(V - 1), hist, st + j);
+    }
+    if ((rc = join()) != IBIP_OK) return rc;
+    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, hist, present, V);
+    hipLaunchKernelGGL(k_copy_u32, dim3(blocks(V)), dim3(256), 0, s, present, flags, V);
+    if ((rc = hip_check(ctx, launch_scan_u32(hist, V, partials, &all->n_pore, s), "scan")) != IBIP_OK) return rc;
+    if ((rc = hip_check(ctx, launch_scan_u32(present, V, partials, &all->R, s), "scan")) != IBIP_OK) return rc;
+    if ((rc = hip_check(ctx, hipMemcpyAsync(h_st, st, st_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
+        return rc;
+    if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+    const uint32_t R = h_st[m].R, n_pore = h_st[m].n_pore;
+    if (R == 0 || R > (uint32_t)kMaxRanks) {
+        alone.insert(alone.end(), g.job.begin(), g.job.end());
+        return IBIP_OK;
+    }
+    // common ranks, the common key, the sorted list
+    hipLaunchKernelGGL(k_rank_tables, dim3(blocks(V)), dim3(256), 0, s, hist, present, flags, V, val, off, head, tail,
+                       (uint32_t)kMaxRanks, all);
+    if ((rc = hip_check(ctx, hipMemcpyAsync(h_off, off, sizeof(uint32_t) * (R + 2), hipMemcpyDeviceToHost, s),
+                        "copy")) != IBIP_OK)
+        return rc;
+    TreeArgs ta{};
+    ta.key = key;
+    ta.off = off;
+    ta.uf = uf;
+    ta.top = top;
+    ta.idx = idx;
+    ta.R = R;
+    ta.sx = g.Y * g.Z;
+    ta.sy = g.Z;
+    ta.n = (uint32_t)nc;
+    for (int32_t j = 0; j < m; j++) {
+        const ibip_job& jb = jobs[g.job[j]];
+        if ((rc = hip_check(ctx, launch_tree_convert(ta, vox[j], jb.image, (const uint32_t*)jb.seq, key, present,
+                                                     jb.dims, (uint32_t)(V - 1), s), "convert")) != IBIP_OK)
+            return rc;
+    }
+    if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+    uint32_t lcap = 0;
+    for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
+    tree_caps(ta, n_pore, (uint32_t)m, lcap);
+    // list, thread of each place (then the full balls), M; the tree's own
+    const size_t pore_bytes = align256(4 * ((size_t)n_pore + 1));
+    uint8_t* tb = (uint8_t*)ensure(ctx, B_TREE, 3 * pore_bytes + 4 * tree_words(ta));
+    if (!tb) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
+    uint32_t* list = (uint32_t*)tb;
+    ta.list = list;
+    ta.gu = (uint32_t*)(tb + pore_bytes);
+    ta.M = ta.nodes = (uint32_t*)(tb + 2 * pore_bytes);
+    tree_carve(ta, (uint32_t*)(tb + 3 * pore_bytes));
+    *h_ctl = TreeCtl{};
+    for (uint32_t j = 0, at = 0; j < (uint32_t)m; j++) {
+        const int64_t lim = jobs[g.job[j]].max_steps;
+        h_job[j] = TreeJob{vox[j], at, (uint32_t)std::min<int64_t>(lim, n_pore), 0};
+        at += h_st[j].n_pore;
+    }
+    const size_t head_bytes = sizeof(TreeCtl) + sizeof(TreeJob) * (size_t)m;
+    Timer& tm = ctx->timer;
+    tm.mark(3, s);
+    if ((rc = hip_check(ctx, hipMemcpyAsync(ta.ctl, h_ctl, head_bytes, hipMemcpyHostToDevice, s), "copy")) != IBIP_OK)
+        return rc;
+    if ((rc = hip_check(ctx, launch_tree_sort(ta, tail, list, s), "sort")) != IBIP_OK) return rc;
+    if ((rc = hip_check(ctx, launch_tree_build(ta, h_off, s), "tree")) != IBIP_OK) return rc;
+    for (int32_t j = 0; j < m; j++) {
+        const ibip_job& jb = jobs[g.job[j]];
+        if ((rc = hip_check(ctx, launch_tree_seed(ta, vox[j], jb.inlets, jb.dims, false, s), "seed")) != IBIP_OK)
+            return rc;
+    }
+    int32_t* seq_c = (int32_t*)top;
+    if ((rc = hip_check(ctx, launch_tree_levels(ta, h_off, seq_c, s), "tree")) != IBIP_OK) return rc;
+    tm.mark(4, s);
+    if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
+        return rc;
+    if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+    if (tm.on) {
+        ctx->timing.loop_kernel_ms += tm.ms(3, 4);
+        ctx->timing.loop_launches++;
+    }
+    if (h_ctl->abort) {
+        alone.insert(alone.end(), g.job.begin(), g.job.end());
+        return IBIP_OK;
+    }
+    // insertion, in each image's part of the common array, and its outputs
+    std::vector<size_t> cnt_at(m, 0);
+    size_t cnt_words = 64;
+    for (int32_t j = 0; j < m; j++) {
+        ibip_job& jb = jobs[g.job[j]];
+        jb.status = h_st[j].solid_seen ? IBIP_OK : IBIP_ENOSOLID;
+        jb.n_steps = h_st[j].solid_seen ? h_job[j].K : 0;
+        if (!jb.sat || jb.n_steps == 0) continue;
+        const int64_t K = jb.n_steps, n = nvox(jb.dims);
+        cnt_at[j] = cnt_words;
+        cnt_words += 2 * (size_t)K + (count_copies(K, n) > 1 ? (size_t)kCntCopies * K : 0) + K / 1000 + 64;
+    }
+    uint32_t* cnt = (uint32_t*)ensure(ctx, B_TMP2, sizeof(uint32_t) * cnt_words);
+    if (!cnt) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
+    if ((rc = fork()) != IBIP_OK) return rc;
+    for (int32_t j = 0; j < m; j++) {
+        ibip_job& jb = jobs[g.job[j]];
+        if (jb.status != IBIP_OK) continue;
+        hipStream_t bs = ctx->bstream[j % S];
+        const int64_t n = nvox(jb.dims), K = jb.n_steps;
+        uint32_t* M = ta.M + h_job[j].m;
+        if (K > 0) hipLaunchKernelGGL(k_rank_to_value, dim3(blocks(K)), dim3(256), 0, bs, M, K, val);
+        PaintArgs pa{(const int32_t*)idx + vox[j], key + vox[j], val, seq_c + vox[j], ta.gu + h_job[j].m,
+                     &st[j].n_full, jb.dims.X, g.Y, g.Z, false, make_fastdiv((uint32_t)g.Z),
+                     make_fastdiv((uint32_t)g.Y)};
+        const int64_t nj = (int64_t)jb.dims.X * ta.sx;
+        hipLaunchKernelGGL(k_paint_shell, dim3(blocks(nj)), dim3(256), 0, bs, pa);
+        hipLaunchKernelGGL(k_paint_full, dim3(std::min<int64_t>(blocks(nj), 2048)), dim3(256), 0, bs, pa);
+        hipLaunchKernelGGL(k_crop, dim3(blocks(n)), dim3(256), 0, bs, pa.seq, idx + vox[j], n,
+                           make_fastdiv((uint32_t)jb.dims.Z), make_fastdiv((uint32_t)jb.dims.Y), g.Y, g.Z, jb.seq,
+                           jb.centre_step);
+        uint32_t* counts = cnt_at[j] ? cnt + cnt_at[j] : nullptr;
+        uint32_t* excl = counts ? counts + K : nullptr;
+        uint32_t* part = counts ? excl + K : nullptr;  // scan partials, the scan's total last
+        uint32_t* spare = counts ? part + K / 1000 + 64 : nullptr;
+        if ((rc = hip_check(ctx, launch_finalise(jb.seq, n, M, jb.rad2, counts, spare, counts ? K : 0, bs),
+                            "finalise")) != IBIP_OK)
+            return rc;
+        if (K > 0 && jb.M)
+            hipLaunchKernelGGL(k_copy_u32, dim3(blocks(K)), dim3(256), 0, bs, M, jb.M, K);
+        if (counts) {
+            hipLaunchKernelGGL(k_copy_u32, dim3(blocks(K)), dim3(256), 0, bs, counts, excl, K);
+            if ((rc = hip_check(ctx, launch_scan_u32(excl, K, part, part + K / 1000 + 63, bs), "scan")) != IBIP_OK)
+                return rc;
+            hipLaunchKernelGGL(k_sat, dim3(blocks(K)), dim3(256), 0, bs, counts, excl, K, st + j, jb.sat);
+        }
+        if ((rc = hip_check(ctx, hipGetLastError(), "batch post")) != IBIP_OK) return rc;
+    }
+    if ((rc = join()) != IBIP_OK) return rc;
+    return hip_check(ctx, hipStreamSynchronize(s), "sync");
+}
+
+// Jobs that the batched paths leave, one after another on the context's
+// stream with the batch's readings (none); that replaces the context's
+// per-step arrays, so ibip_get_steps then refers to no call.
+static void run_alone(ibip_ctx* ctx, ibip_job* jobs, const std::vector<int32_t>& alone, ibip_status& first) {
+    hipStream_t s = ctx->stream;
+    const uint32_t readings = ctx->readings;
+    ctx->readings = 0;
+    for (int32_t q : alone) {
+        ibip_job& jb = jobs[q];
+        ibip_invade_opts o{};
+        o.max_steps = jb.max_steps;
+        int64_t K = 0;
+        ibip_status r = run_invade(ctx, jb.image, jb.inlets, jb.dims, &o, jb.seq, jb.rad2, jb.centre_step, &K);
+        if (r == IBIP_OK && K > 0 && jb.M)
+            r = hip_check(ctx, hipMemcpyAsync(jb.M, ctx->buf[B_M].p, sizeof(uint32_t) * K, hipMemcpyDeviceToDevice, s),
+                          "copy");
+        if (r == IBIP_OK && K > 0 && jb.sat)
+            r = hip_check(ctx, hipMemcpyAsync(jb.sat, ctx->buf[B_SAT].p, sizeof(double) * K, hipMemcpyDeviceToDevice,
+                                              s), "copy");
+        if (r == IBIP_OK) r = hip_check(ctx, hipStreamSynchronize(s), "sync");
+        jb.status = r;
+        jb.n_steps = r == IBIP_OK ? K : 0;
+        if (r != IBIP_OK && first == IBIP_OK) first = r;
+    }
+    ctx->readings = readings;
+    ctx->have_steps = false;
+}
+
+// The step loops of a batch whose jobs all stop after few steps.
+static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
     hipStream_t s0 = ctx->stream;
     // largest jobs first: their loops are the longest
     std::vector<int32_t> order(nj);
@@ -2531,33 +2807,38 @@ ibip_status run_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
         if ((rc = hip_check(ctx, hipStreamWaitEvent(s0, ctx->bev[i], 0), "wait")) != IBIP_OK) return rc;
     }
     if ((rc = hip_check(ctx, hipStreamSynchronize(s0), "sync")) != IBIP_OK) return rc;
-    // the jobs with too many ranks for the batch's tables take the
-    // single-image path (its global-memory loop), one after another on the
-    // context's stream, with the batch's readings (none); that replaces the
-    // context's per-step arrays, so ibip_get_steps then refers to no call
-    if (!alone.empty()) {
-        const uint32_t readings = ctx->readings;
-        ctx->readings = 0;
-        for (int32_t q : alone) {
-            ibip_job& jb = jobs[order[q]];
-            ibip_invade_opts o{};
-            o.max_steps = jb.max_steps;
-            int64_t K = 0;
-            ibip_status r = run_invade(ctx, jb.image, jb.inlets, jb.dims, &o, jb.seq, jb.rad2, jb.centre_step, &K);
-            if (r == IBIP_OK && K > 0 && jb.M)
-                r = hip_check(ctx, hipMemcpyAsync(jb.M, ctx->buf[B_M].p, sizeof(uint32_t) * K,
-                                                  hipMemcpyDeviceToDevice, s0), "copy");
-            if (r == IBIP_OK && K > 0 && jb.sat)
-                r = hip_check(ctx, hipMemcpyAsync(jb.sat, ctx->buf[B_SAT].p, sizeof(double) * K,
-                                                  hipMemcpyDeviceToDevice, s0), "copy");
-            if (r == IBIP_OK) r = hip_check(ctx, hipStreamSynchronize(s0), "sync");
-            jb.status = r;
-            jb.n_steps = r == IBIP_OK ? K : 0;
-            if (r != IBIP_OK && first == IBIP_OK) first = r;
+    // the jobs with too many ranks for the batch's tables
+    for (int32_t& q : alone) q = order[q];
+    if (!alone.empty()) run_alone(ctx, jobs, alone, first);
+    if (first != IBIP_OK) return fail(ctx, first, "invade_batch: at least one job failed (see its status)");
+    return IBIP_OK;
+}
+
+ibip_status run_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
+    bool few = true;
+    for (int32_t i = 0; i < nj; i++) few = few && jobs[i].max_steps > 0 && jobs[i].max_steps < kTreeMinSteps;
+    if (few) return run_batch_loops(ctx, jobs, nj);
+    // largest first, so that a group's images are of like size
+    std::vector<int32_t> order(nj), alone;
+    for (int32_t i = 0; i < nj; i++) order[i] = i;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int32_t a, int32_t b) { return nvox(jobs[a].dims) > nvox(jobs[b].dims); });
+    Group g;
+    ibip_status rc;
+    for (int32_t q : order) {
+        if (!g.job.empty() && g.voxels_with(jobs[q].dims) > kGroupVoxels) {
+            if ((rc = run_batch_group(ctx, jobs, g, alone)) != IBIP_OK) return rc;
+            g = Group{};
         }
-        ctx->readings = readings;
-        ctx->have_steps = false;
+        if (g.voxels_with(jobs[q].dims) > kGroupVoxels) alone.push_back(q);
+        else g.add(q, jobs[q].dims);
     }
+    if (!g.job.empty() && (rc = run_batch_group(ctx, jobs, g, alone)) != IBIP_OK) return rc;
+    ibip_status first = IBIP_OK;
+    if (!alone.empty()) run_alone(ctx, jobs, alone, first);
+    first = IBIP_OK;
+    for (int32_t q : order)
+        if (jobs[q].status != IBIP_OK && first == IBIP_OK) first = (ibip_status)jobs[q].status;
     if (first != IBIP_OK) return fail(ctx, first, "invade_batch: at least one job failed (see its status)");
     return IBIP_OK;
 }

@@ -35,12 +35,26 @@ struct TreeCtl {
     uint32_t ucnt[kTreePulls + 2];  // voxels that round r of the current level left
     uint32_t xcnt[2]; // candidates claimed at the current level; the two in turn
     uint32_t abort;   // a capacity was exceeded: the step loop runs instead
-    uint32_t K;       // steps, after the step limit
+    uint32_t pad;
     uint32_t popped[kCountSlots];  // centres, by block
+};
+static_assert(sizeof(TreeCtl) % 8 == 0, "the images' entries follow the control words");
+
+// One image of a tree. A batch's images share one tree: they lie one after
+// another along x in a common array of (sum of X) x Y x Z voxels (Y and Z those
+// of the largest, the rest solid), take their ranks from one table, and each
+// is entered as a thread of its own, so they are searched level by level
+// together and numbered apart.
+struct TreeJob {
+    uint32_t vox;        // first voxel in the common array
+    uint32_t m;          // first entry in M
+    uint32_t max_steps;  // 0: no limit
+    uint32_t K;          // out: steps
 };
 
 struct TreeArgs {
     TreeCtl* ctl;
+    TreeJob* jobs;       // njobs; event j < njobs is the root of image j
     const uint32_t* key;
     const uint32_t* list;  // pore voxels by rank: rank r at off[r] .. off[r + 1]
     const uint32_t* off;
@@ -70,8 +84,7 @@ struct TreeArgs {
     uint32_t R;
     uint32_t kb;           // bits of a round in the (level, round) codes
     int32_t sx, sy;        // strides along x and y
-    uint32_t n, n_pore;
-    uint32_t max_steps;    // 0: no limit
+    uint32_t n, n_pore, njobs;
 };
 constexpr uint32_t kTreeNone = 0xFFFFFFFFu;
 constexpr uint32_t kTreeClaimed = 0x80000000u;
@@ -80,15 +93,18 @@ constexpr int kPeakWords = 9;   // words per peak: cpm 2, plo, mark, grp, er, he
 constexpr int kEventWords = 16;  // words per event: gm .. bprev, and the two rank arrays
 constexpr int kLevelWords = 3;  // words per voxel of the largest level: U, U2, F
 constexpr int kPoreWords = 9;   // words per pore voxel: rec 8, dist
-// words of scratch for the caps of `a` (control words included)
+// bytes of the control words and the images' entries, which start the scratch
+inline size_t tree_head_bytes(uint32_t njobs) { return align256(sizeof(TreeCtl) + sizeof(TreeJob) * (size_t)njobs); }
+// words of scratch for the caps of `a`
 inline size_t tree_words(const TreeArgs& a) {
-    return (sizeof(TreeCtl) + 255) / 256 * 64 + (size_t)a.pcap * kPeakWords + (size_t)a.ecap * kEventWords +
-           (a.R + 2) + (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3 + (size_t)a.n_pore * kPoreWords + 2;
+    return tree_head_bytes(a.njobs) / 4 + (size_t)a.pcap * kPeakWords + (size_t)a.ecap * kEventWords + (a.R + 2) +
+           (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3 + (size_t)a.n_pore * kPoreWords + 2;
 }
 // lays the control words, peaks, events and lists out in w, and sets a.kb
 inline void tree_carve(TreeArgs& a, uint32_t* w) {
     a.ctl = (TreeCtl*)w;
-    w += (sizeof(TreeCtl) + 255) / 256 * 64;
+    a.jobs = (TreeJob*)(a.ctl + 1);
+    w += tree_head_bytes(a.njobs) / 4;
     a.rec = (uint4*)w;
     w += 8 * (size_t)a.n_pore;
     a.dist = w;
@@ -124,17 +140,36 @@ constexpr int64_t kTreeMinSteps = 1024;
 constexpr uint32_t kTreeSmallJoin = 256;
 constexpr uint32_t kTreeSmall = 2048;
 
-// key (ranks and neighbour bits from dt2), uf and top of every voxel, then the
-// pore voxels sorted by rank into list (cursors: the slice offsets), idx the inverse
-hipError_t launch_tree_convert(const uint8_t* image, uint32_t* key, const uint32_t* present_scanned, ibip_dims d,
-                               uint32_t vlimit, uint32_t* idx, uint32_t* uf, uint32_t* top, uint32_t* cursor,
-                               uint32_t* list, uint32_t R, hipStream_t s);
-// The whole invasion of one image: component tree, levels, step numbers.
-// off_host: the slice offsets (R + 2 entries). Leaves the step of each centre
-// in the memory of a.idx (0 elsewhere), a.M = ranks per step, ctl->K = steps
-// (or ctl->abort), and seq (the memory of a.top) = INT_MAX on pore, -1 on solid.
-hipError_t launch_tree(const TreeArgs& a, const uint32_t* off_host, const uint8_t* inlets, ibip_dims d, bool mask,
-                       int32_t* seq, hipStream_t s);
+// The scratch's caps for n_pore pore voxels in njobs images, the largest level
+// of lcap voxels. More peaks, events or candidates than that and the tree gives
+// up (a blurred-noise or grain image has 60 to 300 pore voxels per peak).
+inline void tree_caps(TreeArgs& a, uint32_t n_pore, uint32_t njobs, uint32_t lcap) {
+    a.n_pore = n_pore;
+    a.njobs = njobs;
+    a.pcap = n_pore / 8 + 4096;
+    a.ecap = n_pore / 16 + 4096 + njobs;
+    a.lcap = lcap;
+    a.xcap = lcap + 4096;
+    a.ncap = n_pore / 6;
+}
+// key (ranks and neighbour bits from dt2), uf and top of the voxels of an image
+// of dims d at voxel `vox` of the common array, whose strides are a's.
+hipError_t launch_tree_convert(const TreeArgs& a, uint32_t vox, const uint8_t* image, const uint32_t* dt2,
+                               uint32_t* key, const uint32_t* present_scanned, ibip_dims d, uint32_t vlimit,
+                               hipStream_t s);
+// the pore voxels sorted by rank into a.list (cursors: the slice offsets), a.idx the inverse
+hipError_t launch_tree_sort(const TreeArgs& a, uint32_t* cursor, uint32_t* list, hipStream_t s);
+// The component tree and what the levels need of it.
+// off_host: the slice offsets (R + 2 entries).
+hipError_t launch_tree_build(const TreeArgs& a, const uint32_t* off_host, hipStream_t s);
+// the seeds of the image of dims d at voxel `vox`
+hipError_t launch_tree_seed(const TreeArgs& a, uint32_t vox, const uint8_t* inlets, ibip_dims d, bool mask,
+                            hipStream_t s);
+// The levels and the steps' numbers. Leaves the step of each centre in the
+// memory of a.idx (0 elsewhere), the images' ranks per step in a.M, their steps
+// in a.jobs (or ctl->abort), and seq (the memory of a.top) = INT_MAX on pore,
+// -1 on solid.
+hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off_host, int32_t* seq, hipStream_t s);
 // state (the memory of a.idx), seq and the slices as the step loop starts from
 hipError_t launch_tree_undo(const TreeArgs& a, int32_t* seq, uint32_t* head, uint32_t* tail, hipStream_t s);
 

@@ -125,25 +125,31 @@ __device__ inline int32_t nb_off(const TreeArgs& a, int d) {
 // ---------------------------------------------------------------------------
 // Setup
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_tree_convert(const uint8_t* __restrict__ img, uint32_t* key,
+// c: a voxel of the image's part of the common array (X x CY x CZ, the image
+// in its corner, solid around it)
+__global__ __launch_bounds__(256) void k_tree_convert(TreeArgs a, uint32_t vox, const uint8_t* __restrict__ img,
+                                                      const uint32_t* dt2, uint32_t* key,
                                                       const uint32_t* __restrict__ present_scanned, uint32_t n,
-                                                      uint32_t vlimit, uint32_t* idx, uint32_t* uf, uint32_t* top,
-                                                      int X, int Y, int Z, FastDiv divZ, FastDiv divY, uint32_t rcap) {
-    const uint32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v >= n) return;
-    uf[v] = v;
-    top[v] = kNone;
+                                                      uint32_t vlimit, int X, int Y, int Z, FastDiv divCZ,
+                                                      FastDiv divCY) {
+    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= n) return;
+    const uint32_t q = fdiv(c, divCZ), x = fdiv(q, divCY), y = q - x * divCY.d, z = c - q * divCZ.d;
+    const uint32_t g = vox + c;
+    a.uf[g] = g;
+    a.top[g] = kNone;
     uint32_t k = 0;
-    if (img[v]) {
-        const uint32_t d = key[v];
-        // d >= vlimit only without any solid voxel; such images are rejected
-        const uint32_t rk = d < vlimit ? present_scanned[d] + 1 : 0u;
-        const uint32_t t = fdiv(v, divZ), xx = fdiv(t, divY);
-        const uint32_t nb = nb_bits(xx, t - xx * (uint32_t)Y, v - t * (uint32_t)Z, X, Y, Z);
-        k = rk > rcap ? 0u : rk | (nb << kNbShift);
+    if (y < (uint32_t)Y && z < (uint32_t)Z) {
+        const uint32_t v = (x * (uint32_t)Y + y) * (uint32_t)Z + z;
+        if (img[v]) {
+            const uint32_t d = dt2[v];
+            // d >= vlimit only without any solid voxel; such images are rejected
+            const uint32_t rk = d < vlimit ? present_scanned[d] + 1 : 0u;
+            k = rk == 0 || rk > a.R ? 0u : rk | (nb_bits(x, y, z, X, Y, Z) << kNbShift);
+        }
     }
-    if ((k & kRankMask) == 0) idx[v] = kNone;
-    key[v] = k;
+    if (k == 0) a.idx[g] = kNone;
+    key[g] = k;
 }
 
 // The pore voxels into their ranks' slices. A block counts the ranks of its
@@ -340,6 +346,7 @@ __global__ __launch_bounds__(256) void k_tree_peaks(TreeArgs a) {
         if (root) {
             if (i < a.pcap) {
                 a.top[v] = i;
+                a.plo[i] = v;
                 a.cpm[i] = make_uint2(0u, i);
                 peak_init(a, i);
             } else {
@@ -462,38 +469,48 @@ __device__ inline void tree_candidate(const TreeArgs& a, uint32_t w, uint32_t t0
 
 // Seeds: Q0 = (inlets U their face neighbours) restricted to pore.
 // mask: a solid inlet voxel (rank 0) seeds nothing (the masked reading).
-__global__ __launch_bounds__(256) void k_tree_seed(TreeArgs a, const uint8_t* __restrict__ inlets, int X, int Y, int Z,
-                                                   FastDiv divZ, FastDiv divY, bool mask) {
+__global__ __launch_bounds__(256) void k_tree_seed(TreeArgs a, uint32_t vox, const uint8_t* __restrict__ inlets,
+                                                   uint32_t n, int X, int Y, int Z, FastDiv divZ, FastDiv divY,
+                                                   bool mask) {
     if (a.ctl->abort) return;
     const uint32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v >= a.n || inlets[v] == 0) return;
-    if (mask && (a.key[v] & kRankMask) == 0) return;
+    if (v >= n || inlets[v] == 0) return;
+    const uint32_t t = fdiv(v, divZ), x = fdiv(t, divY), y = t - x * (uint32_t)Y, z = v - t * (uint32_t)Z;
+    const uint32_t c = vox + x * (uint32_t)a.sx + y * (uint32_t)a.sy + z;
+    if (mask && (a.key[c] & kRankMask) == 0) return;
     // (a solid inlet voxel's key holds no neighbour bits)
-    const uint32_t t = fdiv(v, divZ), xx = fdiv(t, divY);
-    const uint32_t nb = nb_bits(xx, t - xx * (uint32_t)Y, v - t * (uint32_t)Z, X, Y, Z);
+    const uint32_t nb = nb_bits(x, y, z, X, Y, Z);
 #pragma unroll
     for (int j = 0; j < 7; j++) {
         if (j > 0 && !((nb >> (j - 1)) & 1u)) continue;
-        const uint32_t u = j == 0 ? v : v + (uint32_t)nb_off(a, j - 1);
+        const uint32_t u = j == 0 ? c : c + (uint32_t)nb_off(a, j - 1);
         if ((a.key[u] & kRankMask) != 0) tree_candidate(a, u, 0);
     }
 }
 
-// thread 0: the components of the lowest level that hold a seed
-__device__ inline void tree_start(const TreeArgs& a, uint32_t tid, uint32_t nth) {
-    const uint32_t nm = a.ctl->nmerge, nr = a.ctl->nroot;
-    for (uint32_t i = nm + tid; i < nm + nr; i += nth)
-        if (ld(&a.mark[i]) >= 1u) st(&a.grp[i], 0u);
-    if (tid == 0) {
-        a.ctl->nev = 1;
-        st(&a.lastb[0], kNone);
-        st(&a.gm[0], 0u);
-        a.blkoff[1] = 0;
-    }
-}
+// The images' threads: the components of the lowest level that hold a seed.
 __global__ __launch_bounds__(256) void k_tree_start(TreeArgs a) {
     if (a.ctl->abort) return;
-    tree_start(a, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+    const uint32_t tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
+    const uint32_t nm = a.ctl->nmerge, nr = a.ctl->nroot;
+    for (uint32_t i = nm + tid; i < nm + nr; i += nth) {
+        if (a.mark[i] < 1u) continue;
+        uint32_t lo = 0, hi = a.njobs;  // the last image that starts at or before the peak
+        while (hi - lo > 1) {
+            const uint32_t m = (lo + hi) / 2;
+            if (a.jobs[m].vox <= a.plo[i]) lo = m;
+            else hi = m;
+        }
+        a.grp[i] = lo;
+    }
+    for (uint32_t j = tid; j < a.njobs; j += nth) {
+        a.lastb[j] = kNone;
+        a.gm[j] = 0u;
+    }
+    if (tid == 0) {
+        a.ctl->nev = a.njobs;
+        a.blkoff[1] = 0;
+    }
 }
 
 // round in which component `pid` (of level t + 1) was entered at level t,
@@ -1034,13 +1051,14 @@ __global__ __launch_bounds__(kWg) void k_tree_levels(TreeArgs a, uint32_t t_lo, 
 // 1 + log2(2 events) passes over all events (levels of parents and children one
 // after another took 3.8 ms on 512^3 blurred noise).
 // rank[2e]: down of event e, rank[2e + 1]: up; x = the next of the tour
-// (itself at the end), y = downs from here to before x.
+// (itself at the end, the up of the image's root), y = downs from here to
+// before x.
 __global__ __launch_bounds__(256) void k_tree_tour(TreeArgs a) {
     if (a.ctl->abort) return;
     const uint32_t nb = a.ctl->nblk;
-    for (uint32_t b = blockIdx.x * 256 + threadIdx.x; b <= nb; b += gridDim.x * 256) {
-        // (the root event stands in for a block of its own)
-        const uint32_t base = b < nb ? a.bbase[b] : 0u, cnt = b < nb ? a.bcnt[b] : 1u;
+    for (uint32_t b = blockIdx.x * 256 + threadIdx.x; b < nb + a.njobs; b += gridDim.x * 256) {
+        // (each image's root event stands in for a block of its own)
+        const uint32_t base = b < nb ? a.bbase[b] : b - nb, cnt = b < nb ? a.bcnt[b] : 1u;
         for (uint32_t q = 0; q < cnt; q++) {
             const uint32_t e = base + q, child = a.lastb[e];
             a.rank0[2 * e] = make_uint2(child != kNone ? 2 * a.bbase[child] : 2 * e + 1, 1u);
@@ -1059,17 +1077,27 @@ __global__ __launch_bounds__(256) void k_tree_jump(TreeArgs a, const uint2* __re
         out[i] = make_uint2(q.x, p.x == i ? p.y : p.y + q.y);
     }
 }
+// an event's image and step, from the list ranking
+__device__ inline uint32_t event_step(const TreeArgs& a, const uint2* rank, uint32_t e, uint32_t& job) {
+    const uint2 r = rank[2 * (uint64_t)e];
+    job = r.x >> 1;
+    return rank[2 * (uint64_t)job].y - r.y;
+}
+
 // the ranks per step
 __global__ __launch_bounds__(256) void k_tree_steps(TreeArgs a, const uint2* __restrict__ rank) {
     if (a.ctl->abort) return;
-    const uint32_t nb = a.ctl->nblk, nev = a.ctl->nev, lim = a.max_steps ? a.max_steps : kNone;
-    const uint32_t tid = blockIdx.x * 256 + threadIdx.x;
-    if (tid == 0) a.ctl->K = min(nev - 1, lim);
-    for (uint32_t b = tid; b < nb; b += gridDim.x * 256) {
+    const uint32_t nb = a.ctl->nblk, tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
+    for (uint32_t j = tid; j < a.njobs; j += nth) {
+        const uint32_t K = rank[2 * (uint64_t)j].y - 1, lim = a.jobs[j].max_steps;
+        a.jobs[j].K = lim ? min(K, lim) : K;
+    }
+    for (uint32_t b = tid; b < nb; b += nth) {
         const uint32_t base = a.bbase[b], cnt = a.bcnt[b], t = a.blev[b];
         for (uint32_t q = 0; q < cnt; q++) {
-            const uint32_t k = nev - rank[2 * (base + q)].y;
-            if (k <= lim) a.M[k - 1] = t;
+            uint32_t j;
+            const uint32_t k = event_step(a, rank, base + q, j), lim = a.jobs[j].max_steps;
+            if (lim == 0 || k <= lim) a.M[a.jobs[j].m + k - 1] = t;
         }
     }
 }
@@ -1077,14 +1105,19 @@ __global__ __launch_bounds__(256) void k_tree_steps(TreeArgs a, const uint2* __r
 // idx becomes the steps (0 past the step limit); seq: INT_MAX on pore, -1 on solid
 __global__ __launch_bounds__(256) void k_tree_finish(TreeArgs a, const uint2* __restrict__ rank, int32_t* seq) {
     if (a.ctl->abort) return;
-    const uint32_t nev = a.ctl->nev;
     uint32_t centres = 0;
     for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < a.n; v += gridDim.x * 256) {
         const uint32_t i = a.idx[v];
-        // (a candidate's flag is gone once it is popped, as every candidate is)
+        // (a candidate's flag is gone once it is popped, as every candidate is;
+        // the images' roots, events below njobs, hold no voxel)
         const uint32_t e = i != kNone ? a.dist[i] : 0u;
-        uint32_t k = e ? nev - rank[2 * (uint64_t)e].y : 0u;
-        if (a.max_steps && k > a.max_steps) k = 0;
+        uint32_t k = 0;
+        if (e) {
+            uint32_t j;
+            k = event_step(a, rank, e, j);
+            const uint32_t lim = a.jobs[j].max_steps;
+            if (lim && k > lim) k = 0;
+        }
         centres += k ? 1u : 0u;
         a.idx[v] = k;
         seq[v] = i != kNone ? INT_MAX : -1;
@@ -1104,20 +1137,23 @@ inline unsigned blocks(uint64_t n, unsigned t = 256) { return (unsigned)((n + t 
 
 }  // namespace
 
-hipError_t launch_tree_convert(const uint8_t* image, uint32_t* key, const uint32_t* present_scanned, ibip_dims d,
-                               uint32_t vlimit, uint32_t* idx, uint32_t* uf, uint32_t* top, uint32_t* cursor,
-                               uint32_t* list, uint32_t R, hipStream_t s) {
-    const uint32_t n = (uint32_t)nvox(d);
-    hipLaunchKernelGGL(k_tree_convert, dim3(blocks(n)), dim3(256), 0, s, image, key, present_scanned, n, vlimit, idx,
-                       uf, top, d.X, d.Y, d.Z, make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y), R);
-    const uint32_t chunk = n > (1u << 24) ? 16384u : n > (1u << 21) ? 4096u : 1024u;
-    hipLaunchKernelGGL(k_tree_sort, dim3(blocks(n, chunk)), dim3(256), sizeof(uint32_t) * (R + 1), s, key, n, chunk, R,
-                       cursor, list, idx);
+hipError_t launch_tree_convert(const TreeArgs& a, uint32_t vox, const uint8_t* image, const uint32_t* dt2,
+                               uint32_t* key, const uint32_t* present_scanned, ibip_dims d, uint32_t vlimit,
+                               hipStream_t s) {
+    const uint32_t n = (uint32_t)d.X * (uint32_t)a.sx;
+    hipLaunchKernelGGL(k_tree_convert, dim3(blocks(n)), dim3(256), 0, s, a, vox, image, dt2, key, present_scanned, n,
+                       vlimit, d.X, d.Y, d.Z, make_fastdiv((uint32_t)a.sy), make_fastdiv((uint32_t)(a.sx / a.sy)));
     return hipGetLastError();
 }
 
-hipError_t launch_tree(const TreeArgs& a, const uint32_t* off, const uint8_t* inlets, ibip_dims d, bool mask,
-                       int32_t* seq, hipStream_t s) {
+hipError_t launch_tree_sort(const TreeArgs& a, uint32_t* cursor, uint32_t* list, hipStream_t s) {
+    const uint32_t chunk = a.n > (1u << 24) ? 16384u : a.n > (1u << 21) ? 4096u : 1024u;
+    hipLaunchKernelGGL(k_tree_sort, dim3(blocks(a.n, chunk)), dim3(256), sizeof(uint32_t) * (a.R + 1), s, a.key, a.n,
+                       chunk, a.R, cursor, list, a.idx);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_build(const TreeArgs& a, const uint32_t* off, hipStream_t s) {
     auto size = [&](uint32_t t) { return off[t + 1] - off[t]; };
     // phase 1
     for (uint32_t t = a.R; t >= 1;) {
@@ -1135,9 +1171,19 @@ hipError_t launch_tree(const TreeArgs& a, const uint32_t* off, const uint8_t* in
     hipLaunchKernelGGL(k_tree_parents, dim3(std::min(blocks(a.pcap), 1024u)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_tree_tops, dim3(blocks(a.n)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_tree_records, dim3(blocks(a.n)), dim3(256), 0, s, a);
-    // phase 2
-    hipLaunchKernelGGL(k_tree_seed, dim3(blocks(a.n)), dim3(256), 0, s, a, inlets, d.X, d.Y, d.Z,
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_seed(const TreeArgs& a, uint32_t vox, const uint8_t* inlets, ibip_dims d, bool mask,
+                            hipStream_t s) {
+    const uint32_t n = (uint32_t)nvox(d);
+    hipLaunchKernelGGL(k_tree_seed, dim3(blocks(n)), dim3(256), 0, s, a, vox, inlets, n, d.X, d.Y, d.Z,
                        make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y), mask);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off, int32_t* seq, hipStream_t s) {
+    auto size = [&](uint32_t t) { return off[t + 1] - off[t]; };
     hipLaunchKernelGGL(k_tree_start, dim3(64), dim3(256), 0, s, a);
     uint32_t side = 0;
     for (uint32_t t = 1; t <= a.R;) {

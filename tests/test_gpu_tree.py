@@ -93,3 +93,26 @@ def test_tree_step_limit(dev, steps):
     assert r["K"] == ref["K"]
     for k in ("centre_step", "seq", "rad2", "M"):
         assert np.array_equal(r[k].cpu().numpy().view(np.uint32), np.asarray(ref[k]).astype(np.uint32)), k
+
+
+@pytest.mark.parametrize("limits", [[5, 40, 900, 7], [5, 0, 900, 7], [0, 2000, 0, 0]])
+def test_batch_step_limits(dev, limits):
+    """Batches of uneven images whose jobs all stop after few steps (the step
+    loops) and others (one tree for all): each job as the oracle alone."""
+    import torch
+
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    imgs = [synth.blurred_noise((20, 61, 33), 2.5, 0.6, 1), synth.overlapping_spheres((45, 30, 70), 16, 0.6, 2),
+            synth.blurred_noise((1, 120, 90), 4.0, 0.55, 3), synth.overlapping_spheres((9, 64, 8), 9, 0.7, 4)]
+    inls = [synth.face_mask(i.shape, 1, 0) for i in imgs]
+    out = ibip.invade_batch([torch.from_numpy(i).to(dev) for i in imgs],
+                            [torch.from_numpy(i).to(dev) for i in inls], max_steps=limits, sat=True)
+    for img, inl, lim, b in zip(imgs, inls, limits, out):
+        ref = oracle.invade(img, inl, max_steps=lim)
+        assert b["status"] == 0 and b["K"] == ref["K"]
+        for k in ("centre_step", "seq", "rad2", "M"):
+            assert np.array_equal(b[k].cpu().numpy().view(np.uint32), np.asarray(ref[k]).astype(np.uint32)), k
+        n = np.bincount(ref["seq"][ref["seq"] > 0], minlength=ref["K"] + 1)[1:]
+        assert np.array_equal(b["sat"].cpu().numpy(), np.cumsum(n) / float((img != 0).sum()))
