@@ -264,10 +264,12 @@ ibip_status ibip_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t n);
  * invasion loop of Section 2.1). Jobs are submitted at any time; a worker
  * thread admits a pending job as soon as an execution slot is free and the
  * job's scratch (about 26 bytes per voxel) fits in the server's HBM pool, and
- * runs it on its slot's stream: setup, the step loop in one workgroup, sphere
- * insertion and finalisation, without host synchronisation, so admitted jobs
- * overlap on the device. A job behind one that does not fit yet may start
- * first (within `lookahead` places), so a huge job does not block the queue.
+ * runs it on its slot's stream: setup, the component tree (whose own scratch,
+ * about 45 bytes per pore voxel, comes from the pool as well; without room for
+ * it, and for jobs stopped after fewer than 1,024 steps, the step loop in one
+ * workgroup), sphere insertion and finalisation. Admitted jobs overlap on the
+ * device. A job behind one that does not fit yet may start first (within
+ * `lookahead` places), so a huge job does not block the queue.
  * A job's results are those of ibip_invade on the same inputs.
  * The job's input buffers must hold their data when it is submitted, and its
  * output buffers must stay valid until ibip_server_wait returns for it.
@@ -300,9 +302,9 @@ ibip_status ibip_server_poll(ibip_server* s, int64_t ticket, int32_t* done);
    its latency into *latency_ms (either may be NULL), then forget the ticket.
    Returns the job's status. */
 ibip_status ibip_server_wait(ibip_server* s, int64_t ticket, ibip_job* result, double* latency_ms);
-/* Cancel a job. A pending job is dropped at once; a running one stops at the
-   next check of its step loop (every 1024 steps, and between its loop
-   segments) and nothing more is queued for it. Its status becomes ECANCELLED
+/* Cancel a job. A pending job is dropped at once; a running one stops after
+   the part that runs (setup, tree; in a step loop at its next check, every
+   1024 steps and between its segments) and nothing more is queued for it. Its status becomes ECANCELLED
    (its outputs are unspecified) unless it had finished before the request
    took effect. EINVAL if the job is done or unknown. */
 ibip_status ibip_server_cancel(ibip_server* s, int64_t ticket);

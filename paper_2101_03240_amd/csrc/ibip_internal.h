@@ -354,6 +354,14 @@ JobBufs carve(uint8_t* base, ibip_dims d, int32_t* caller_state, bool want_sat);
 // EDT, ranks, slices and seeds; loop state initialised on the device
 hipError_t job_setup(const JobBufs& j, LoopState* st, const uint8_t* image, const uint8_t* inlets, ibip_dims d,
                      int64_t max_steps, int32_t* seq, hipStream_t s, EdtTiles tiles = EdtTiles{});
+// its two halves: up to the ranks and slice offsets (rank tables for the tree
+// and the loop alike), and what the step loop needs besides
+hipError_t job_setup_ranks(const JobBufs& j, LoopState* st, const uint8_t* image, ibip_dims d, int64_t max_steps,
+                           hipStream_t s, EdtTiles tiles);
+hipError_t job_setup_loop(const JobBufs& j, const uint8_t* image, const uint8_t* inlets, ibip_dims d, int32_t* seq,
+                          hipStream_t s);
+hipError_t job_post(const JobBufs& j, LoopState* st, ibip_dims d, int64_t K, int32_t* seq, uint32_t* rad2,
+                    uint32_t* M_out, double* sat_out, hipStream_t s);
 // EDT tile widths from a tuning (defaults where it holds 0)
 inline EdtTiles edt_tiles(const ibip_tuning& t) {
     EdtTiles e;

@@ -2157,8 +2157,8 @@ static __global__ void k_sat(const uint32_t* counts, const uint32_t* count_excl,
     if (k < K) sat[k] = (double)(count_excl[k] + counts[k]) / (double)st->n_pore;
 }
 
-hipError_t job_setup(const JobBufs& j, LoopState* st, const uint8_t* image, const uint8_t* inlets, ibip_dims d,
-                     int64_t max_steps, int32_t* seq, hipStream_t s, EdtTiles tiles) {
+hipError_t job_setup_ranks(const JobBufs& j, LoopState* st, const uint8_t* image, ibip_dims d, int64_t max_steps,
+                           hipStream_t s, EdtTiles tiles) {
     const int64_t n = nvox(d), V = value_range(d);
     hipError_t e;
     static_assert(sizeof(LoopState) % 4 == 0, "LoopState is cleared as words");
@@ -2179,10 +2179,65 @@ hipError_t job_setup(const JobBufs& j, LoopState* st, const uint8_t* image, cons
     // a job's tables hold kMaxRanks ranks; its loop rejects an image with more
     hipLaunchKernelGGL(k_rank_tables, dim3(blocks(V)), dim3(256), 0, s, j.hist, present, flags, V, j.val, j.off,
                        j.head, j.tail, (uint32_t)kMaxRanks, st);
-    hipLaunchKernelGGL(k_convert, dim3(blocks(n)), dim3(256), 0, s, image, j.key, present, n, (uint32_t)(V - 1),
+    return hipGetLastError();
+}
+
+hipError_t job_setup_loop(const JobBufs& j, const uint8_t* image, const uint8_t* inlets, ibip_dims d, int32_t* seq,
+                          hipStream_t s) {
+    const int64_t n = nvox(d), V = value_range(d);
+    hipLaunchKernelGGL(k_convert, dim3(blocks(n)), dim3(256), 0, s, image, j.key, j.hist + V, n, (uint32_t)(V - 1),
                        j.state, seq, d.X, d.Y, d.Z, make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y),
                        (uint32_t)kMaxRanks);
     hipLaunchKernelGGL(k_seed, dim3(blocks(n)), dim3(256), 0, s, inlets, j.key, d.X, d.Y, d.Z, j.tail, j.bucket,
+                       false, (uint32_t)kMaxRanks);
+    return hipGetLastError();
+}
+
+hipError_t job_setup(const JobBufs& j, LoopState* st, const uint8_t* image, const uint8_t* inlets, ibip_dims d,
+                     int64_t max_steps, int32_t* seq, hipStream_t s, EdtTiles tiles) {
+    const hipError_t e = job_setup_ranks(j, st, image, d, max_steps, s, tiles);
+    return e != hipSuccess ? e : job_setup_loop(j, image, inlets, d, seq, s);
+}
+
+TreeArgs job_tree_args(const JobBufs& j, const LoopState& hs, const uint32_t* off_host, ibip_dims d, int32_t* seq) {
+    TreeArgs ta{};
+    ta.key = j.key;
+    ta.list = j.bucket;
+    ta.off = j.off;
+    ta.uf = j.tmp32;
+    ta.top = (uint32_t*)seq;
+    ta.idx = (uint32_t*)j.state;
+    ta.gu = j.full;
+    ta.M = ta.nodes = j.M;
+    ta.R = hs.R;
+    ta.sx = d.Y * d.Z;
+    ta.sy = d.Z;
+    ta.n = (uint32_t)nvox(d);
+    uint32_t lcap = 0;
+    for (uint32_t r = 1; r <= hs.R; r++) lcap = std::max(lcap, off_host[r + 1] - off_host[r]);
+    tree_caps(ta, hs.n_pore, 1, lcap);
+    return ta;
+}
+
+hipError_t job_tree(const JobBufs& j, const TreeArgs& ta, const TreeCtl* head, const uint32_t* off_host,
+                    const uint8_t* image, const uint8_t* inlets, ibip_dims d, int32_t* seq, hipStream_t s) {
+    hipError_t e;
+    const int64_t V = value_range(d);
+    if ((e = hipMemcpyAsync(ta.ctl, head, sizeof(TreeCtl) + sizeof(TreeJob), hipMemcpyHostToDevice, s)) != hipSuccess)
+        return e;
+    if ((e = launch_tree_convert(ta, 0, image, j.key, j.key, j.hist + V, d, (uint32_t)(V - 1), s)) != hipSuccess)
+        return e;
+    if ((e = launch_tree_sort(ta, j.tail, j.bucket, s)) != hipSuccess) return e;
+    if ((e = launch_tree_build(ta, off_host, s)) != hipSuccess) return e;
+    if ((e = launch_tree_seed(ta, 0, inlets, d, false, s)) != hipSuccess) return e;
+    return launch_tree_levels(ta, off_host, seq, s);
+}
+
+hipError_t job_tree_undo(const JobBufs& j, const TreeArgs& ta, const uint8_t* inlets, ibip_dims d, int32_t* seq,
+                         hipStream_t s) {
+    const hipError_t e = launch_tree_undo(ta, seq, j.head, j.tail, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_seed, dim3(blocks(nvox(d))), dim3(256), 0, s, inlets, j.key, d.X, d.Y, d.Z, j.tail, j.bucket,
                        false, (uint32_t)kMaxRanks);
     return hipGetLastError();
 }

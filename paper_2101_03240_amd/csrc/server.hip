@@ -5,11 +5,15 @@
 // fits in the server's HBM pool (first fit over one device allocation,
 // looking past a job that does not fit yet to smaller ones behind it, within
 // a bounded window, so a huge job does not block the queue). An admitted job
-// runs entirely stream-ordered on its slot's stream: setup, the step loop in
-// one workgroup, sphere insertion and finalisation, with no host
-// synchronisation; jobs on different slots overlap on the device. The worker
-// polls each slot's completion event, returns the job's scratch to the pool
-// and records its latency from submission to completion.
+// runs stream-ordered on its slot's stream in parts: setup up to the ranks, the
+// component tree, sphere insertion and finalisation; jobs on different slots
+// overlap on the device. Between the parts the worker, which polls each slot's
+// completion event, reads what the next one's launches depend on. The tree's
+// own scratch comes from the pool too, once the job's pore voxels are known; a
+// job for which there is no room then, that stops after few steps, or whose
+// tree gives up runs its step loop in one workgroup instead. At the end the
+// worker returns the job's scratch to the pool and records its latency from
+// submission to completion.
 #include <chrono>
 #include <condition_variable>
 #include <cstring>
@@ -22,6 +26,7 @@
 #include <vector>
 
 #include "ibip_internal.h"
+#include "tree.h"
 
 namespace ibip {
 namespace {
@@ -71,6 +76,7 @@ enum JobState { J_PENDING = 0, J_RUNNING = 1, J_DONE = 2 };
 struct Job {
     ibip_job job{};
     size_t bytes = 0, off = 0;
+    size_t tree_bytes = 0, tree_off = 0;  // the tree's part of the pool, while it has one
     int slot = -1;
     int state = J_PENDING;
     bool cancel = false;  // cancellation requested while it ran
@@ -78,6 +84,12 @@ struct Job {
 };
 
 constexpr size_t kSlotSmall = 4096;  // LoopState + loop arguments of one slot
+// pinned: those, the tree's control words (at 2048), then the slice offsets
+constexpr size_t kSlotPinned = kSlotSmall + sizeof(uint32_t) * (kMaxRanks + 2);
+static_assert(sizeof(TreeCtl) + sizeof(TreeJob) <= 2048, "the tree's head fits beside the loop state");
+
+// What runs on a slot: setup, the component tree, the step loop, post-processing.
+enum Phase { P_SETUP = 1, P_TREE, P_LOOP, P_POST };
 
 struct Slot {
     hipStream_t stream = nullptr;
@@ -86,7 +98,8 @@ struct Slot {
     uint8_t* host_small = nullptr;  // pinned: LoopState copy at 0, loop-argument staging at 512
     int64_t ticket = -1;
     bool broken = false;            // its stream failed; no job is admitted to it again
-    int phase = 0;                  // 1: the job's step loop, 2: its post-processing
+    int phase = 0;                  // Phase
+    TreeArgs tree{};                // the job's tree, once it has one
     uint32_t* cancel_host = nullptr;  // coherent pinned word the job's loop reads every 1024 steps
     uint32_t* cancel_dev = nullptr;   // its device address
 };
@@ -119,75 +132,141 @@ namespace {
 
 void set_err(ibip_server* S, const std::string& m) { S->err = m; }
 
+JobBufs job_bufs(ibip_server* S, const Job& J) {
+    return carve(S->pool_base + J.off, J.job.dims, J.job.centre_step, false);
+}
+
+// A launch on the slot failed: work queued before it may still write into the
+// job's region, so wait for it before the region returns to the pool, and
+// retire the slot if its stream is in an error state.
+void launch_failed(ibip_server* S, Slot& sl, hipError_t e) {
+    set_err(S, std::string("server: launch failed: ") + hipGetErrorString(e));
+    if (hipStreamSynchronize(sl.stream) != hipSuccess) {
+        (void)hipGetLastError();
+        sl.broken = true;
+    }
+}
+
 // Start job `t` on slot `si` (mu held). Returns false if a HIP call failed.
 bool start_job(ibip_server* S, int64_t t, int si) {
     Job& J = S->jobs[t];
     Slot& sl = S->slots[si];
     const ibip_job& jb = J.job;
-    JobBufs b = carve(S->pool_base + J.off, jb.dims, jb.centre_step, false);
+    const JobBufs b = job_bufs(S, J);
     LoopState* st = (LoopState*)sl.dev_small;
-    void* dargs = sl.dev_small + 512;
-    hipError_t e = job_setup(b, st, jb.image, jb.inlets, jb.dims, jb.max_steps, jb.seq, sl.stream,
-                             edt_tiles(S->tuning));
-    // a step with more centres than the threshold stops the loop; the worker
-    // then runs that step over the whole GPU and resumes the loop (advance())
-    fill_loop_args(sl.host_small + 512, b, st, jb.dims, wide_threshold(S->tuning.batch_wide));
-    __atomic_store_n(sl.cancel_host, 0u, __ATOMIC_RELEASE);
-    set_loop_cancel(sl.host_small + 512, sl.cancel_dev);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(dargs, sl.host_small + 512, loop_args_bytes(), hipMemcpyHostToDevice, sl.stream);
-    if (e == hipSuccess) e = launch_loop_jobs(dargs, 1, sl.stream);
+    hipError_t e = job_setup_ranks(b, st, jb.image, jb.dims, jb.max_steps, sl.stream, edt_tiles(S->tuning));
     if (e == hipSuccess) e = hipMemcpyAsync(sl.host_small, st, sizeof(LoopState), hipMemcpyDeviceToHost, sl.stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(sl.host_small + kSlotSmall, b.off, sizeof(uint32_t) * (kMaxRanks + 2),
+                           hipMemcpyDeviceToHost, sl.stream);
     if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);
     if (e != hipSuccess) {
-        set_err(S, std::string("server: launch failed: ") + hipGetErrorString(e));
-        // work queued before the failure may still write into the job's
-        // region: wait for it before the caller returns the region to the
-        // pool, and retire the slot if its stream is in an error state
-        if (hipStreamSynchronize(sl.stream) != hipSuccess) {
-            (void)hipGetLastError();
-            sl.broken = true;
-        }
+        launch_failed(S, sl, e);
         return false;
     }
+    __atomic_store_n(sl.cancel_host, 0u, __ATOMIC_RELEASE);
     J.slot = si;
     J.state = J_RUNNING;
     sl.ticket = t;
-    sl.phase = 1;
+    sl.phase = P_SETUP;
     S->stats.running++;
     S->stats.pending--;
     if (S->stats.running > S->stats.peak_running) S->stats.peak_running = S->stats.running;
     return true;
 }
 
-// The slot's queued work ended (mu held). After a loop segment that stopped
-// at a wide step: queue that step over the whole GPU and the next loop
-// segment; after the last segment: queue the post-processing. Returns false
-// when the job is finished (or a launch failed: *e holds the error).
-bool advance(ibip_server* S, int si, hipError_t* e) {
+void release_tree(ibip_server* S, Job& J) {
+    if (!J.tree_bytes) return;
+    S->pool.release(J.tree_off, J.tree_bytes);
+    S->stats.bytes_in_use -= (int64_t)J.tree_bytes;
+    J.tree_bytes = 0;
+}
+
+// The step loop of a job in one workgroup, to its first wide step or its end.
+hipError_t launch_loop(ibip_server* S, Slot& sl, const Job& J) {
+    const JobBufs b = job_bufs(S, J);
+    LoopState* st = (LoopState*)sl.dev_small;
+    void* dargs = sl.dev_small + 512;
+    // a step with more centres than the threshold stops the loop; the worker
+    // then runs that step over the whole GPU and resumes the loop (advance())
+    fill_loop_args(sl.host_small + 512, b, st, J.job.dims, wide_threshold(S->tuning.batch_wide));
+    set_loop_cancel(sl.host_small + 512, sl.cancel_dev);
+    const hipError_t e = hipMemcpyAsync(dargs, sl.host_small + 512, loop_args_bytes(), hipMemcpyHostToDevice, sl.stream);
+    return e == hipSuccess ? launch_loop_jobs(dargs, 1, sl.stream) : e;
+}
+
+// The slot's queued work ended (mu held through lk): queue the job's next
+// part. Returns false when the job is finished (or a launch failed: *e holds
+// the error).
+bool advance(ibip_server* S, int si, hipError_t* e, std::unique_lock<std::mutex>& lk) {
     Slot& sl = S->slots[si];
-    if (sl.phase != 1 || *e != hipSuccess) return false;
+    if (sl.phase == P_POST || *e != hipSuccess) return false;
     Job& J = S->jobs[sl.ticket];
     const ibip_job& jb = J.job;
-    const LoopState* hs = (const LoopState*)sl.host_small;
-    if (J.cancel || hs->status == LS_CANCEL) return false;  // finish_job reports the cancellation
+    LoopState* hs = (LoopState*)sl.host_small;
     LoopState* st = (LoopState*)sl.dev_small;
+    const uint32_t* h_off = (const uint32_t*)(sl.host_small + kSlotSmall);
+    TreeCtl* h_ctl = (TreeCtl*)(sl.host_small + 2048);
+    TreeJob* h_job = (TreeJob*)(h_ctl + 1);
+    if (J.cancel || hs->status == LS_CANCEL) return false;  // finish_job reports the cancellation
+    const JobBufs b = job_bufs(S, J);
     hipError_t r = hipSuccess;
-    if (hs->status == LS_WIDE && hs->err == 0) {
+    bool state_back = true;  // the loop state is read back after this part
+    if (sl.phase == P_SETUP) {
+        if (!hs->solid_seen || hs->R > (uint32_t)kMaxRanks) {
+            hs->err = !hs->solid_seen ? 2u : 3u;
+            return false;
+        }
+        const bool few = jb.max_steps > 0 && jb.max_steps < kTreeMinSteps;
+        if (!few && hs->n_pore > 0) {
+            sl.tree = job_tree_args(b, *hs, h_off, jb.dims, jb.seq);
+            const size_t bytes = align256(4 * tree_words(sl.tree));
+            if (S->pool.alloc(bytes, &J.tree_off)) {
+                J.tree_bytes = bytes;
+                S->stats.bytes_in_use += (int64_t)bytes;
+                if (S->stats.bytes_in_use > S->stats.peak_bytes) S->stats.peak_bytes = S->stats.bytes_in_use;
+            }
+        }
+        if (J.tree_bytes) {
+            tree_carve(sl.tree, (uint32_t*)(S->pool_base + J.tree_off));
+            *h_ctl = TreeCtl{};
+            *h_job = TreeJob{0, 0, (uint32_t)std::min<int64_t>(jb.max_steps, hs->n_pore), 0};
+            // about a thousand launches: callers need not wait for them (the
+            // job is running, so its entry stays)
+            lk.unlock();
+            r = job_tree(b, sl.tree, h_ctl, h_off, jb.image, jb.inlets, jb.dims, jb.seq, sl.stream);
+            if (r == hipSuccess)
+                r = hipMemcpyAsync(h_ctl, sl.tree.ctl, sizeof(TreeCtl) + sizeof(TreeJob), hipMemcpyDeviceToHost,
+                                   sl.stream);
+            lk.lock();
+            sl.phase = P_TREE;
+            state_back = false;
+        } else {
+            r = job_setup_loop(b, jb.image, jb.inlets, jb.dims, jb.seq, sl.stream);
+            if (r == hipSuccess) r = launch_loop(S, sl, J);
+            sl.phase = P_LOOP;
+        }
+    } else if (sl.phase == P_TREE && h_ctl->abort) {
+        // more peaks, steps or candidates than there is room for
+        r = job_tree_undo(b, sl.tree, jb.inlets, jb.dims, jb.seq, sl.stream);
+        if (r == hipSuccess) r = launch_loop(S, sl, J);
+        sl.phase = P_LOOP;
+    } else if (sl.phase == P_TREE) {
+        hs->k = h_job->K + 1;
+        r = job_post(b, st, jb.dims, h_job->K, jb.seq, jb.rad2, jb.M, nullptr, sl.stream);
+        sl.phase = P_POST;
+        state_back = false;
+    } else if (hs->status == LS_WIDE && hs->err == 0) {
         r = launch_wide_and_loop_host(sl.host_small + 512, (int64_t)jb.dims.X * jb.dims.Y * jb.dims.Z, sl.stream);
     } else {
-        JobBufs b = carve(S->pool_base + J.off, jb.dims, jb.centre_step, false);
         r = job_post_devk(b, st, jb.dims, jb.seq, jb.rad2, jb.M, sl.stream);
-        sl.phase = 2;
+        sl.phase = P_POST;
     }
-    if (r == hipSuccess) r = hipMemcpyAsync(sl.host_small, st, sizeof(LoopState), hipMemcpyDeviceToHost, sl.stream);
+    if (r == hipSuccess && state_back)
+        r = hipMemcpyAsync(sl.host_small, st, sizeof(LoopState), hipMemcpyDeviceToHost, sl.stream);
     if (r == hipSuccess) r = hipEventRecord(sl.done, sl.stream);
     if (r != hipSuccess) {
-        set_err(S, std::string("server: launch failed: ") + hipGetErrorString(r));
-        if (hipStreamSynchronize(sl.stream) != hipSuccess) {
-            (void)hipGetLastError();
-            sl.broken = true;
-        }
+        launch_failed(S, sl, r);
         *e = r;
         return false;
     }
@@ -200,7 +279,7 @@ void finish_job(ibip_server* S, int si, hipError_t e) {
     const LoopState* hs = (const LoopState*)sl.host_small;
     J.job.status = IBIP_OK;
     J.job.n_steps = 0;
-    const bool cancelled = sl.phase == 1 && (J.cancel || hs->status == LS_CANCEL);
+    const bool cancelled = sl.phase != P_POST && (J.cancel || hs->status == LS_CANCEL);
     if (e != hipSuccess) J.job.status = IBIP_EDEVICE;
     else if (cancelled) J.job.status = IBIP_ECANCELLED;
     else if (hs->err == 2) J.job.status = IBIP_ENOSOLID;
@@ -209,6 +288,7 @@ void finish_job(ibip_server* S, int si, hipError_t e) {
     else J.job.n_steps = (int64_t)hs->k - 1;
     J.state = J_DONE;
     J.t_done = Clock::now();
+    release_tree(S, J);
     S->pool.release(J.off, J.bytes);
     S->stats.bytes_in_use -= (int64_t)J.bytes;
     S->stats.running--;
@@ -230,7 +310,7 @@ void worker_main(ibip_server* S) {
             if (q == hipErrorNotReady) continue;
             hipError_t e = q == hipSuccess ? hipSuccess : q;
             progressed = true;
-            if (advance(S, (int)si, &e)) continue;
+            if (advance(S, (int)si, &e, lk)) continue;
             finish_job(S, (int)si, e);
         }
         if (progressed) S->cv_done.notify_all();
@@ -330,7 +410,7 @@ ibip_status ibip_server_create(ibip_server** out, int32_t device, const ibip_ser
         ok = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking) == hipSuccess &&
              hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) == hipSuccess &&
              hipMalloc(&sl.dev_small, kSlotSmall) == hipSuccess &&
-             hipHostMalloc(&sl.host_small, kSlotSmall, hipHostMallocDefault) == hipSuccess &&
+             hipHostMalloc(&sl.host_small, kSlotPinned, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&sl.cancel_host, 64, hipHostMallocCoherent | hipHostMallocMapped) == hipSuccess &&
              hipHostGetDevicePointer((void**)&sl.cancel_dev, sl.cancel_host, 0) == hipSuccess;
     }

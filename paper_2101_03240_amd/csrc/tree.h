@@ -170,6 +170,16 @@ hipError_t launch_tree_seed(const TreeArgs& a, uint32_t vox, const uint8_t* inle
 // in a.jobs (or ctl->abort), and seq (the memory of a.top) = INT_MAX on pore,
 // -1 on solid.
 hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off_host, int32_t* seq, hipStream_t s);
+// One job after job_setup_ranks, whose state and slice offsets the host has
+// read: the tree's arguments (tree_carve lays its own scratch out, tree_words
+// of them), the whole tree on s (head: zeroed control words and the job's
+// entry, in pinned memory), and the start of the step loop after a tree that
+// gave up.
+TreeArgs job_tree_args(const JobBufs& j, const LoopState& hs, const uint32_t* off_host, ibip_dims d, int32_t* seq);
+hipError_t job_tree(const JobBufs& j, const TreeArgs& ta, const TreeCtl* head, const uint32_t* off_host,
+                    const uint8_t* image, const uint8_t* inlets, ibip_dims d, int32_t* seq, hipStream_t s);
+hipError_t job_tree_undo(const JobBufs& j, const TreeArgs& ta, const uint8_t* inlets, ibip_dims d, int32_t* seq,
+                         hipStream_t s);
 // state (the memory of a.idx), seq and the slices as the step loop starts from
 hipError_t launch_tree_undo(const TreeArgs& a, int32_t* seq, uint32_t* head, uint32_t* tail, hipStream_t s);
 

@@ -116,3 +116,26 @@ def test_batch_step_limits(dev, limits):
             assert np.array_equal(b[k].cpu().numpy().view(np.uint32), np.asarray(ref[k]).astype(np.uint32)), k
         n = np.bincount(ref["seq"][ref["seq"] > 0], minlength=ref["K"] + 1)[1:]
         assert np.array_equal(b["sat"].cpu().numpy(), np.cumsum(n) / float((img != 0).sum()))
+
+
+@pytest.mark.parametrize("budget", [5 << 19, 64 << 20])
+def test_served_with_and_without_room_for_the_tree(dev, budget):
+    """A server whose pool holds one job's scratch but not its tree's (the step
+    loop runs), and one with room for both; a step limit below the tree's."""
+    import torch
+
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = synth.blurred_noise((44, 46, 40), 3.0, 0.6, 8)
+    inl = synth.face_mask(img.shape, 0, 0)
+    with ibip.Server(dev, hbm_budget_bytes=budget, max_inflight=2) as srv:
+        ts = [srv.submit(torch.from_numpy(img).to(dev), torch.from_numpy(inl).to(dev), max_steps=k)
+              for k in (0, 50, 0)]
+        res = [srv.wait(t) for t in ts]
+        assert srv.stats()["bytes_in_use"] == 0
+    for k, b in zip((0, 50, 0), res):
+        ref = oracle.invade(img, inl, max_steps=k)
+        assert b["status"] == 0 and b["K"] == ref["K"]
+        for f in ("centre_step", "seq", "rad2", "M"):
+            assert np.array_equal(b[f].cpu().numpy().view(np.uint32), np.asarray(ref[f]).astype(np.uint32)), f
