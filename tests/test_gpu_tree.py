@@ -118,7 +118,7 @@ def test_batch_step_limits(dev, limits):
         assert np.array_equal(b["sat"].cpu().numpy(), np.cumsum(n) / float((img != 0).sum()))
 
 
-@pytest.mark.parametrize("budget", [5 << 19, 64 << 20])
+@pytest.mark.parametrize("budget", [3 << 20, 64 << 20])
 def test_served_with_and_without_room_for_the_tree(dev, budget):
     """A server whose pool holds one job's scratch but not its tree's (the step
     loop runs), and one with room for both; a step limit below the tree's."""
