@@ -1393,144 +1393,66 @@ __device__ inline uint32_t ball_m(const PaintArgs& a, uint32_t m) {
 constexpr int kStampGroup = 4;
 
 __device__ inline void stamp_group(int32_t* seq, const uint32_t (&v)[kStampGroup], const bool (&ok)[kStampGroup],
-                                   int32_t k) {
+                                   const int32_t (&k)[kStampGroup]) {
     int32_t cur[kStampGroup];
 #pragma unroll
     for (int t = 0; t < kStampGroup; t++) cur[t] = seq[v[t]];
 #pragma unroll
     for (int t = 0; t < kStampGroup; t++)
-        if (ok[t] && cur[t] > k) atomicMin(&seq[v[t]], k);
+        if (ok[t] && cur[t] > k[t]) atomicMin(&seq[v[t]], k[t]);
 }
 
-// The cap of centre c (step k, painted ball {|o|^2 < m}) away from its first
-// preceding neighbour in qmask, filtered by the other preceding neighbours:
-// for each point (p, q) of the disk p^2 + q^2 <= m - 1 across the cap's axis,
-// one stamp at the ball's outermost voxel along that axis.
-struct CapGeom {
-    int sgn, posA, posB, posC, dimA, dimB, dimC, sA, sB, sC, Rb;
-    uint32_t rest0;
-    int comp[6];
-};
+// Caps. A face neighbour p of centre c precedes it when p's ball is painted at
+// an earlier step, or in the same step with p the smaller index, and is at
+// least as large (mp >= m). What B(c) = {|o|^2 < m} has outside B(p) are
+// outermost voxels of B(c) along the axis, on the far side from p: a voxel w
+// away from the centre on that side is outside when |o|^2 + 2w + 1 >= mp, and
+// |o|^2 <= m - 1, so w >= h = ceil((mp - m) / 2). Every preceding neighbour cuts
+// such a half-space, so with A the axis of the neighbour with the largest ball,
+// the stamps lie over a box (p, q) across A: p^2 + q^2 <= m - 1 - h^2, and p and
+// q beyond the h of the neighbours on their own axes. Towards a pore's middle mp
+// grows by about 2 sqrt(m) a voxel, so most boxes are empty: of 4.4 M centres of
+// 200^3 blurred noise 0.6 M have points, 34 M together, where the disks of all
+// centres hold 250 M.
+//
+// A wave's boxes differ widely in size, so their points are laid end to end and
+// dealt to the lanes: each lane finds its point's box by a search of the
+// starts, kept with the boxes' parameters in LDS.
+enum CapWord { kCapStart, kCapC, kCapK, kCapM, kCapNear, kCapFar, kCapBp, kCapBm, kCapCp, kCapCm, kCapDA, kCapDB, kCapDC,
+               kCapP, kCapQ, kCapL, kCapW, kCapWords };
+// Boxes up to this many points are dealt together, so that their starts stay
+// small; a larger box (at most the image's voxels) fills the wave by itself and
+// is dealt alone.
+constexpr uint32_t kCapTogether = 1024;
 
-__device__ inline CapGeom cap_geom(const PaintArgs& a, uint32_t m, uint32_t qmask, int x, int y, int z) {
-    CapGeom g;
-    const int j0 = __ffs(qmask) - 1;
-    const int A = j0 >> 1;              // axis of the cap
-    g.sgn = (j0 & 1) ? -1 : 1;          // cap on the side away from the neighbour
-    const int B = (A + 1) % 3, C = (A + 2) % 3;
-    // per-axis values of A, B and C (indices fit 31 bits, so the stamp
-    // addresses are 32-bit sums)
-    const int yzi = a.Y * a.Z;
-    g.posA = A == 0 ? x : A == 1 ? y : z;
-    g.posB = B == 0 ? x : B == 1 ? y : z;
-    g.posC = C == 0 ? x : C == 1 ? y : z;
-    g.dimA = A == 0 ? a.X : A == 1 ? a.Y : a.Z;
-    g.dimB = B == 0 ? a.X : B == 1 ? a.Y : a.Z;
-    g.dimC = C == 0 ? a.X : C == 1 ? a.Y : a.Z;
-    g.sA = A == 0 ? yzi : A == 1 ? a.Z : 1;
-    g.sB = B == 0 ? yzi : B == 1 ? a.Z : 1;
-    g.sC = C == 0 ? yzi : C == 1 ? a.Z : 1;
-    // the other preceding neighbours filter the cap: neighbour j tests
-    // |o - n_j|^2 = |o|^2 - 2 s_j o_(axis j) + 1 < mp[j], where o_(axis j) is
-    // the cap offset along A (0), B (1) or C (2)
-    g.rest0 = qmask & ~(1u << j0);
-#pragma unroll
-    for (int j = 0; j < 6; j++) g.comp[j] = (j >> 1) == A ? 0 : (j >> 1) == B ? 1 : 2;
-    g.Rb = (int)isqrt_u32(m - 1);
-    return g;
-}
-
-// The stamp of point (p, q) (in the disk when ok), false if none.
-__device__ inline bool cap_point(const CapGeom& g, int c, uint32_t m, const uint32_t (&mp)[6], int p, int q, bool ok,
-                                 uint32_t& tv) {
-    const int pb = g.posB + p, pc = g.posC + q;
-    const int rem = (int)(m - 1) - p * p - q * q;
-    ok = ok && rem >= 0 && pb >= 0 && pb < g.dimB && pc >= 0 && pc < g.dimC;
-    const int w = ok ? (int)isqrt_u32((uint32_t)rem) : 0;
-    const int oa = g.sgn * w;
-    const int pa = g.posA + oa;
-    ok = ok && pa >= 0 && pa < g.dimA;
-    const uint32_t oo = (uint32_t)(w * w + p * p + q * q);
-    // (unrolled over the six neighbours: a loop over the set bits indexes
-    // the arrays at run time, which puts them in scratch memory)
-#pragma unroll
-    for (int j = 0; j < 6; j++) {
-        if (!((g.rest0 >> j) & 1u)) continue;
-        const int sj = (j & 1) ? 1 : -1;      // n_j component
-        const int oj = g.comp[j] == 0 ? oa : g.comp[j] == 1 ? p : q;
-        const uint32_t d = oo - 2 * sj * oj + 1;  // |o - n_j|^2
-        ok = ok && d >= mp[j];
-    }
-    tv = ok ? (uint32_t)(c + oa * g.sA + p * g.sB + q * g.sC) : (uint32_t)c;
+// The stamp of a box's point r (a point of box b of the wave's table w).
+__device__ inline bool cap_point(const uint32_t (*w)[64], int b, uint32_t r, bool ok, uint32_t& tv) {
+    const uint32_t L = w[kCapL][b];
+    const uint32_t row = r / L;
+    const int p = (int)w[kCapP][b] + (int)row, q = (int)w[kCapQ][b] + (int)(r - row * L);
+    const uint32_t pp = (uint32_t)p * (uint32_t)p, qq = (uint32_t)q * (uint32_t)q;
+    const int64_t rem = (int64_t)w[kCapM][b] - 1 - pp - qq;
+    ok = ok && rem >= 0;
+    const uint32_t o = ok ? isqrt_u32((uint32_t)rem) : 0u;
+    ok = ok && o <= w[kCapW][b];  // inside the image along A
+    const uint32_t oo = o * o + pp + qq + 1;  // |o|^2 + 1; |o - n|^2 = that - 2 n.o
+    const uint32_t p2 = 2u * (uint32_t)p, q2 = 2u * (uint32_t)q;
+    ok = ok && oo + 2 * o >= w[kCapNear][b] && oo - 2 * o >= w[kCapFar][b] && oo - p2 >= w[kCapBp][b] &&
+         oo + p2 >= w[kCapBm][b] && oo - q2 >= w[kCapCp][b] && oo + q2 >= w[kCapCm][b];
+    const uint32_t c = w[kCapC][b];
+    tv = ok ? c + o * w[kCapDA][b] + (uint32_t)p * w[kCapDB][b] + (uint32_t)q * w[kCapDC][b] : c;
     return ok;
 }
 
-// A lane stamps its own cap: rows p, and along each row groups of q.
-__device__ inline void stamp_cap_lane(const PaintArgs& a, int c, int32_t k, uint32_t m, uint32_t qmask, int x, int y,
-                                      int z, const uint32_t (&mp)[6]) {
-    const CapGeom g = cap_geom(a, m, qmask, x, y, z);
-    for (int p = -g.Rb; p <= g.Rb; p++) {
-        if (g.posB + p < 0 || g.posB + p >= g.dimB) continue;
-        const int U = (int)isqrt_u32(m - 1 - (uint32_t)(p * p));
-        for (int q0 = -U; q0 <= U; q0 += kStampGroup) {
-            uint32_t tv[kStampGroup];
-            bool tok[kStampGroup];
-#pragma unroll
-            for (int t = 0; t < kStampGroup; t++) tok[t] = cap_point(g, c, m, mp, p, q0 + t, q0 + t <= U, tv[t]);
-            stamp_group(a.seq, tv, tok, k);
-        }
-    }
-}
-
-// The whole wave stamps one cap (arguments uniform): the rows of the
-// square holding the disk side by side, a lane per (row, column) point.
-__device__ inline void stamp_cap_wave(const PaintArgs& a, int c, int32_t k, uint32_t m, uint32_t qmask, int x, int y,
-                                      int z, const uint32_t (&mp)[6]) {
-    const int lane = threadIdx.x & 63;
-    const CapGeom g = cap_geom(a, m, qmask, x, y, z);
-    const int L = 2 * g.Rb + 1;
-    if (L <= 64) {
-        const int rpr = 64 / L;  // rows per round
-        const int r0 = lane / L, q = lane - r0 * L - g.Rb;
-        const bool lane_ok = r0 < rpr;
-        for (int p0 = -g.Rb; p0 <= g.Rb; p0 += kStampGroup * rpr) {
-            uint32_t tv[kStampGroup];
-            bool tok[kStampGroup];
-#pragma unroll
-            for (int t = 0; t < kStampGroup; t++) {
-                const int p = p0 + r0 + t * rpr;
-                tok[t] = cap_point(g, c, m, mp, p, q, lane_ok && p <= g.Rb, tv[t]);
-            }
-            stamp_group(a.seq, tv, tok, k);
-        }
-    } else {
-        for (int p = -g.Rb; p <= g.Rb; p++) {
-            if (g.posB + p < 0 || g.posB + p >= g.dimB) continue;
-            for (int q0 = -g.Rb; q0 <= g.Rb; q0 += 64 * kStampGroup) {
-                uint32_t tv[kStampGroup];
-                bool tok[kStampGroup];
-#pragma unroll
-                for (int t = 0; t < kStampGroup; t++) {
-                    const int q = q0 + lane + 64 * t;
-                    tok[t] = cap_point(g, c, m, mp, p, q, q <= g.Rb, tv[t]);
-                }
-                stamp_group(a.seq, tv, tok, k);
-            }
-        }
-    }
-}
-
-// Caps up to this radius are stamped by their own lane, larger ones by the
-// whole wave.
-constexpr int kSmallCap = 2;
-
-// One thread per voxel finds its centre's cap: centres with an earlier,
-// at-least-as-large face neighbour stamp a cap, the others are listed for the
-// full-ball pass. Caps differ widely in size, and with one lane per centre
-// most lanes of a wave idled while the largest cap among them was stamped:
-// small caps stay with their lane, large ones are stamped one centre at a
-// time by all 64 lanes, lanes over the points of the cap's disk.
+// One thread per voxel finds its centre's cap: centres with a preceding face
+// neighbour stamp a cap, the others are listed for the full-ball pass.
+// Bound by the points' arithmetic (two thirds of them stamp nothing). 512^3 blurred
+// noise: 6.8 ms; 22.0 with whole disks across the axis, one small cap to a lane
+// and one large cap to the wave at a time, 48.8 with disks not cut by h. 200^3
+// grains: 0.40 and 1.04 ms.
 __global__ __launch_bounds__(256) void k_paint_shell(PaintArgs a) {
+    __shared__ uint32_t tab[4][kCapWords][64];
+    uint32_t(*w)[64] = tab[threadIdx.x >> 6];
     const int64_t yz = (int64_t)a.Y * a.Z;
     const int64_t n = (int64_t)a.X * yz;
     int64_t nb_unused;
@@ -1565,7 +1487,7 @@ __global__ __launch_bounds__(256) void k_paint_shell(PaintArgs a) {
         for (int j = 0; j < 6; j++) vp[j] = a.val[rp[j]];
 #pragma unroll
         for (int j = 0; j < 6; j++) {
-            const bool q = inb[j] && kp[j] > 0 && kp[j] < k && rp[j] >= rc;
+            const bool q = inb[j] && kp[j] > 0 && (kp[j] < k || (kp[j] == k && !(j & 1))) && rp[j] >= rc;
             qmask |= q ? 1u << j : 0u;
             mp[j] = q ? ball_m(a, vp[j]) : 0u;
         }
@@ -1580,28 +1502,112 @@ __global__ __launch_bounds__(256) void k_paint_shell(PaintArgs a) {
         base = __shfl(base, leader, 64);
         if (full) a.full[base + (uint32_t)__popcll(mf & lanemask_lt())] = (uint32_t)c;
     }
-    // small caps: each lane stamps its own (the wave runs as long as its
-    // largest small cap); large caps: the whole wave on one cap at a time
-    const bool cap = k > 0 && qmask != 0;
-    const uint32_t rbl = cap ? isqrt_u32(m - 1) : 0u;
-    if (cap && rbl <= (uint32_t)kSmallCap)
-        stamp_cap_lane(a, (int)c, k, m, qmask, x, y, z, mp);
-    uint64_t pending = __ballot(cap && rbl > (uint32_t)kSmallCap);
-    while (pending) {
-        const int src = __ffsll((unsigned long long)pending) - 1;
-        pending &= pending - 1;
-        uint32_t mps[6];
+
+    // the cap's axis A (B and C the next two): its neighbour on side n has the
+    // largest ball; the cap is on the other side
+    int j0 = 0;
+    uint32_t mx = 0;
 #pragma unroll
-        for (int j = 0; j < 6; j++) mps[j] = __builtin_amdgcn_readlane(mp[j], src);
-        stamp_cap_wave(a, __builtin_amdgcn_readlane((int)c, src), __builtin_amdgcn_readlane(k, src),
-                       __builtin_amdgcn_readlane(m, src), __builtin_amdgcn_readlane(qmask, src),
-                       __builtin_amdgcn_readlane(x, src), __builtin_amdgcn_readlane(y, src),
-                       __builtin_amdgcn_readlane(z, src), mps);
+    for (int j = 0; j < 6; j++) {
+        j0 = mp[j] > mx ? j : j0;
+        mx = max(mx, mp[j]);
+    }
+    const int A = j0 >> 1;
+    const bool swap = (j0 & 1) == 0;  // the neighbour at -1
+    const uint32_t a0 = A == 0 ? mp[0] : A == 1 ? mp[2] : mp[4], a1 = A == 0 ? mp[1] : A == 1 ? mp[3] : mp[5];
+    const uint32_t b0 = A == 0 ? mp[2] : A == 1 ? mp[4] : mp[0], b1 = A == 0 ? mp[3] : A == 1 ? mp[5] : mp[1];
+    const uint32_t c0 = A == 0 ? mp[4] : A == 1 ? mp[0] : mp[2], c1 = A == 0 ? mp[5] : A == 1 ? mp[1] : mp[3];
+    const int posA = A == 0 ? x : A == 1 ? y : z, posB = A == 0 ? y : A == 1 ? z : x, posC = A == 0 ? z : A == 1 ? x : y;
+    const int dimA = A == 0 ? a.X : A == 1 ? a.Y : a.Z, dimB = A == 0 ? a.Y : A == 1 ? a.Z : a.X,
+              dimC = A == 0 ? a.Z : A == 1 ? a.X : a.Y;
+    const uint32_t sx = (uint32_t)yz, sy = (uint32_t)a.Z;
+    const uint32_t sA = A == 0 ? sx : A == 1 ? sy : 1u, sB = A == 0 ? sy : A == 1 ? 1u : sx, sC = A == 0 ? 1u : A == 1 ? sx : sy;
+    uint32_t area = 0;
+    int pl = 0, ql = 0, L = 1;
+    if (qmask) {
+        // h of each side (0 where no neighbour precedes on it)
+        const uint32_t hA = (mx - m + 1) >> 1;
+        const int hBm = b0 ? (int)((b0 - m + 1) >> 1) : 0, hBp = b1 ? (int)((b1 - m + 1) >> 1) : 0;
+        const int hCm = c0 ? (int)((c0 - m + 1) >> 1) : 0, hCp = c1 ? (int)((c1 - m + 1) >> 1) : 0;
+        const int64_t hB = max(hBm, hBp), hC = max(hCm, hCp);
+        const int64_t rest = (int64_t)m - 1 - (int64_t)hA * hA;
+        if (rest >= hB * hB + hC * hC) {
+            // a neighbour at -1 leaves p >= hBm, one at +1 leaves p <= -hBp
+            const int RB = (int)isqrt_u32((uint32_t)(rest - hC * hC)), RC = (int)isqrt_u32((uint32_t)(rest - hB * hB));
+            pl = max(b0 ? hBm : -RB, -posB);
+            ql = max(c0 ? hCm : -RC, -posC);
+            const int ph = min(b1 ? -hBp : RB, dimB - 1 - posB);
+            const int qh = min(c1 ? -hCp : RC, dimC - 1 - posC);
+            if (pl <= ph && ql <= qh) {
+                L = qh - ql + 1;
+                area = (uint32_t)(ph - pl + 1) * (uint32_t)L;
+            }
+        }
+    }
+    uint64_t pending = __ballot(area != 0);
+    while (pending) {
+        // the boxes to deal: all the small ones, then the large ones one by one
+        const uint64_t small = __ballot(area <= kCapTogether) & pending;
+        const uint64_t now = small ? small : pending & (~pending + 1);
+        pending &= ~now;
+        const bool mine = (now >> lane) & 1;
+        uint32_t end = mine ? area : 0u;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t t = __shfl_up(end, d, 64);
+            if (lane >= d) end += t;
+        }
+        const uint32_t total = __builtin_amdgcn_readlane(end, 63);
+        const int nbox = __popcll(now);
+        if (lane >= nbox) w[kCapStart][lane] = 0xffffffffu;
+        if (mine) {
+            const int i = __popcll(now & lanemask_lt());
+            w[kCapStart][i] = end - area;
+            w[kCapC][i] = (uint32_t)c;
+            w[kCapK][i] = (uint32_t)k;
+            w[kCapM][i] = m;
+            w[kCapNear][i] = mx;
+            w[kCapFar][i] = swap ? a1 : a0;
+            w[kCapBp][i] = b1;
+            w[kCapBm][i] = b0;
+            w[kCapCp][i] = c1;
+            w[kCapCm][i] = c0;
+            w[kCapDA][i] = swap ? sA : 0u - sA;
+            w[kCapDB][i] = sB;
+            w[kCapDC][i] = sC;
+            w[kCapP][i] = (uint32_t)pl;
+            w[kCapQ][i] = (uint32_t)ql;
+            w[kCapL][i] = (uint32_t)L;
+            w[kCapW][i] = (uint32_t)(swap ? dimA - 1 - posA : posA);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t i0 = (uint32_t)lane; i0 - (uint32_t)lane < total; i0 += 64 * kStampGroup) {
+            uint32_t tv[kStampGroup];
+            bool tok[kStampGroup];
+            int32_t tk[kStampGroup];
+#pragma unroll
+            for (int t = 0; t < kStampGroup; t++) {
+                const uint32_t i = i0 + 64u * t;
+                int box = 0;
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1)
+                    if (w[kCapStart][box + d] <= i) box += d;
+                tok[t] = cap_point(w, box, i - w[kCapStart][box], i < total, tv[t]);
+                tk[t] = (int32_t)w[kCapK][box];
+            }
+            stamp_group(a.seq, tv, tok, tk);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-// One wave per listed centre: the whole ball, lanes over (x, y) columns,
-// each lane writing a contiguous run along z.
+// One wave per listed centre: the whole ball. The box around it (cut to the
+// image) is taken by rows along z, as many side by side as fit the wave, so that
+// a wave's loads cover whole runs of memory; a point of the box is in the ball
+// when |o|^2 < m. 2.95 ms on 512^3 blurred noise; 6.3 ms with a lane to a column
+// (x, y), its run along z in turn (19 of 64 lanes busy, a line a lane).
 __global__ __launch_bounds__(256) void k_paint_full(PaintArgs a) {
     const int lane = threadIdx.x & 63;
     const uint32_t nf = *a.n_full;
@@ -1610,33 +1616,37 @@ __global__ __launch_bounds__(256) void k_paint_full(PaintArgs a) {
     const int64_t b = paint_block(a, nblocks);
     if (b < 0) return;
     for (uint32_t i = f0 + (uint32_t)b * 4 + (threadIdx.x >> 6); i < nf; i += (uint32_t)nblocks * 4) {
-        const int64_t c = a.full[i];
+        const uint32_t c = a.full[i];
         const int32_t k = a.state[c];
+        int32_t tk[kStampGroup];
+#pragma unroll
+        for (int t = 0; t < kStampGroup; t++) tk[t] = k;
         const uint32_t m = ball_m(a, a.val[a.key[c] & kRankMask]);
         int x, y, z;
-        coords((uint32_t)c, a, x, y, z);
-        const int Rb = (int)isqrt_u32(m - 1);
-        for (int dx = -Rb; dx <= Rb; dx++) {
-            const int xx = x + dx;
-            if (xx < 0 || xx >= a.X) continue;
-            const uint32_t rem = m - 1 - (uint32_t)(dx * dx);
-            const int U = (int)isqrt_u32(rem);
-            for (int dy = -U + lane; dy <= U; dy += 64) {
-                const int yy = y + dy;
-                if (yy < 0 || yy >= a.Y) continue;
-                const int W = (int)isqrt_u32(rem - (uint32_t)(dy * dy));
-                const int z0 = max(z - W, 0), z1 = min(z + W, a.Z - 1);
-                const uint32_t rowv = ((uint32_t)xx * (uint32_t)a.Y + (uint32_t)yy) * (uint32_t)a.Z;
-                for (int zz = z0; zz <= z1; zz += kStampGroup) {
-                    uint32_t tv[kStampGroup];
-                    bool tok[kStampGroup];
+        coords(c, a, x, y, z);
+        const int R = (int)isqrt_u32(m - 1);
+        const int xl = max(-R, -x), xh = min(R, a.X - 1 - x);
+        const int yl = max(-R, -y), yh = min(R, a.Y - 1 - y);
+        const int zl = max(-R, -z), zh = min(R, a.Z - 1 - z);
+        const uint32_t ny = (uint32_t)(yh - yl + 1), L = (uint32_t)(zh - zl + 1);
+        const uint32_t rows = (uint32_t)(xh - xl + 1) * ny;
+        const uint32_t rpr = L < 64 ? 64 / L : 1;  // rows side by side
+        const uint32_t r0 = L < 64 ? (uint32_t)lane / L : 0u;
+        const int dz0 = zl + lane - (int)(r0 * L);
+        for (uint32_t row0 = r0; row0 - r0 < rows; row0 += rpr * kStampGroup) {
+            for (int dz = dz0; dz - dz0 + zl <= zh; dz += 64) {
+                uint32_t tv[kStampGroup];
+                bool tok[kStampGroup];
 #pragma unroll
-                    for (int t = 0; t < kStampGroup; t++) {
-                        tok[t] = zz + t <= z1;
-                        tv[t] = rowv + (uint32_t)min(zz + t, z1);
-                    }
-                    stamp_group(a.seq, tv, tok, k);
+                for (int t = 0; t < kStampGroup; t++) {
+                    const uint32_t row = row0 + rpr * t;
+                    const uint32_t q = row / ny;
+                    const int dx = xl + (int)q, dy = yl + (int)(row - q * ny);
+                    const int64_t rem = (int64_t)m - (uint32_t)(dx * dx) - (uint32_t)(dy * dy);
+                    tok[t] = r0 < rpr && row < rows && dz <= zh && (int64_t)(uint32_t)(dz * dz) < rem;
+                    tv[t] = tok[t] ? c + (uint32_t)((dx * a.Y + dy) * a.Z + dz) : c;
                 }
+                stamp_group(a.seq, tv, tok, tk);
             }
         }
     }
