@@ -20,7 +20,7 @@
 // the unique fixed point.
 #include <climits>
 
-#include "ibip_internal.h"
+#include "basin.h"
 
 namespace ibip {
 
@@ -28,18 +28,6 @@ namespace {
 
 constexpr int TX = 8, TY = 16, TZ = 32;  // 4096 voxels per tile, 16 per thread
 constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
-
-struct CapSeq {
-    const int32_t* seq;
-    __device__ uint32_t operator()(int64_t v) const {
-        int32_t s = seq[v];
-        return s < 0 ? 0u : (s == 0 ? kInf32 : (uint32_t)s);
-    }
-};
-struct CapU32 {
-    const uint32_t* cap;
-    __device__ uint32_t operator()(int64_t v) const { return cap[v]; }
-};
 
 // One sweep over the active tiles, in ascending tile order or (rev) in
 // descending order. Tiles update w in place, so a tile that starts after a
@@ -346,9 +334,50 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
+// By basins: *done unless there is no scratch or an image with more basins or
+// edges than its lists hold (noise of single voxels), which the sweeps take.
+static ibip_status reconstruct_basins(ibip_ctx* ctx, const int32_t* seq, const uint32_t* cap32, bool conn26,
+                                      ibip_dims d, uint32_t* w, int* n_iter, bool* done) {
+    hipStream_t s = ctx->stream;
+    BasinArgs a{};
+    basin_caps(a, nvox(d));
+    a.X = d.X;
+    a.Y = d.Y;
+    a.Z = d.Z;
+    a.divZ = make_fastdiv((uint32_t)d.Z);
+    a.divY = make_fastdiv((uint32_t)d.Y);
+    void* mem = ensure(ctx, B_TREE, basin_bytes(a));
+    uint32_t* h = (uint32_t*)pinned(ctx, 4096);
+    if (!mem || !h) return IBIP_OK;
+    basin_carve(a, mem);
+    h += 512;
+    ibip_status rc;
+    if ((rc = hip_check(ctx, hipMemsetAsync(a.ctl, 0, sizeof(BasinCtl), s), "memset")) != IBIP_OK) return rc;
+    if ((rc = hip_check(ctx, launch_basin_graph(a, seq, cap32, conn26, w, s), "basins")) != IBIP_OK) return rc;
+    for (int from = 0, to = 8; from < kBasinRounds; from = to, to += 8) {
+        if ((rc = hip_check(ctx, launch_basin_rounds(a, from, to, s), "basin rounds")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, launch_basin_finish(a, seq, cap32, w, to, s), "basins")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, hipMemcpyAsync(h, a.ctl, offsetof(BasinCtl, np), hipMemcpyDeviceToHost, s),
+                            "copy")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+        const BasinCtl* c = (const BasinCtl*)h;
+        if (c->abort || c->abort_edges) return IBIP_OK;
+        if (c->live[to - 1]) continue;
+        *done = true;
+        if (n_iter)
+            for (*n_iter = 1; c->live[*n_iter - 1];) ++*n_iter;
+        return IBIP_OK;
+    }
+    return fail(ctx, IBIP_EDEVICE, "reconstruct: edges left after the last round");
+}
+
 ibip_status reconstruct(ibip_ctx* ctx, const int32_t* seq, const uint32_t* cap32, bool conn26, ibip_dims d,
                         uint32_t* w, int* n_iter) {
     hipStream_t s = ctx->stream;
+    bool done = false;
+    ibip_status rb = reconstruct_basins(ctx, seq, cap32, conn26, d, w, n_iter, &done);
+    if (rb != IBIP_OK || done) return rb;
     const int ntx = (d.X + TX - 1) / TX, nty = (d.Y + TY - 1) / TY, ntz = (d.Z + TZ - 1) / TZ;
     const int64_t ntiles = (int64_t)ntx * nty * ntz;
     constexpr int kBatch = 16;  // sweeps per host check
