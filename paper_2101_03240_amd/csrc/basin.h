@@ -44,13 +44,13 @@ struct BasinArgs {
     uint32_t* par;   // [n] climb, then label
     int64_t n;
     int X, Y, Z;
-    FastDiv divZ, divY;
+    int nty, ntz;    // tiles along y and z
     uint32_t pcap, pall, ecap;
 };
 
-// Capacities of the lists for an image of n voxels; the scratch they take; its
-// layout at `mem` (8-byte aligned).
-void basin_caps(BasinArgs& a, int64_t n);
+// Sizes of the lists for an image; the scratch they take; its layout at `mem`
+// (8-byte aligned).
+void basin_caps(BasinArgs& a, ibip_dims d);
 size_t basin_bytes(const BasinArgs& a);
 void basin_carve(BasinArgs& a, void* mem);
 // Basins and edges of a capacity image and its seeds w; rounds from..to-1; and,

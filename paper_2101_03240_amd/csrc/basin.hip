@@ -16,10 +16,12 @@
 // that chose the same edge the larger index hooks. Inside a component the
 // roots reach each other by edges no worse than the best edge that leaves it, so
 // B(root) = min(w, B(other root)), and compressing H by (min of w, root) gives B
-// once no edge is left between components: 6 to 8 rounds on the images above.
+// once no edge is left between components: 6 to 9 rounds on such images.
 //
-// Against relaxing tiles to the fixed point (trap.hip), which took 176 sweeps
-// with the front crossing the image: MEASURED
+// Against relaxing tiles to the fixed point (trap.hip), 64 to 184 sweeps while the
+// front crosses the image: trapping of 512^3 19.2 -> 6.3 ms (climbs 0.73, labels 0.53,
+// edges 0.85, rounds 2.5, result 0.34), of 230 x 171 x 199 2.31 -> 0.72 ms; opening of
+// 512^3 20.0 -> 7.4 ms. Bound by gathers at the edges' ends and best edges.
 #include "basin.h"
 
 namespace ibip {
@@ -34,6 +36,14 @@ __device__ inline uint64_t ld64(const uint64_t* p) {
 }
 __device__ inline uint32_t to(uint64_t h) { return (uint32_t)h; }
 __device__ inline uint64_t hook(uint32_t w, uint32_t t) { return (uint64_t)w << 32 | t; }
+
+// Sets a flag that most waves set: read first, by one lane of each.
+__device__ inline void raise(uint32_t* flag, bool want) {
+    const uint64_t m = __ballot(want);
+    if (m && (int)(threadIdx.x & 63) == __ffsll((unsigned long long)m) - 1 &&
+        __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+        __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Places for `mine` entries of each thread in the list of slot s: one atomic per
 // workgroup of 256 threads, which all call it; kBasinSlots lists, since an atomic on
@@ -63,73 +73,136 @@ __device__ inline uint32_t slot_append(uint32_t* cnt, uint32_t mine) {
     return first + before + incl - mine;
 }
 
-struct Place {
-    int64_t v;
-    int x, y, z;
-    bool in;
-};
-__device__ inline Place place(const BasinArgs& a) {
-    Place p;
-    const int64_t v = (int64_t)blockIdx.x * kBasinWg + threadIdx.x;
-    p.in = v < a.n;
-    p.v = p.in ? v : 0;
-    const uint32_t t = fdiv((uint32_t)p.v, a.divZ), xx = fdiv(t, a.divY);
-    p.z = (int)((uint32_t)p.v - t * (uint32_t)a.Z);
-    p.y = (int)(t - xx * (uint32_t)a.Y);
-    p.x = (int)xx;
-    return p;
-}
-__device__ inline bool inside(const BasinArgs& a, int x, int y, int z) {
-    return (unsigned)x < (unsigned)a.X && (unsigned)y < (unsigned)a.Y && (unsigned)z < (unsigned)a.Z;
-}
-
-// par[v] = the neighbour to climb to, or kTop | label where v is a top. All
-// neighbours are loaded before the first is used (an outside one reads v).
-template <class Cap, bool kConn26>
-__global__ __launch_bounds__(kBasinWg) void k_basin_up(BasinArgs a, Cap cap) {
-    const Place p = place(a);
-    const int64_t yz = (int64_t)a.Y * a.Z;
-    const uint32_t c = p.in ? cap(p.v) : 0u;
-    uint64_t best = (uint64_t)c << 32 | (uint32_t)p.v;
-    if (kConn26) {
-        if (c) {
-#pragma unroll
-            for (int j = 0; j < 27; j++) {
-                const int dx = j / 9 - 1, dy = j / 3 % 3 - 1, dz = j % 3 - 1;
-                if (j == 13) continue;
-                const int64_t u = inside(a, p.x + dx, p.y + dy, p.z + dz) ? p.v + dx * yz + dy * a.Z + dz : p.v;
-                best = max(best, (uint64_t)cap(u) << 32 | (uint32_t)u);
-            }
-        }
-    } else {
-        const int64_t u[6] = {p.x > 0 ? p.v - yz : p.v,  p.x < a.X - 1 ? p.v + yz : p.v,
-                              p.y > 0 ? p.v - a.Z : p.v, p.y < a.Y - 1 ? p.v + a.Z : p.v,
-                              p.z > 0 ? p.v - 1 : p.v,   p.z < a.Z - 1 ? p.v + 1 : p.v};
-        uint32_t cu[6];
-#pragma unroll
-        for (int j = 0; j < 6; j++) cu[j] = cap(u[j]);
-#pragma unroll
-        for (int j = 0; j < 6; j++) best = max(best, (uint64_t)cu[j] << 32 | (uint32_t)u[j]);
+// A tile of 2048 voxels, 32 along z: 8 x 8 x 32, or 64 x 32 of a plane (kFlat, for
+// images of one plane, which fill an eighth of the former), with a halo of one.
+// A thread has the voxels of one z and every eighth row.
+template <bool kFlat>
+struct Tile {
+    static constexpr int TX = kFlat ? 1 : 8, TY = kFlat ? 64 : 8, TZ = 32;
+    static constexpr int HX = kFlat ? 1 : TX + 2, HY = TY + 2, HZ = TZ + 2, HN = HX * HY * HZ;
+    int x0, y0, z0;
+    __device__ Tile(const BasinArgs& a) {
+        const uint32_t t = blockIdx.x / (uint32_t)a.ntz;
+        z0 = (int)(blockIdx.x - t * (uint32_t)a.ntz) * TZ;
+        x0 = (int)(t / (uint32_t)a.nty) * TX;
+        y0 = (int)(t % (uint32_t)a.nty) * TY;
     }
-    const uint32_t up = (uint32_t)best;
-    const bool top = c != 0 && up == (uint32_t)p.v;
+    // voxel i of the tile (z fastest): its place, its place in the halo's box
+    __device__ static int lx(int i) { return kFlat ? 0 : i / (TY * TZ); }
+    __device__ static int ly(int i) { return kFlat ? i / TZ : i / TZ % TY; }
+    __device__ static int lz(int i) { return i % TZ; }
+    __device__ static int halo(int i) { return ((lx(i) + (kFlat ? 0 : 1)) * HY + ly(i) + 1) * HZ + lz(i) + 1; }
+    __device__ bool in(const BasinArgs& a, int i) const { return x0 + lx(i) < a.X && y0 + ly(i) < a.Y && z0 + lz(i) < a.Z; }
+    __device__ int64_t voxel(const BasinArgs& a, int i) const {
+        return ((int64_t)(x0 + lx(i)) * a.Y + y0 + ly(i)) * a.Z + z0 + lz(i);
+    }
+    // f of the tile and its halo into LDS (0 or `out` outside the image): all
+    // loads are issued before the first is used, from clamped places
+    template <class F>
+    __device__ void load(const BasinArgs& a, F f, uint32_t* lds, uint32_t out) const {
+        constexpr int kPer = (HN + kBasinWg - 1) / kBasinWg;
+        uint32_t h[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; q++) {
+            const int i = min((int)threadIdx.x + q * kBasinWg, HN - 1);
+            const int hz = i % HZ, hy = i / HZ % HY, hx = i / (HZ * HY);
+            const int gx = x0 + hx - (kFlat ? 0 : 1), gy = y0 + hy - 1, gz = z0 + hz - 1;
+            const bool ok = (unsigned)gx < (unsigned)a.X && (unsigned)gy < (unsigned)a.Y && (unsigned)gz < (unsigned)a.Z;
+            const int64_t v = ((int64_t)min(max(gx, 0), a.X - 1) * a.Y + min(max(gy, 0), a.Y - 1)) * a.Z + min(max(gz, 0), a.Z - 1);
+            const uint32_t val = f(v);
+            h[q] = ok ? val : out;
+        }
+#pragma unroll
+        for (int q = 0; q < kPer; q++) {
+            const int i = (int)threadIdx.x + q * kBasinWg;
+            if (i < HN) lds[i] = h[q];
+        }
+    }
+};
+constexpr int kTileVoxels = 2048, kOwn = kTileVoxels / kBasinWg;
+
+// par[v] = the end of v's climb inside its tile: kTop | label at a top, else
+// the voxel outside the tile that it goes on to.
+template <class Cap, bool kConn26, bool kFlat>
+__global__ __launch_bounds__(kBasinWg) void k_basin_up(BasinArgs a, Cap cap) {
+    using T = Tile<kFlat>;
+    __shared__ uint32_t hw[T::HN];
+    __shared__ uint16_t up[kTileVoxels];  // the tile's voxel to climb to (itself at a top), or kOut | direction
+    constexpr uint32_t kOut = 0x8000u;
+    const T t(a);
+    const int tid = threadIdx.x;
+    t.load(a, cap, hw, 0u);
+    __syncthreads();
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kOwn; j++) {
+        const int i = tid + j * kBasinWg, h = T::halo(i);
+        // directions 0..26 are in the order of the neighbours' indices; 13 is v itself
+        uint64_t best = (uint64_t)hw[h] << 5 | 13u;
+#pragma unroll
+        for (int q = 0; q < 27; q++) {
+            const int dx = q / 9 - 1, dy = q / 3 % 3 - 1, dz = q % 3 - 1;
+            if (q == 13 || (kFlat && dx) || (!kConn26 && (dx != 0) + (dy != 0) + (dz != 0) > 1)) continue;
+            best = max(best, (uint64_t)hw[h + (dx * T::HY + dy) * T::HZ + dz] << 5 | (uint32_t)q);
+        }
+        const int q = (int)((uint32_t)best & 31u);
+        const int x = T::lx(i) + q / 9 - 1, y = T::ly(i) + q / 3 % 3 - 1, z = T::lz(i) + q % 3 - 1;
+        const bool stay = (unsigned)x < (unsigned)T::TX && (unsigned)y < (unsigned)T::TY && (unsigned)z < (unsigned)T::TZ;
+        up[i] = (uint16_t)(stay ? (uint32_t)((x * T::TY + y) * T::TZ + z) : kOut | (uint32_t)q);
+        mine += q == 13 && hw[h] != 0;  // (outside the image the capacity is 0)
+    }
+    __syncthreads();
+    uint32_t end[kOwn];
+#pragma unroll
+    for (int j = 0; j < kOwn; j++) {
+        const int i = tid + j * kBasinWg;
+        uint32_t e = (uint32_t)i;
+        if (hw[T::halo(i)])
+            for (uint32_t n; (n = up[e]) != e && !(n & kOut);) e = n;
+        end[j] = e;
+    }
     const uint32_t slot = blockIdx.x % kBasinSlots;
-    const uint32_t i = slot_append(&a.ctl->np[slot * kBasinPad], top ? 1u : 0u);
-    uint32_t val = c == 0 ? kNone : up;
-    if (top) {
-        if (i < a.pcap) {
-            const uint32_t id = slot * a.pcap + i;
+    uint32_t k = slot_append(&a.ctl->np[slot * kBasinPad], mine);
+    // the tops' labels, in place of their capacities
+    uint32_t own[kOwn];
+#pragma unroll
+    for (int j = 0; j < kOwn; j++) own[j] = hw[T::halo(tid + j * kBasinWg)];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOwn; j++) {
+        const int i = tid + j * kBasinWg;
+        if (!own[j] || up[i] != i) continue;
+        uint32_t id = kNone;
+        if (k < a.pcap) {
+            id = slot * a.pcap + k;
             a.H[id] = hook(0xffffffffu, id);
             a.best[id] = 0;
             a.best[a.pall + 1 + id] = 0;
-            val = kTop | id;
+            id |= kTop;
         } else {
-            val = kNone;
             a.ctl->abort = 1;
         }
+        k++;
+        hw[T::halo(i)] = id;
     }
-    if (p.in) a.par[p.v] = val;
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.H[a.pall] = hook(0xffffffffu, a.pall);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOwn; j++) {
+        const int i = tid + j * kBasinWg;
+        if (!t.in(a, i)) continue;
+        uint32_t val = kNone;
+        if (own[j]) {
+            const uint32_t e = end[j], n = up[e];
+            if (n & kOut) {
+                const int q = (int)(n & 31u);
+                val = (uint32_t)(t.voxel(a, (int)e) + ((int64_t)(q / 9 - 1) * a.Y + (q / 3 % 3 - 1)) * a.Z + q % 3 - 1);
+            } else {
+                val = hw[T::halo((int)e)];
+            }
+        }
+        a.par[t.voxel(a, i)] = val;
+    }
+    if (blockIdx.x == 0 && tid == 0) a.H[a.pall] = hook(0xffffffffu, a.pall);
 }
 
 // par[v] = the label at the end of v's climb. A launch makes up to `hops` hops
@@ -146,70 +219,78 @@ __global__ __launch_bounds__(256) void k_basin_label(BasinArgs a, int hops, int 
         a.par[v] = p;
         left |= !(p & kTop);
     }
-    if (left) a.ctl->climb[pass] = 1;
+    raise(&a.ctl->climb[pass], left);
 }
 
 // The edges between basins, and to O from the seeds. Of the edges between two
 // basins only the best matters, so an edge goes into the list only if the pair
 // of voxels one step aside, between the same two basins, is not better (of equals
 // the one at the larger index is): on the images above 8 to 17 % of all voxels.
-template <class Cap, bool kConn26>
+template <class Cap, bool kConn26, bool kFlat>
 __global__ __launch_bounds__(kBasinWg) void k_basin_edges(BasinArgs a, Cap cap, const uint32_t* w0) {
     if (a.ctl->abort) return;
-    const Place p = place(a);
-    const int64_t yz = (int64_t)a.Y * a.Z;
-    const uint32_t la = p.in ? a.par[p.v] : kNone;
+    using T = Tile<kFlat>;
+    __shared__ uint32_t hl[T::HN], hc[T::HN];
+    const T t(a);
+    const int tid = threadIdx.x;
+    t.load(a, [&](int64_t v) { return a.par[v]; }, hl, kNone);
+    t.load(a, cap, hc, 0u);
+    __syncthreads();
     constexpr int kDirs = kConn26 ? 13 : 3;
-    uint32_t eb[kDirs + 1], ew[kDirs + 1];
+    uint32_t take[kOwn], seed[kOwn];  // bit d: the edge in direction d; the seed's weight
     uint32_t mine = 0;
-    const uint32_t c = la == kNone ? 0u : cap(p.v);
-    const int64_t st[6] = {-yz, yz, -(int64_t)a.Z, (int64_t)a.Z, -1, 1};
-    bool side[6];  // v has a neighbour there
-    side[0] = p.x > 0; side[1] = p.x < a.X - 1;
-    side[2] = p.y > 0; side[3] = p.y < a.Y - 1;
-    side[4] = p.z > 0; side[5] = p.z < a.Z - 1;
 #pragma unroll
-    for (int d = 0; d < kDirs; d++) {
-        const int j = kConn26 ? d + 14 : d == 0 ? 22 : d == 1 ? 16 : 14;  // the later half of the 3 x 3 x 3
-        const int dx = j / 9 - 1, dy = j / 3 % 3 - 1, dz = j % 3 - 1;
-        eb[d] = kNone;
-        ew[d] = 0;
-        if (la == kNone || !inside(a, p.x + dx, p.y + dy, p.z + dz)) continue;
-        const int64_t u = p.v + dx * yz + dy * a.Z + dz;
-        const uint32_t lb = a.par[u];
-        if (lb == kNone || lb == la) continue;
-        const uint32_t w = min(c, cap(u));
-        bool best = true;
+    for (int j = 0; j < kOwn; j++) {
+        const int i = tid + j * kBasinWg, h = T::halo(i);
+        const uint32_t la = hl[h];
+        take[j] = seed[j] = 0;
+        const int64_t v = t.in(a, i) ? t.voxel(a, i) : 0;
+        uint32_t s0 = w0[v];
+        if (la == kNone) s0 = 0;
+        uint32_t mask = 0;
 #pragma unroll
-        for (int j2 = 0; j2 < 6; j2++) {
-            const int e = j2 & 1 ? 1 : -1;
-            const int ux = p.x + dx + (j2 < 2 ? e : 0), uy = p.y + dy + (j2 >> 1 == 1 ? e : 0), uz = p.z + dz + (j2 > 3 ? e : 0);
-            if (!kConn26 && ((j2 < 2 && dx) || (j2 >> 1 == 1 && dy) || (j2 > 3 && dz))) continue;
-            const bool ok = side[j2] && inside(a, ux, uy, uz);
-            const int64_t v2 = ok ? p.v + st[j2] : p.v, u2 = ok ? u + st[j2] : u;
-            const bool same = ok && a.par[v2] == la && a.par[u2] == lb;
-            const uint32_t w2 = min(cap(v2), cap(u2));
-            best = best && !(same && (w2 > w || (w2 == w && e > 0)));
-        }
-        if (best) {
-            eb[d] = lb;
-            ew[d] = w;
-            mine++;
-        }
-    }
-    eb[kDirs] = kNone;
-    ew[kDirs] = la == kNone ? 0u : w0[p.v];
-    if (ew[kDirs]) {
-        bool best = true;
+        for (int d = 0; d < kDirs; d++) {
+            const int q = kConn26 ? d + 14 : d == 0 ? 22 : d == 1 ? 16 : 14;  // the later half of the neighbours
+            const int dx = q / 9 - 1, dy = q / 3 % 3 - 1, dz = q % 3 - 1;
+            if (kFlat && dx) continue;
+            const int off = (dx * T::HY + dy) * T::HZ + dz;
+            const uint32_t lb = hl[h + off];
+            if (la != kNone && lb != kNone && lb != la) {
+                const uint32_t w = min(hc[h], hc[h + off]);
+                uint32_t better = 0;
 #pragma unroll
-        for (int j2 = 0; j2 < 6; j2++) {
-            const int64_t v2 = side[j2] ? p.v + st[j2] : p.v;
-            const uint32_t w2 = w0[v2];
-            best = best && !(side[j2] && a.par[v2] == la && (w2 > ew[kDirs] || (w2 == ew[kDirs] && (j2 & 1))));
+                for (int b = 0; b < 6; b++) {
+                    const int e = b & 1 ? 1 : -1;
+                    const int ex = b < 2 ? e : 0, ey = b >> 1 == 1 ? e : 0, ez = b > 3 ? e : 0;
+                    // (inside the halo; along the edge itself there is no such pair)
+                    if ((kFlat && ex) || (!kConn26 && (ex * dx || ey * dy || ez * dz)) || dx + ex > 1 || dx + ex < -1 ||
+                        dy + ey > 1 || dy + ey < -1 || dz + ez > 1 || dz + ez < -1)
+                        continue;
+                    const int side = h + (ex * T::HY + ey) * T::HZ + ez;
+                    const uint32_t w2 = min(hc[side], hc[side + off]);
+                    better |= (uint32_t)(hl[side] == la) & (uint32_t)(hl[side + off] == lb) &
+                              (uint32_t)(e > 0 ? w2 >= w : w2 > w);
+                }
+                mask |= (1u - better) << d;
+            }
         }
-        if (best) {
-            eb[kDirs] = kTop | a.pall;
-            mine++;
+        take[j] = mask;
+        mine += (uint32_t)__popc(mask);
+        if (s0) {
+#pragma unroll
+            for (int b = 0; b < 6; b++) {
+                const int e = b & 1 ? 1 : -1;
+                const int ex = b < 2 ? e : 0, ey = b >> 1 == 1 ? e : 0, ez = b > 3 ? e : 0;
+                if (kFlat && ex) continue;
+                if (hl[h + (ex * T::HY + ey) * T::HZ + ez] != la) continue;  // (so it is inside the image)
+                const uint32_t w2 = w0[v + ((int64_t)ex * a.Y + ey) * a.Z + ez];
+                if (w2 > s0 || (w2 == s0 && e > 0)) {
+                    s0 = 0;
+                    break;
+                }
+            }
+            seed[j] = s0;
+            mine += s0 != 0;
         }
     }
     const uint32_t slot = blockIdx.x % kBasinSlots;
@@ -218,12 +299,23 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_edges(BasinArgs a, Cap cap, 
         if (mine) a.ctl->abort_edges = 1;
         return;
     }
+    uint32_t k = slot * a.ecap + i;
 #pragma unroll
-    for (int d = 0; d <= kDirs; d++) {
-        if (eb[d] == kNone) continue;
-        const uint32_t k = slot * a.ecap + i++;
-        a.ends[k] = (uint64_t)(eb[d] & ~kTop) << 32 | (la & ~kTop);
-        a.wt[k] = ew[d];
+    for (int j = 0; j < kOwn; j++) {
+        const int h = T::halo(tid + j * kBasinWg);
+        const uint32_t la = hl[h] & ~kTop;
+#pragma unroll
+        for (int d = 0; d < kDirs; d++) {
+            if (!(take[j] >> d & 1u)) continue;
+            const int q = kConn26 ? d + 14 : d == 0 ? 22 : d == 1 ? 16 : 14;
+            const int off = ((q / 9 - 1) * T::HY + (q / 3 % 3 - 1)) * T::HZ + q % 3 - 1;
+            a.ends[k] = (uint64_t)(hl[h + off] & ~kTop) << 32 | la;
+            a.wt[k++] = min(hc[h], hc[h + off]);
+        }
+        if (seed[j]) {
+            a.ends[k] = (uint64_t)a.pall << 32 | la;
+            a.wt[k++] = seed[j];
+        }
     }
 }
 
@@ -273,7 +365,7 @@ __global__ __launch_bounds__(256) void k_basin_offer(BasinArgs a, int round) {
         offer(best, x, key, on && x != a.pall);
         offer(best, y, key, on && y != a.pall);
     }
-    if (live) a.ctl->live[round] = 1;
+    raise(&a.ctl->live[round], live);
 }
 
 // Every root with an edge hooks under the root at its best edge's other end.
@@ -317,7 +409,7 @@ __global__ __launch_bounds__(256) void k_basin_flat(BasinArgs a, int hops, int r
         if (to(h) != t0) __hip_atomic_store(&a.H[p], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         left |= q == hops;
     }
-    if (left) a.ctl->deep[round] = 1;
+    raise(&a.ctl->deep[round], left);
 }
 
 // w[v] = min(cap(v), B(label)).
@@ -345,30 +437,47 @@ __global__ __launch_bounds__(256) void k_basin_finish(BasinArgs a, Cap cap, uint
     w[v] = r;
 }
 
+template <bool kFlat>
+int64_t tiles(const BasinArgs& a) {
+    return (int64_t)((a.X + Tile<kFlat>::TX - 1) / Tile<kFlat>::TX) * a.nty * a.ntz;
+}
+
 inline unsigned blocks(int64_t n, unsigned t = 256) { return (unsigned)((n + t - 1) / t); }
 
-template <class Cap, bool kConn26>
+template <class Cap, bool kConn26, bool kFlat>
 hipError_t start(const BasinArgs& a, Cap cap, const uint32_t* w, hipStream_t s) {
-    const unsigned nb = blocks(a.n, kBasinWg), few = std::min<unsigned>(blocks(a.n, 256), 2048);
-    hipLaunchKernelGGL((k_basin_up<Cap, kConn26>), dim3(nb), dim3(kBasinWg), 0, s, a, cap);
+    const unsigned nb = (unsigned)(tiles<kFlat>(a)), few = std::min<unsigned>(blocks(a.n), 2048);
+    hipLaunchKernelGGL((k_basin_up<Cap, kConn26, kFlat>), dim3(nb), dim3(kBasinWg), 0, s, a, cap);
     int pass = 0;
-    // climbs of up to 2^5, 2^13, 2^21, 2^29 and 2^37 voxels
+    // climbs of up to 2^5, 2^13, 2^21, 2^29 and 2^37 tiles
     for (int64_t reach = kBasinHops; pass == 0 || reach < 256 * a.n; reach *= 256, pass++)
         hipLaunchKernelGGL(k_basin_label, dim3(few), dim3(256), 0, s, a, pass ? 256 : kBasinHops, pass);
-    hipLaunchKernelGGL((k_basin_edges<Cap, kConn26>), dim3(nb), dim3(kBasinWg), 0, s, a, cap, w);
+    hipLaunchKernelGGL((k_basin_edges<Cap, kConn26, kFlat>), dim3(nb), dim3(kBasinWg), 0, s, a, cap, w);
     return hipGetLastError();
+}
+template <class Cap>
+hipError_t start(const BasinArgs& a, Cap cap, bool conn26, const uint32_t* w, hipStream_t s) {
+    if (a.X == 1) return conn26 ? start<Cap, true, true>(a, cap, w, s) : start<Cap, false, true>(a, cap, w, s);
+    return conn26 ? start<Cap, true, false>(a, cap, w, s) : start<Cap, false, false>(a, cap, w, s);
 }
 
 }  // namespace
 
-void basin_caps(BasinArgs& a, int64_t n) {
-    // each slot takes every kBasinSlots-th workgroup's voxels
-    const int64_t per = ((n + kBasinWg - 1) / kBasinWg + kBasinSlots - 1) / kBasinSlots * kBasinWg;
-    const bool all = n <= (1 << 20);  // room for whatever the image holds
+void basin_caps(BasinArgs& a, ibip_dims d) {
+    a.X = d.X;
+    a.Y = d.Y;
+    a.Z = d.Z;
+    a.n = nvox(d);
+    const int ty = a.X == 1 ? Tile<true>::TY : Tile<false>::TY;
+    a.nty = (a.Y + ty - 1) / ty;
+    a.ntz = (a.Z + Tile<true>::TZ - 1) / Tile<true>::TZ;
+    // each slot takes every kBasinSlots-th tile's voxels
+    const int64_t nt = a.X == 1 ? tiles<true>(a) : tiles<false>(a);
+    const int64_t per = (nt + kBasinSlots - 1) / kBasinSlots * kTileVoxels;
+    const bool all = per * kBasinSlots <= 1 << 20;  // room for whatever the image holds
     a.pcap = (uint32_t)(all ? per : per / 8);
     a.ecap = (uint32_t)(all ? 4 * per : per / 2);
     a.pall = a.pcap * kBasinSlots;
-    a.n = n;
 }
 
 size_t basin_bytes(const BasinArgs& a) {
@@ -389,8 +498,7 @@ void basin_carve(BasinArgs& a, void* mem) {
 
 hipError_t launch_basin_graph(const BasinArgs& a, const int32_t* seq, const uint32_t* cap32, bool conn26,
                               const uint32_t* w, hipStream_t s) {
-    if (cap32) return conn26 ? start<CapU32, true>(a, CapU32{cap32}, w, s) : start<CapU32, false>(a, CapU32{cap32}, w, s);
-    return conn26 ? start<CapSeq, true>(a, CapSeq{seq}, w, s) : start<CapSeq, false>(a, CapSeq{seq}, w, s);
+    return cap32 ? start(a, CapU32{cap32}, conn26, w, s) : start(a, CapSeq{seq}, conn26, w, s);
 }
 
 hipError_t launch_basin_rounds(const BasinArgs& a, int from, int to, hipStream_t s) {

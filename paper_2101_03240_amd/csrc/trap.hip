@@ -9,7 +9,8 @@
 // capacity on the path (a maximin, or widest-path, value), v is free iff
 // W(v) >= seq[v]. The paper's reverse sweep over thresholds computes the same
 // predicate one level at a time; W gives it for every level at once and is
-// computed here by data-parallel relaxation to the fixed point
+// computed on the graph of the image's basins (basin.hip), or, where that has no
+// room, by data-parallel relaxation to the fixed point
 //   W(v) = max(W0(v), min(cap(v), max over face neighbours u of W(u))).
 //
 // Relaxation runs per 8 x 16 x 32 tile: the tile and a one-voxel halo sit in
@@ -334,18 +335,15 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-// By basins: *done unless there is no scratch or an image with more basins or
-// edges than its lists hold (noise of single voxels), which the sweeps take.
+// By basins: *done unless there is no scratch (13 B a voxel, in the buffer that
+// the invasion's tree has had) or the image, of more than 2^20 voxels, has more
+// basins than an eighth of them or more edges than half (noise of single voxels;
+// blurred noise and grains have 1/60 and 1/6): those take the sweeps.
 static ibip_status reconstruct_basins(ibip_ctx* ctx, const int32_t* seq, const uint32_t* cap32, bool conn26,
                                       ibip_dims d, uint32_t* w, int* n_iter, bool* done) {
     hipStream_t s = ctx->stream;
     BasinArgs a{};
-    basin_caps(a, nvox(d));
-    a.X = d.X;
-    a.Y = d.Y;
-    a.Z = d.Z;
-    a.divZ = make_fastdiv((uint32_t)d.Z);
-    a.divY = make_fastdiv((uint32_t)d.Y);
+    basin_caps(a, d);
     void* mem = ensure(ctx, B_TREE, basin_bytes(a));
     uint32_t* h = (uint32_t*)pinned(ctx, 4096);
     if (!mem || !h) return IBIP_OK;
@@ -354,7 +352,7 @@ static ibip_status reconstruct_basins(ibip_ctx* ctx, const int32_t* seq, const u
     ibip_status rc;
     if ((rc = hip_check(ctx, hipMemsetAsync(a.ctl, 0, sizeof(BasinCtl), s), "memset")) != IBIP_OK) return rc;
     if ((rc = hip_check(ctx, launch_basin_graph(a, seq, cap32, conn26, w, s), "basins")) != IBIP_OK) return rc;
-    for (int from = 0, to = 8; from < kBasinRounds; from = to, to += 8) {
+    for (int from = 0, to = 10; from < kBasinRounds; from = to, to += 11) {
         if ((rc = hip_check(ctx, launch_basin_rounds(a, from, to, s), "basin rounds")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, launch_basin_finish(a, seq, cap32, w, to, s), "basins")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, hipMemcpyAsync(h, a.ctl, offsetof(BasinCtl, np), hipMemcpyDeviceToHost, s),
