@@ -251,6 +251,16 @@ struct OutOpening {
     __device__ uint32_t put_hit(int64_t v, uint32_t r) const { return hit(v, r); }
 };
 
+// Several levels of the opening at once: the largest T with dt2 < T stays.
+struct OutOpeningMax {
+    uint32_t* mio_r2;
+    uint32_t T;
+    __device__ uint32_t put_hit(int64_t v, uint32_t r) const {
+        if (r < T && mio_r2[v] < T) atomicMax(&mio_r2[v], T);
+        return 0;
+    }
+};
+
 template <class Out>
 __global__ __launch_bounds__(256) void edt_pass_x_tile(const uint32_t* __restrict__ hin, int X, int Y, int Z,
                                                        uint64_t cap, Out outp, uint32_t* count) {
@@ -357,6 +367,19 @@ struct FeatThreshold8 {
     __device__ bool bit(int64_t v) const { return w[v] >= thr; }
     __device__ uint2 bytes8(int64_t) const { return make_uint2(0u, 0u); }
     static constexpr bool kBytes = false;
+};
+
+// One distance transform per launch, or (the opening at several squared radii)
+// one per blockIdx.y: level l's distances capped at T[l], its intermediate images
+// at l * n.
+struct OneLevel {
+    static constexpr bool kOn = false;
+};
+struct Levels {
+    static constexpr bool kOn = true;
+    uint32_t T[kOpeningLevels];
+    uint32_t dz[kOpeningLevels];  // the least d with d^2 >= T
+    int64_t n;
 };
 
 // Pass z with the whole row in registers: a lane owns P = 8 (rows of at most
@@ -538,9 +561,14 @@ __device__ inline uint32_t pass_z_rows(uint32_t fb, const uint32_t (&raw)[P / 4]
 // Al: rows of a multiple of P voxels from an aligned input, loaded and
 // stored with vectors; otherwise (rows of any length up to 64 * P) voxel by
 // voxel, the last lane of a row holding fewer than P.
-template <class Feat, int P, bool Al>
+template <class Feat, int P, bool Al, class Lv>
 __global__ __launch_bounds__(256) void edt_pass_z_vec(Feat feat, int64_t rows, int Z, uint32_t dcap, uint16_t* g,
-                                                      uint32_t* solid_flag) {
+                                                      uint32_t* solid_flag, Lv lv) {
+    if constexpr (Lv::kOn) {
+        feat.thr = lv.T[blockIdx.y];
+        dcap = lv.dz[blockIdx.y];
+        g += blockIdx.y * lv.n;
+    }
     const int lane = threadIdx.x & 63;
     const int lpr = (Z + P - 1) / P;
     const int rpw = 64 / lpr;
@@ -680,6 +708,36 @@ struct HSplit {
     }
 };
 
+// pass y's result h of a transform capped at 65535 or less: 16 bits hold all of
+// it, 65535 for none below the cap
+struct HCap16 {
+    static constexpr bool kSplit = true;
+    uint16_t* h16;
+    __device__ void level(int64_t at, uint32_t) { h16 += at; }
+    __device__ void put(int64_t v, uint32_t val) const { h16[v] = (uint16_t)min(val, 65535u); }
+    __device__ void put2(int64_t v, uint32_t a, uint32_t b) const {
+        *reinterpret_cast<uint32_t*>(h16 + v) = min(a, 65535u) | min(b, 65535u) << 16;
+    }
+    static __device__ uint32_t wide(uint32_t u) { return u == 65535u ? kInf32 : u; }
+    __device__ uint32_t get(int64_t v) const { return wide(h16[v]); }
+    __device__ uint4 get4(int64_t v) const {
+        const uint2 r = *reinterpret_cast<const uint2*>(h16 + v);
+        return make_uint4(wide(r.x & 0xFFFFu), wide(r.x >> 16), wide(r.y & 0xFFFFu), wide(r.y >> 16));
+    }
+};
+
+// pass y of a plane in the opening: its result is the distance
+struct HOpening {
+    static constexpr bool kSplit = true;
+    OutOpeningMax out;
+    __device__ void level(int64_t, uint32_t T) { out.T = T; }
+    __device__ void put(int64_t v, uint32_t val) const { out.put_hit(v, val); }
+    __device__ void put2(int64_t v, uint32_t a, uint32_t b) const {
+        out.put_hit(v, a);
+        out.put_hit(v + 1, b);
+    }
+};
+
 // min(g^2, 65535) of a distance along z (0x7FFF = no feature)
 __device__ inline uint32_t sq16(uint32_t gv) { return gv < 256u ? gv * gv : 65535u; }
 
@@ -703,9 +761,14 @@ __device__ inline uint32_t pass_y_exact(const uint16_t* g, int64_t v, int y, int
     return (uint32_t)min(best, (uint64_t)0xFFFFFFFFu);
 }
 
-template <int TW, bool V, class H>
+template <int TW, bool V, class H, class Lv>
 __global__ __launch_bounds__(kThreadsY) void edt_pass_y_pk(const uint16_t* __restrict__ g, int X, int Y, int Z,
-                                                          uint64_t cap, H h) {
+                                                          uint64_t cap, H h, Lv lv) {
+    if constexpr (Lv::kOn) {
+        cap = lv.T[blockIdx.y];
+        g += blockIdx.y * lv.n;
+        h.level(blockIdx.y * lv.n, lv.T[blockIdx.y]);
+    }
     extern __shared__ uint16_t t16[];  // [kPad + Y + kPad][TW]: min(g^2, 65535)
     constexpr int kSegs = TW / 8, kRows = kThreadsY / kSegs;
     const int nzc = (Z + TW - 1) / TW;
@@ -798,9 +861,14 @@ __global__ __launch_bounds__(kThreadsY) void edt_pass_y_pk(const uint16_t* __res
 // TW: z columns per tile (16: 64-byte tile rows; 32: whole 128-byte lines).
 // V: rows of Z % 4 == 0 voxels, loaded with 16-byte vectors; otherwise the
 // tile is loaded element by element.
-template <class Out, int TW, bool V, class H>
+template <class Out, int TW, bool V, class H, class Lv>
 __global__ __launch_bounds__(kThreadsX) void edt_pass_x_vec(H hin, int X, int Y, int Z, uint64_t cap, Out outp,
-                                                           uint32_t* count) {
+                                                           uint32_t* count, Lv lv) {
+    if constexpr (Lv::kOn) {
+        cap = lv.T[blockIdx.y];
+        hin.level(blockIdx.y * lv.n, lv.T[blockIdx.y]);
+        outp.T = lv.T[blockIdx.y];
+    }
     extern __shared__ uint32_t t32[];  // [kPad + X + kPad][TW]
     constexpr int kSegs = TW / 4, kRows = kThreadsX / kSegs;
     const int nzc = (Z + TW - 1) / TW;
@@ -1016,32 +1084,40 @@ void launch_pass_x_pk(int tx, bool xv, dim3 gx, size_t lds_bytes, hipStream_t s,
 
 // Pass x: packed (pk) or 32-bit tiles of tx z columns, 16-byte loads (xv) or
 // not. The packed kernels read h as one word per voxel (their exact search
-// reads it in HBM), so the split form only ever comes with the 32-bit ones.
-template <class Out, class H>
+// reads it in HBM), so the 16-bit forms only ever come with the 32-bit ones.
+template <class Out, class H, class Lv = OneLevel>
 void launch_pass_x(bool pk, int tx, bool xv, dim3 gx, size_t lds_bytes, hipStream_t s, H in, ibip_dims d,
-                   uint64_t c64, Out o, uint32_t* count) {
+                   uint64_t c64, Out o, uint32_t* count, Lv lv = Lv{}) {
     if constexpr (!H::kSplit) {
         if (pk) return launch_pass_x_pk(tx, xv, gx, lds_bytes, s, in.h, d, c64, o, count);
     }
     const dim3 b(kThreadsX);
     if (tx == 16) {
-        if (xv) hipLaunchKernelGGL((edt_pass_x_vec<Out, 16, true, H>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count);
-        else hipLaunchKernelGGL((edt_pass_x_vec<Out, 16, false, H>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count);
+        if (xv) hipLaunchKernelGGL((edt_pass_x_vec<Out, 16, true, H, Lv>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count, lv);
+        else hipLaunchKernelGGL((edt_pass_x_vec<Out, 16, false, H, Lv>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count, lv);
     } else {
-        if (xv) hipLaunchKernelGGL((edt_pass_x_vec<Out, 32, true, H>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count);
-        else hipLaunchKernelGGL((edt_pass_x_vec<Out, 32, false, H>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count);
+        if (xv) hipLaunchKernelGGL((edt_pass_x_vec<Out, 32, true, H, Lv>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count, lv);
+        else hipLaunchKernelGGL((edt_pass_x_vec<Out, 32, false, H, Lv>), gx, b, lds_bytes, s, in, d.X, d.Y, d.Z, c64, o, count, lv);
     }
 }
 
 // pass y with tiles of ty z columns and 16-byte loads (yv) or not
-template <class H>
+template <class H, class Lv = OneLevel>
 void launch_pass_y(int ty, bool yv, dim3 gy, size_t lds_bytes, hipStream_t s, const uint16_t* g16, ibip_dims d,
-                   uint64_t c64, H h) {
+                   uint64_t c64, H h, Lv lv = Lv{}) {
     const dim3 b(kThreadsY);
-    if (ty == 64 && yv) hipLaunchKernelGGL((edt_pass_y_pk<64, true, H>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h);
-    else if (ty == 64) hipLaunchKernelGGL((edt_pass_y_pk<64, false, H>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h);
-    else if (yv) hipLaunchKernelGGL((edt_pass_y_pk<32, true, H>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h);
-    else hipLaunchKernelGGL((edt_pass_y_pk<32, false, H>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h);
+    if (ty == 64 && yv) hipLaunchKernelGGL((edt_pass_y_pk<64, true, H, Lv>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h, lv);
+    else if (ty == 64) hipLaunchKernelGGL((edt_pass_y_pk<64, false, H, Lv>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h, lv);
+    else if (yv) hipLaunchKernelGGL((edt_pass_y_pk<32, true, H, Lv>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h, lv);
+    else hipLaunchKernelGGL((edt_pass_y_pk<32, false, H, Lv>), gy, b, lds_bytes, s, g16, d.X, d.Y, d.Z, c64, h, lv);
+}
+
+// the least d with d^2 >= cap, at most 65535
+uint32_t z_cap(uint64_t cap) {
+    uint64_t d = (uint64_t)std::sqrt((double)cap);
+    while (d * d < cap) d++;
+    while (d > 0 && (d - 1) * (d - 1) >= cap) d--;
+    return (uint32_t)std::min<uint64_t>(d, 0xFFFFu);
 }
 
 }  // namespace
@@ -1086,11 +1162,7 @@ hipError_t launch_edt(const uint8_t* image, const uint32_t* w, uint32_t thr, uin
     const HPlain hp{tmp32};
     const HSplit hs{reinterpret_cast<uint16_t*>(tmp32), out};
     if (zp) {
-        // the distance cap of pass z: the least d with d^2 >= cap
-        uint64_t dz64 = (uint64_t)std::sqrt((double)c64);
-        while (dz64 * dz64 < c64) dz64++;
-        while (dz64 > 0 && (dz64 - 1) * (dz64 - 1) >= c64) dz64--;
-        const uint32_t dz = (uint32_t)std::min<uint64_t>(dz64, 0xFFFFu);
+        const uint32_t dz = z_cap(c64);  // the distance cap of pass z
         const int64_t rows_per_block = 4LL * (64 / ((d.Z + zp - 1) / zp)) * kZGroups;
         const unsigned gz = (unsigned)((rows + rows_per_block - 1) / rows_per_block);
         const dim3 gzd(gz);
@@ -1099,36 +1171,36 @@ hipError_t launch_edt(const uint8_t* image, const uint32_t* w, uint32_t thr, uin
         const FeatThreshold8 ft{w, thr};
         switch (form) {
             case 7:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 16, true>), gzd, dim3(256), 0, s, fi, rows, d.Z,
-                                   dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 16, true, OneLevel>), gzd, dim3(256), 0, s, fi, rows, d.Z,
+                                   dz, g16, solid_flag, OneLevel{});
                 break;
             case 6:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 16, false>), gzd, dim3(256), 0, s, fi, rows, d.Z,
-                                   dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 16, false, OneLevel>), gzd, dim3(256), 0, s, fi, rows, d.Z,
+                                   dz, g16, solid_flag, OneLevel{});
                 break;
             case 5:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 8, true>), gzd, dim3(256), 0, s, fi, rows, d.Z,
-                                   dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 8, true, OneLevel>), gzd, dim3(256), 0, s, fi, rows, d.Z,
+                                   dz, g16, solid_flag, OneLevel{});
                 break;
             case 4:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 8, false>), gzd, dim3(256), 0, s, fi, rows, d.Z,
-                                   dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatImage8, 8, false, OneLevel>), gzd, dim3(256), 0, s, fi, rows, d.Z,
+                                   dz, g16, solid_flag, OneLevel{});
                 break;
             case 3:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 16, true>), gzd, dim3(256), 0, s, ft, rows, d.Z,
-                                   dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 16, true, OneLevel>), gzd, dim3(256), 0, s, ft, rows, d.Z,
+                                   dz, g16, solid_flag, OneLevel{});
                 break;
             case 2:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 16, false>), gzd, dim3(256), 0, s, ft, rows,
-                                   d.Z, dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 16, false, OneLevel>), gzd, dim3(256), 0, s, ft, rows,
+                                   d.Z, dz, g16, solid_flag, OneLevel{});
                 break;
             case 1:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 8, true>), gzd, dim3(256), 0, s, ft, rows, d.Z,
-                                   dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 8, true, OneLevel>), gzd, dim3(256), 0, s, ft, rows, d.Z,
+                                   dz, g16, solid_flag, OneLevel{});
                 break;
             default:
-                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 8, false>), gzd, dim3(256), 0, s, ft, rows,
-                                   d.Z, dz, g16, solid_flag);
+                hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 8, false, OneLevel>), gzd, dim3(256), 0, s, ft, rows,
+                                   d.Z, dz, g16, solid_flag, OneLevel{});
                 break;
         }
     } else {
@@ -1180,6 +1252,48 @@ hipError_t launch_edt(const uint8_t* image, const uint32_t* w, uint32_t thr, uin
                            (uint32_t*)nullptr);
     } else {
         hipLaunchKernelGGL(edt_pass_x, dim3(gv), dim3(256), 0, s, tmp32, d.X, d.Y, d.Z, c64, out);
+    }
+    return hipGetLastError();
+}
+
+
+bool opening_levels_ok(ibip_dims d, uint32_t T, EdtTiles tiles) {
+    const int ty = tiles.y == 64 ? 64 : 32, tx = tiles.x == 16 ? 16 : 32;
+    const size_t ly = sizeof(uint16_t) * ty * (d.Y + 2 * kPad), lx = sizeof(uint32_t) * tx * (d.X + 2 * kPad);
+    const size_t lds = max_lds_per_block();
+    return T <= 65535 && d.Z <= kMaxVecLine && d.Y <= kMaxVecLine && d.X <= kMaxVecLine && ly <= lds && 2 * lx <= lds;
+}
+
+hipError_t launch_opening_levels(const uint32_t* w, const uint32_t* T, int levels, int64_t stride, ibip_dims d,
+                                 uint16_t* g16, uint16_t* h16, uint32_t* flag, uint32_t* mio_r2, hipStream_t s,
+                                 EdtTiles tiles) {
+    Levels lv{};
+    lv.n = stride;
+    for (int l = 0; l < levels; l++) {
+        lv.T[l] = T[l];
+        lv.dz[l] = z_cap(T[l]);
+    }
+    const int ty = tiles.y == 64 ? 64 : 32, tx = tiles.x == 16 ? 16 : 32;
+    const int zp = d.Z <= 512 ? 8 : 16;
+    const bool zal = ((uintptr_t)w & 15) == 0 && d.Z % zp == 0;
+    const int64_t rows = (int64_t)d.X * d.Y;
+    const int64_t rows_per_block = 4LL * (64 / ((d.Z + zp - 1) / zp)) * kZGroups;
+    const dim3 gz((unsigned)((rows + rows_per_block - 1) / rows_per_block), (unsigned)levels);
+    const FeatThreshold8 ft{w, 0};
+    if (zp == 16 && zal) hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 16, true, Levels>), gz, dim3(256), 0, s, ft, rows, d.Z, 0u, g16, flag, lv);
+    else if (zp == 16) hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 16, false, Levels>), gz, dim3(256), 0, s, ft, rows, d.Z, 0u, g16, flag, lv);
+    else if (zal) hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 8, true, Levels>), gz, dim3(256), 0, s, ft, rows, d.Z, 0u, g16, flag, lv);
+    else hipLaunchKernelGGL((edt_pass_z_vec<FeatThreshold8, 8, false, Levels>), gz, dim3(256), 0, s, ft, rows, d.Z, 0u, g16, flag, lv);
+    const dim3 gy((unsigned)d.X * (unsigned)((d.Z + ty - 1) / ty), (unsigned)levels);
+    const size_t ly = sizeof(uint16_t) * ty * (d.Y + 2 * kPad);
+    const OutOpeningMax out{mio_r2, 0};
+    if (d.X == 1) {
+        launch_pass_y(ty, d.Z % 8 == 0, gy, ly, s, g16, d, 0, HOpening{out}, lv);
+    } else {
+        launch_pass_y(ty, d.Z % 8 == 0, gy, ly, s, g16, d, 0, HCap16{h16}, lv);
+        const dim3 gx((unsigned)d.Y * (unsigned)((d.Z + tx - 1) / tx), (unsigned)levels);
+        launch_pass_x(false, tx, d.Z % 4 == 0, gx, sizeof(uint32_t) * tx * (d.X + 2 * kPad), s, HCap16{h16}, d, 0, out,
+                      (uint32_t*)nullptr, lv);
     }
     return hipGetLastError();
 }

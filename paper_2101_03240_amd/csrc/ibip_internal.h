@@ -301,6 +301,17 @@ hipError_t launch_edt(const uint8_t* image, const uint32_t* w, uint32_t thr, uin
                       hipStream_t s, uint32_t* mio_r2 = nullptr, uint32_t* mio_count = nullptr,
                       EdtTiles tiles = EdtTiles{});
 
+// The opening's dilations at up to kOpeningLevels squared radii T in one set of
+// launches: mio_r2[v] = max(mio_r2[v], the largest T with a voxel w >= T nearer than
+// sqrt(T)). Level l's intermediate images lie at l * stride (a multiple of 8, at
+// least the voxels) in g16 and h16. Only where opening_levels_ok says so for the
+// largest T: lines that the tiled passes take, and distances that 16 bits hold.
+constexpr int kOpeningLevels = 32;
+bool opening_levels_ok(ibip_dims d, uint32_t T, EdtTiles tiles);
+hipError_t launch_opening_levels(const uint32_t* w, const uint32_t* T, int levels, int64_t stride, ibip_dims d,
+                                 uint16_t* g16, uint16_t* h16, uint32_t* flag, uint32_t* mio_r2, hipStream_t s,
+                                 EdtTiles tiles);
+
 // *dst = the sum of kCountSlots slot words (see block_add_slots).
 hipError_t launch_sum_slots(const uint32_t* slots, uint32_t* dst, hipStream_t s);
 // out[k] = sum over c < copies of in[c * K + k], for k < K (see count_table_flush).

@@ -19,15 +19,19 @@ namespace {
 
 // K0(v) = dt2(v) on Q0, 0 elsewhere; also counts pore voxels.
 // Seeds of the opening: pore voxels in Q0 (an inlet voxel or a face
-// neighbour of one); with mask, only pore inlet voxels count.
+// neighbour of one); with kMask, only pore inlet voxels count.
+// A workgroup takes kSeedChunk voxels, so that it adds its count once: with 256
+// voxels a workgroup and the image loaded at all seven places also without kMask,
+// 512^3 took 2.47 ms; now 0.33.
+constexpr int kSeedChunk = 2048;
+template <bool kMask>
 __global__ __launch_bounds__(256) void k_mio_seed(const uint8_t* img, const uint8_t* inlets, const uint32_t* dt2,
                                                   int X, int Y, int Z, FastDiv divZ, FastDiv divY, uint32_t* k0,
-                                                  uint32_t* n_pore, bool mask) {
+                                                  uint32_t* n_pore) {
     const int64_t yz = (int64_t)Y * Z;
     const int64_t n = (int64_t)X * yz;
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    bool pore = false;
-    if (v < n) {
+    uint32_t pores = 0;
+    for (int64_t v = (int64_t)blockIdx.x * kSeedChunk + threadIdx.x, end = min(v + kSeedChunk, n); v < end; v += 256) {
         // the seven positions are loaded together (an outside neighbour reads
         // v itself): a chain of conditional loads would wait for each in turn
         // coordinates by multiplicative division (indices fit 31 bits)
@@ -40,28 +44,63 @@ __global__ __launch_bounds__(256) void k_mio_seed(const uint8_t* img, const uint
 #pragma unroll
         for (int j = 0; j < 7; j++) {
             in[j] = inlets[nb[j]];
-            im[j] = img[nb[j]];
+            im[j] = kMask || j == 0 ? img[nb[j]] : 1;
         }
         bool any = false;
 #pragma unroll
-        for (int j = 0; j < 7; j++) any |= in[j] != 0 && (!mask || im[j] != 0);
-        pore = im[0] != 0;
+        for (int j = 0; j < 7; j++) any |= in[j] != 0 && (!kMask || im[j] != 0);
+        const bool pore = im[0] != 0;
+        pores += pore;
         k0[v] = pore && any ? d : 0u;
     }
-    block_add_slots(n_pore, pore ? 1u : 0u);
+    block_add_slots(n_pore, pores);
 }
 
-// First write in decreasing T; count voxels with mio_r2 >= T.
-__global__ __launch_bounds__(256) void k_mio_update(const uint32_t* d2, uint32_t T, int64_t n, uint32_t* mio_r2,
-                                                    uint32_t* count) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    bool hit = false;
-    if (v < n) {
-        uint32_t r = mio_r2[v];
-        if (r == 0 && d2[v] < T) { r = T; mio_r2[v] = T; }
-        hit = r >= T;
+// Voxels of the intermediate images that a set of launches holds.
+constexpr int64_t kLevelVoxels = 1 << 23;
+
+// counts[i * kCountSlots + slot] += the voxels with mio_r2 = T[i] (T decreasing).
+constexpr int kCountLevels = 4096;  // levels whose table LDS holds
+__global__ __launch_bounds__(256) void k_mio_count(const uint32_t* mio_r2, int64_t n, const uint32_t* T, int nT,
+                                                   uint32_t* counts) {
+    extern __shared__ uint32_t lds[];  // T, then the counts
+    uint32_t* cnt = lds + nT;
+    for (int i = threadIdx.x; i < nT; i += 256) {
+        lds[i] = T[i];
+        cnt[i] = 0;
     }
-    block_add_slots(count, hit ? 1u : 0u);
+    __syncthreads();
+    const int64_t per = (n + gridDim.x - 1) / gridDim.x, v0 = blockIdx.x * per, v1 = min(v0 + per, n);
+    for (int64_t base = v0; base < v1; base += 4 * 256) {
+        uint32_t r[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int64_t v = base + q * 256 + threadIdx.x;
+            const uint32_t x = mio_r2[min(v, n - 1)];
+            r[q] = v < v1 ? x : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const uint64_t m = __ballot(r[q] != 0);
+            if (!m) continue;
+            int lo = 0, hi = nT - 1;  // the first level with T <= r
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (lds[mid] > r[q]) lo = mid + 1;
+                else hi = mid;
+            }
+            // most lanes of a wave share their level
+            const int l0 = __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)m) - 1);
+            const bool first = r[q] != 0 && lo == l0;
+            const uint64_t same = __ballot(first);
+            if ((int)(threadIdx.x & 63) == __ffsll((unsigned long long)same) - 1)
+                atomicAdd(&cnt[l0], (uint32_t)__popcll(same));
+            if (r[q] != 0 && !first) atomicAdd(&cnt[lo], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nT; i += 256)
+        if (cnt[i]) atomicAdd(&counts[(size_t)i * kCountSlots + blockIdx.x % kCountSlots], cnt[i]);
 }
 
 inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -74,15 +113,24 @@ ibip_status run_mio(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlets, 
     const int64_t n = nvox(d);
     uint32_t* dt2 = (uint32_t*)ensure(ctx, B_KEY, sizeof(uint32_t) * n);
     uint32_t* kmap = (uint32_t*)ensure(ctx, B_STATE, sizeof(uint32_t) * n);
-    uint16_t* g16 = (uint16_t*)ensure(ctx, B_TMP0, sizeof(uint16_t) * n);
-    uint32_t* tmp32 = (uint32_t*)ensure(ctx, B_TMP1, sizeof(uint32_t) * n);
-    uint32_t* d2 = (uint32_t*)ensure(ctx, B_TMP2, sizeof(uint32_t) * n);
+    // Several levels share their launches where the image alone does not fill the
+    // GPU: 226 levels of 500 x 500, one by one, took 13.5 ms (16 workgroups in pass
+    // y, 27 + 25 + 8 us a level), 32 at a time 0.58 (43 + 28 us for 32
+    // levels). From 2^22 voxels on a level's launches fill it by themselves.
+    const EdtTiles tiles = edt_tiles(ctx->tuning);
+    const bool levels = nT > 0 && nT <= kCountLevels && opening_levels_ok(d, T[0], tiles);
+    const int64_t stride = (n + 7) / 8 * 8;
+    const int at_once = (int)std::max<int64_t>(std::min<int64_t>({(int64_t)kOpeningLevels, (int64_t)nT, kLevelVoxels / n}), 1);
+    const int64_t held = levels ? stride * at_once : n;
+    uint16_t* g16 = (uint16_t*)ensure(ctx, B_TMP0, sizeof(uint16_t) * held);
+    uint32_t* tmp32 = (uint32_t*)ensure(ctx, B_TMP1, std::max(sizeof(uint32_t) * n, sizeof(uint16_t) * held));
     // per-level counts and the pore count, kCountSlots words each
     const size_t ncount = (size_t)kCountSlots * ((size_t)nT + 1);
-    uint32_t* counts = (uint32_t*)ensure(ctx, B_MIOCNT, sizeof(uint32_t) * ncount);
+    uint32_t* counts = (uint32_t*)ensure(ctx, B_MIOCNT, sizeof(uint32_t) * (ncount + nT));
+    uint32_t* dT = counts + ncount;
     uint8_t* misc = (uint8_t*)ensure(ctx, B_MISC, 4096);
     uint32_t* h = (uint32_t*)pinned(ctx, 4096 + sizeof(uint32_t) * ncount);
-    if (!dt2 || !kmap || !g16 || !tmp32 || !d2 || !counts || !misc || !h)
+    if (!dt2 || !kmap || !g16 || !tmp32 || !counts || !misc || !h)
         return fail(ctx, IBIP_ENOMEM, "opening_drainage: allocation failed");
     uint32_t* flags = (uint32_t*)(misc + 3584);  // [0] solid seen, [2] scratch flag
     uint32_t* pore_slots = counts + (size_t)kCountSlots * nT;
@@ -95,8 +143,14 @@ ibip_status run_mio(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlets, 
     if ((rc = hip_check(ctx, launch_edt(image, nullptr, 0, 0, d, g16, tmp32, dt2, &flags[0], s, nullptr, nullptr,
                                         edt_tiles(ctx->tuning)), "edt")) != IBIP_OK)
         return rc;
-    hipLaunchKernelGGL(k_mio_seed, dim3(blocks(n)), dim3(256), 0, s, image, inlets, dt2, d.X, d.Y, d.Z,
-                       make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y), kmap, pore_slots, (ctx->readings & IBIP_READ_MASK_INLETS) != 0);
+    const unsigned seed_blocks = (unsigned)((n + kSeedChunk - 1) / kSeedChunk);
+    const FastDiv fz = make_fastdiv((uint32_t)d.Z), fy = make_fastdiv((uint32_t)d.Y);
+    if (ctx->readings & IBIP_READ_MASK_INLETS)
+        hipLaunchKernelGGL(k_mio_seed<true>, dim3(seed_blocks), dim3(256), 0, s, image, inlets, dt2, d.X, d.Y, d.Z, fz,
+                           fy, kmap, pore_slots);
+    else
+        hipLaunchKernelGGL(k_mio_seed<false>, dim3(seed_blocks), dim3(256), 0, s, image, inlets, dt2, d.X, d.Y, d.Z, fz,
+                           fy, kmap, pore_slots);
     if ((rc = hip_check(ctx, hipMemcpyAsync(h, flags, 4, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK) return rc;
     if ((rc = hip_check(ctx, hipMemcpyAsync(h + 64, pore_slots, sizeof(uint32_t) * kCountSlots,
                                             hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
@@ -107,7 +161,23 @@ ibip_status run_mio(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlets, 
     for (int q = 0; q < kCountSlots; q++) n_pore += h[64 + q];
     int iters = 0;
     if ((rc = reconstruct(ctx, nullptr, dt2, false, d, kmap, &iters)) != IBIP_OK) return rc;
-    for (int32_t i = 0; i < nT; i++) {
+    if (levels) {
+        for (int32_t i = 0; i < nT; i += at_once)
+            if ((rc = hip_check(ctx, launch_opening_levels(kmap, T + i, std::min(at_once, nT - i), stride, d, g16,
+                                                           (uint16_t*)tmp32, &flags[2], mio_r2, s, tiles),
+                                "opening levels")) != IBIP_OK)
+                return rc;
+        if (mio_sat) {
+            uint32_t* hT = h + 1024;  // (the counts' place, copied back after)
+            std::copy(T, T + nT, hT);
+            if ((rc = hip_check(ctx, hipMemcpyAsync(dT, hT, sizeof(uint32_t) * nT, hipMemcpyHostToDevice, s), "copy")) !=
+                IBIP_OK)
+                return rc;
+            hipLaunchKernelGGL(k_mio_count, dim3((unsigned)std::max<int64_t>(std::min<int64_t>(n / 8192, 1024), 1)),
+                               dim3(256), sizeof(uint32_t) * 2 * nT, s, mio_r2, n, dT, nT, counts);
+        }
+    }
+    for (int32_t i = levels ? nT : 0; i < nT; i++) {
         // distance to the kept centres, capped at T; the last pass writes T
         // into mio_r2 where it is still 0 and the distance is below T
         if ((rc = hip_check(ctx, launch_edt(nullptr, kmap, T[i], T[i], d, g16, tmp32, nullptr, &flags[2], s, mio_r2,
@@ -126,12 +196,14 @@ ibip_status run_mio(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlets, 
         ctx->timing.mio_ms += ctx->timer.ms(10, 11);
         ctx->timing.relax_sweeps += iters;
     }
-    if (mio_sat)
+    if (mio_sat) {
+        uint64_t c = 0;
         for (int32_t i = 0; i < nT; i++) {
-            uint64_t c = 0;
+            if (!levels) c = 0;  // (counted per level; else the voxels first reached at each)
             for (int q = 0; q < kCountSlots; q++) c += hc[(size_t)kCountSlots * i + q];
             mio_sat[i] = n_pore ? (double)c / (double)n_pore : 0.0;
         }
+    }
     return IBIP_OK;
 }
 
