@@ -28,8 +28,7 @@ namespace ibip {
 
 namespace {
 
-constexpr uint32_t kTop = 0x80000000u;    // in par: a label (basin), not a voxel
-constexpr uint32_t kNone = 0xffffffffu;   // in par: capacity 0
+constexpr uint32_t kTop = kBasinTop, kNone = kBasinNone;
 
 __device__ inline uint64_t ld64(const uint64_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -138,18 +137,20 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_up(BasinArgs a, Cap cap) {
     for (int j = 0; j < kOwn; j++) {
         const int i = tid + j * kBasinWg, h = T::halo(i);
         // directions 0..26 are in the order of the neighbours' indices; 13 is v itself
-        uint64_t best = (uint64_t)hw[h] << 5 | 13u;
+        const uint32_t me = hw[h];
+        uint64_t best = (uint64_t)Cap::rank(me) << 5 | 13u;
 #pragma unroll
         for (int q = 0; q < 27; q++) {
             const int dx = q / 9 - 1, dy = q / 3 % 3 - 1, dz = q % 3 - 1;
             if (q == 13 || (kFlat && dx) || (!kConn26 && (dx != 0) + (dy != 0) + (dz != 0) > 1)) continue;
-            best = max(best, (uint64_t)hw[h + (dx * T::HY + dy) * T::HZ + dz] << 5 | (uint32_t)q);
+            const uint32_t c = Cap::rank(hw[h + (dx * T::HY + dy) * T::HZ + dz]);
+            best = max(best, (uint64_t)(Cap::open(me, dx) ? c : 0u) << 5 | (uint32_t)q);
         }
         const int q = (int)((uint32_t)best & 31u);
         const int x = T::lx(i) + q / 9 - 1, y = T::ly(i) + q / 3 % 3 - 1, z = T::lz(i) + q % 3 - 1;
         const bool stay = (unsigned)x < (unsigned)T::TX && (unsigned)y < (unsigned)T::TY && (unsigned)z < (unsigned)T::TZ;
         up[i] = (uint16_t)(stay ? (uint32_t)((x * T::TY + y) * T::TZ + z) : kOut | (uint32_t)q);
-        mine += q == 13 && hw[h] != 0;  // (outside the image the capacity is 0)
+        mine += q == 13 && Cap::rank(me) != 0;  // (outside the image the capacity is 0)
     }
     __syncthreads();
     uint32_t end[kOwn];
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_up(BasinArgs a, Cap cap) {
     for (int j = 0; j < kOwn; j++) {
         const int i = tid + j * kBasinWg;
         uint32_t e = (uint32_t)i;
-        if (hw[T::halo(i)])
+        if (Cap::rank(hw[T::halo(i)]))
             for (uint32_t n; (n = up[e]) != e && !(n & kOut);) e = n;
         end[j] = e;
     }
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_up(BasinArgs a, Cap cap) {
     // the tops' labels, in place of their capacities
     uint32_t own[kOwn];
 #pragma unroll
-    for (int j = 0; j < kOwn; j++) own[j] = hw[T::halo(tid + j * kBasinWg)];
+    for (int j = 0; j < kOwn; j++) own[j] = Cap::rank(hw[T::halo(tid + j * kBasinWg)]);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kOwn; j++) {
@@ -178,6 +179,10 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_up(BasinArgs a, Cap cap) {
             a.H[id] = hook(0xffffffffu, id);
             a.best[id] = 0;
             a.best[a.pall + 1 + id] = 0;
+            if (a.mst) {
+                a.mst[id] = 0;
+                a.topv[id] = (uint32_t)t.voxel(a, i);
+            }
             id |= kTop;
         } else {
             a.ctl->abort = 1;
@@ -245,7 +250,7 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_edges(BasinArgs a, Cap cap, 
         const uint32_t la = hl[h];
         take[j] = seed[j] = 0;
         const int64_t v = t.in(a, i) ? t.voxel(a, i) : 0;
-        uint32_t s0 = w0[v];
+        uint32_t s0 = w0 ? w0[v] : 0u;
         if (la == kNone) s0 = 0;
         uint32_t mask = 0;
 #pragma unroll
@@ -255,8 +260,8 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_edges(BasinArgs a, Cap cap, 
             if (kFlat && dx) continue;
             const int off = (dx * T::HY + dy) * T::HZ + dz;
             const uint32_t lb = hl[h + off];
-            if (la != kNone && lb != kNone && lb != la) {
-                const uint32_t w = min(hc[h], hc[h + off]);
+            if (la != kNone && lb != kNone && lb != la && Cap::open(hc[h], dx)) {
+                const uint32_t w = min(Cap::rank(hc[h]), Cap::rank(hc[h + off]));
                 uint32_t better = 0;
 #pragma unroll
                 for (int b = 0; b < 6; b++) {
@@ -267,7 +272,7 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_edges(BasinArgs a, Cap cap, 
                         dy + ey > 1 || dy + ey < -1 || dz + ez > 1 || dz + ez < -1)
                         continue;
                     const int side = h + (ex * T::HY + ey) * T::HZ + ez;
-                    const uint32_t w2 = min(hc[side], hc[side + off]);
+                    const uint32_t w2 = min(Cap::rank(hc[side]), Cap::rank(hc[side + off]));
                     better |= (uint32_t)(hl[side] == la) & (uint32_t)(hl[side + off] == lb) &
                               (uint32_t)(e > 0 ? w2 >= w : w2 > w);
                 }
@@ -310,7 +315,7 @@ __global__ __launch_bounds__(kBasinWg) void k_basin_edges(BasinArgs a, Cap cap, 
             const int q = kConn26 ? d + 14 : d == 0 ? 22 : d == 1 ? 16 : 14;
             const int off = ((q / 9 - 1) * T::HY + (q / 3 % 3 - 1)) * T::HZ + q % 3 - 1;
             a.ends[k] = (uint64_t)(hl[h + off] & ~kTop) << 32 | la;
-            a.wt[k++] = min(hc[h], hc[h + off]);
+            a.wt[k++] = min(Cap::rank(hc[h]), Cap::rank(hc[h + off]));
         }
         if (seed[j]) {
             a.ends[k] = (uint64_t)a.pall << 32 | la;
@@ -382,7 +387,10 @@ __global__ __launch_bounds__(256) void k_basin_hook(BasinArgs a, int round) {
         if (key) {
             const uint64_t e = a.ends[(uint32_t)key];
             const uint32_t o = (uint32_t)e == p ? (uint32_t)(e >> 32) : (uint32_t)e;
-            if (!(o != a.pall && best[o] == key && p < o)) a.H[p] = hook((uint32_t)(key >> 32), o);
+            if (!(o != a.pall && best[o] == key && p < o)) {
+                a.H[p] = hook((uint32_t)(key >> 32), o);
+                if (a.mst) a.mst[p] = hook((uint32_t)(key >> 32), o);
+            }
         }
         next[p] = 0;
     }
@@ -391,25 +399,21 @@ __global__ __launch_bounds__(256) void k_basin_hook(BasinArgs a, int round) {
 // H[p] = (smallest weight on the way to p's root, that root), as far as `hops`
 // hops go. The offers follow what is left of a longer chain.
 __global__ __launch_bounds__(256) void k_basin_flat(BasinArgs a, int hops, int round) {
-    if (a.ctl->abort || a.ctl->abort_edges || !a.ctl->live[round] || (hops > kBasinHops && !a.ctl->deep[round])) return;
+    if (a.ctl->abort || a.ctl->abort_edges || !a.ctl->live[round]) return;
     const uint32_t slot = blockIdx.x % kBasinSlots, part = blockIdx.x / kBasinSlots, parts = gridDim.x / kBasinSlots;
     const uint32_t np = a.ctl->np[slot * kBasinPad];
-    bool left = false;
     for (uint32_t i = part * 256 + threadIdx.x; i < np; i += parts * 256) {
         const uint32_t p = slot * a.pcap + i;
         uint64_t h = ld64(&a.H[p]);
         if (to(h) == p) continue;
         const uint32_t t0 = to(h);
-        int q = 0;
-        for (; q < hops; q++) {
+        for (int q = 0; q < hops; q++) {
             const uint64_t g = ld64(&a.H[to(h)]);
             if (to(g) == to(h)) break;
             h = hook(min((uint32_t)(h >> 32), (uint32_t)(g >> 32)), to(g));
         }
         if (to(h) != t0) __hip_atomic_store(&a.H[p], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        left |= q == hops;
     }
-    raise(&a.ctl->deep[round], left);
 }
 
 // w[v] = min(cap(v), B(label)).
@@ -501,14 +505,18 @@ hipError_t launch_basin_graph(const BasinArgs& a, const int32_t* seq, const uint
     return cap32 ? start(a, CapU32{cap32}, conn26, w, s) : start(a, CapSeq{seq}, conn26, w, s);
 }
 
+hipError_t launch_basin_graph_keys(const BasinArgs& a, const uint32_t* key, hipStream_t s) {
+    const CapKey cap{key};
+    return a.X == 1 ? start<CapKey, false, true>(a, cap, nullptr, s) : start<CapKey, false, false>(a, cap, nullptr, s);
+}
+
 hipError_t launch_basin_rounds(const BasinArgs& a, int from, int to, hipStream_t s) {
     // (workgroups by the image's size: a slot's list is read by 1 to 32 of them)
     const unsigned g = kBasinSlots * (unsigned)std::min<int64_t>(std::max<int64_t>(a.n >> 18, 1), 32);
     for (int r = from; r < to; r++) {
         hipLaunchKernelGGL(k_basin_offer, dim3(g), dim3(256), 0, s, a, r);
         hipLaunchKernelGGL(k_basin_hook, dim3(g), dim3(256), 0, s, a, r);
-        hipLaunchKernelGGL(k_basin_flat, dim3(g), dim3(256), 0, s, a, kBasinHops, r);
-        hipLaunchKernelGGL(k_basin_flat, dim3(g), dim3(256), 0, s, a, 32 * kBasinHops, r);
+        hipLaunchKernelGGL(k_basin_flat, dim3(g), dim3(256), 0, s, a, 8 * kBasinHops, r);
     }
     return hipGetLastError();
 }

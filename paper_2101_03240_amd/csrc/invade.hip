@@ -1866,7 +1866,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         const bool mask = (ctx->readings & IBIP_READ_MASK_INLETS) != 0;
         if ((rc = hip_check(ctx, hipMemcpyAsync(ta.ctl, h_ctl, head_bytes, hipMemcpyHostToDevice, s), "copy")) != IBIP_OK)
             return rc;
-        if ((rc = hip_check(ctx, launch_tree_build(ta, h_off, s), "tree")) != IBIP_OK) return rc;
+        if ((rc = hip_check(ctx, launch_tree_build(ta, s), "tree")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, launch_tree_seed(ta, 0, inlets, d, mask, s), "tree")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, launch_tree_levels(ta, h_off, seq, s), "tree")) != IBIP_OK) return rc;
         tm.mark(4, s);
@@ -2238,7 +2238,7 @@ hipError_t job_tree(const JobBufs& j, const TreeArgs& ta, const TreeCtl* head, c
     if ((e = launch_tree_convert(ta, 0, image, j.key, j.key, j.hist + V, d, (uint32_t)(V - 1), s)) != hipSuccess)
         return e;
     if ((e = launch_tree_sort(ta, j.tail, j.bucket, s)) != hipSuccess) return e;
-    if ((e = launch_tree_build(ta, off_host, s)) != hipSuccess) return e;
+    if ((e = launch_tree_build(ta, s)) != hipSuccess) return e;
     if ((e = launch_tree_seed(ta, 0, inlets, d, false, s)) != hipSuccess) return e;
     return launch_tree_levels(ta, off_host, seq, s);
 }
@@ -2522,7 +2522,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     if ((rc = hip_check(ctx, hipMemcpyAsync(ta.ctl, h_ctl, head_bytes, hipMemcpyHostToDevice, s), "copy")) != IBIP_OK)
         return rc;
     if ((rc = hip_check(ctx, launch_tree_sort(ta, tail, list, s), "sort")) != IBIP_OK) return rc;
-    if ((rc = hip_check(ctx, launch_tree_build(ta, h_off, s), "tree")) != IBIP_OK) return rc;
+    if ((rc = hip_check(ctx, launch_tree_build(ta, s), "tree")) != IBIP_OK) return rc;
     for (int32_t j = 0; j < m; j++) {
         const ibip_job& jb = jobs[g.job[j]];
         if ((rc = hip_check(ctx, launch_tree_seed(ta, vox[j], jb.inlets, jb.dims, false, s), "seed")) != IBIP_OK)

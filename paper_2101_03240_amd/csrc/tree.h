@@ -2,7 +2,7 @@
 // by the single-image path, the batch and the server.
 #pragma once
 
-#include "ibip_internal.h"
+#include "basin.h"
 
 namespace ibip {
 
@@ -75,6 +75,7 @@ struct TreeArgs {
     uint32_t *gm, *gbase, *lastb, *bg, *bbase, *bcnt, *blev, *bprev;
     uint2 *rank0, *rank1;  // 2 ecap each: list ranking of the events' tour (next, steps)
     uint32_t* blkoff;      // R + 2: first block of each level
+    char* basin;           // the basins' scratch (phase 1, over what the others need later)
     // lists of one level: places that a round left (two in turn), places
     // popped, and candidates in components entered (three words each)
     uint32_t *U, *U2, *F, *X;
@@ -95,30 +96,67 @@ constexpr int kLevelWords = 3;  // words per voxel of the largest level: U, U2, 
 constexpr int kPoreWords = 9;   // words per pore voxel: rec 8, dist
 // bytes of the control words and the images' entries, which start the scratch
 inline size_t tree_head_bytes(uint32_t njobs) { return align256(sizeof(TreeCtl) + sizeof(TreeJob) * (size_t)njobs); }
+// The basins of phase 1 (par in a.uf's memory) in the scratch at `mem`, which takes
+// *bytes: the control words, the slices of the tree's edges by level (counts, which
+// start as zero, and offsets), the edges, and the basins' own.
+struct TreeBasins {
+    BasinArgs b;
+    uint32_t *cnt, *at;  // R + 2 each
+    uint2* edge;         // [pall] the tops of the two basins
+};
+inline TreeBasins tree_basins(const TreeArgs& a, char* mem, size_t* bytes) {
+    TreeBasins t{};
+    basin_caps(t.b, ibip_dims{(int32_t)(a.n / (uint32_t)a.sx), a.sx / a.sy, a.sy});
+    char* m = mem;
+    auto take = [&m](size_t k) {
+        char* p = m;
+        m += (k + 7) / 8 * 8;
+        return p;
+    };
+    const size_t P = (size_t)t.b.pall + 1, E = (size_t)t.b.ecap * kBasinSlots;
+    t.b.ctl = (BasinCtl*)take(sizeof(BasinCtl));
+    t.cnt = (uint32_t*)take(4 * ((size_t)a.R + 2));
+    t.at = (uint32_t*)take(4 * ((size_t)a.R + 2));
+    t.edge = (uint2*)take(8 * P);
+    t.b.H = (uint64_t*)take(8 * P);
+    t.b.best = (uint64_t*)take(16 * P);
+    t.b.mst = (uint64_t*)take(8 * P);
+    t.b.topv = (uint32_t*)take(4 * P);
+    t.b.ends = (uint64_t*)take(8 * E);
+    t.b.wt = (uint32_t*)take(4 * E);
+    t.b.par = a.uf;
+    *bytes = (size_t)(m - mem);
+    return t;
+}
 // words of scratch for the caps of `a`
 inline size_t tree_words(const TreeArgs& a) {
-    return tree_head_bytes(a.njobs) / 4 + (size_t)a.pcap * kPeakWords + (size_t)a.ecap * kEventWords + (a.R + 2) +
-           (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3 + (size_t)a.n_pore * kPoreWords + 2;
+    size_t basins;
+    tree_basins(a, nullptr, &basins);
+    const size_t later = (size_t)a.ecap * kEventWords + (a.R + 2) + (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3 +
+                         (size_t)a.n_pore * kPoreWords + 2;
+    return tree_head_bytes(a.njobs) / 4 + (size_t)a.pcap * kPeakWords + 2 + std::max(later, basins / 4 + 4);
 }
-// lays the control words, peaks, events and lists out in w, and sets a.kb
+// lays the control words, peaks, and the rest out in w, and sets a.kb
 inline void tree_carve(TreeArgs& a, uint32_t* w) {
     a.ctl = (TreeCtl*)w;
     a.jobs = (TreeJob*)(a.ctl + 1);
     w += tree_head_bytes(a.njobs) / 4;
-    a.rec = (uint4*)w;
-    w += 8 * (size_t)a.n_pore;
-    a.dist = w;
-    w += (a.n_pore + 1u) / 2 * 2;
     a.cpm = (uint2*)w;
     w += 2 * (size_t)a.pcap;
-    a.rank0 = (uint2*)w;
-    w += 4 * (size_t)a.ecap;
-    a.rank1 = (uint2*)w;
-    w += 4 * (size_t)a.ecap;
     for (uint32_t** p : {&a.plo, &a.mark, &a.grp, &a.er, &a.head, &a.lcnt, &a.E}) {
         *p = w;
         w += a.pcap;
     }
+    w += (4 - (w - (uint32_t*)a.ctl) % 4) % 4;  // (the records are read by 16 bytes)
+    a.basin = (char*)w;
+    a.rec = (uint4*)w;
+    w += 8 * (size_t)a.n_pore;
+    a.dist = w;
+    w += (a.n_pore + 1u) / 2 * 2;
+    a.rank0 = (uint2*)w;
+    w += 4 * (size_t)a.ecap;
+    a.rank1 = (uint2*)w;
+    w += 4 * (size_t)a.ecap;
     for (uint32_t** p : {&a.gm, &a.gbase, &a.lastb, &a.bg, &a.bbase, &a.bcnt, &a.blev, &a.bprev}) {
         *p = w;
         w += a.ecap;
@@ -136,8 +174,7 @@ inline void tree_carve(TreeArgs& a, uint32_t* w) {
 }
 // Calls stopped after fewer steps run the step loop.
 constexpr int64_t kTreeMinSteps = 1024;
-// Levels of at most this many voxels run in one workgroup (joins, searches).
-constexpr uint32_t kTreeSmallJoin = 256;
+// Levels of at most this many voxels are searched in one workgroup.
 constexpr uint32_t kTreeSmall = 2048;
 
 // The scratch's caps for n_pore pore voxels in njobs images, the largest level
@@ -160,8 +197,7 @@ hipError_t launch_tree_convert(const TreeArgs& a, uint32_t vox, const uint8_t* i
 // the pore voxels sorted by rank into a.list (cursors: the slice offsets), a.idx the inverse
 hipError_t launch_tree_sort(const TreeArgs& a, uint32_t* cursor, uint32_t* list, hipStream_t s);
 // The component tree and what the levels need of it.
-// off_host: the slice offsets (R + 2 entries).
-hipError_t launch_tree_build(const TreeArgs& a, const uint32_t* off_host, hipStream_t s);
+hipError_t launch_tree_build(const TreeArgs& a, hipStream_t s);
 // the seeds of the image of dims d at voxel `vox`
 hipError_t launch_tree_seed(const TreeArgs& a, uint32_t vox, const uint8_t* inlets, ibip_dims d, bool mask,
                             hipStream_t s);

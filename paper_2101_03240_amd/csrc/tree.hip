@@ -29,9 +29,10 @@
 // the children by descending level and, in a level, by round.
 //
 // Phases:
-//  1. The component tree: levels from the highest rank down; a union-find over
-//     voxels joins the voxels of a level to their neighbours of the same or a
-//     higher rank. The root of a component is its highest voxel (rank, then
+//  1. The component tree: the voxels climb to their basins' tops, and Boruvka
+//     rounds on the basins leave the edges that hold their graph together (basin.hip);
+//     level by level from the highest rank down, a union-find joins the basins of
+//     the level's edges. The root of a component is its highest top (rank, then
 //     lowest index), its peak; a peak whose component joins a higher one at
 //     level t keeps (t, the other peak), so the label of a voxel's component
 //     at any level is found by walking from the voxel's peak.
@@ -136,7 +137,6 @@ __global__ __launch_bounds__(256) void k_tree_convert(TreeArgs a, uint32_t vox, 
     if (c >= n) return;
     const uint32_t q = fdiv(c, divCZ), x = fdiv(q, divCY), y = q - x * divCY.d, z = c - q * divCZ.d;
     const uint32_t g = vox + c;
-    a.uf[g] = g;
     a.top[g] = kNone;
     uint32_t k = 0;
     if (y < (uint32_t)Y && z < (uint32_t)Z) {
@@ -187,10 +187,10 @@ __global__ __launch_bounds__(256) void k_tree_sort(const uint32_t* __restrict__ 
 // ---------------------------------------------------------------------------
 // Phase 1: the component tree
 // ---------------------------------------------------------------------------
-// Root of x. A link without kUfPeak leads from a voxel to a root or to a voxel
-// of the same level and is never changed; the links of merged peaks are
-// shortened on the way. Links always lead to a higher voxel (rank, then lowest
-// index), so the walk ends.
+// Root of x. A link without kUfPeak leads from a voxel to its basin's top, or
+// from a top to one of the same level, and is never changed; the links of merged
+// peaks are shortened on the way. Links always lead to a higher voxel (rank, then
+// lowest index, or from its basin to the top), so the walk ends.
 __device__ inline uint32_t uf_find(uint32_t* uf, uint32_t x) {
     for (;;) {
         const uint32_t v = ld(&uf[x]), y = v & ~kUfPeak;
@@ -230,94 +230,90 @@ __device__ inline uint32_t uf_union(const TreeArgs& a, uint32_t p, uint32_t q, u
     }
 }
 
-// Joins voxel u of level t to its neighbours of the same or a higher rank. The
-// walks from all neighbours to their roots go side by side, their loads in
-// flight together (one walk after another costs a memory round trip per link).
-__device__ inline void tree_join(const TreeArgs& a, uint32_t u, uint32_t t) {
-    const uint32_t ku = a.key[u];
-    uint32_t w[6], kw[6], x[6], first[6], to[6];
-    uint32_t hi = 0, open = 0;
-#pragma unroll
-    for (int d = 0; d < 6; d++) {
-        const bool in = (ku >> (kNbShift + d)) & 1u;
-        w[d] = in ? u + (uint32_t)nb_off(a, d) : u;
-        kw[d] = a.key[w[d]] & kRankMask;
-        x[d] = ld(&a.uf[w[d]]) & ~kUfPeak;
-        kw[d] = in ? kw[d] : 0u;
-        first[d] = to[d] = kNone;
-        hi |= (kw[d] > t ? 1u : 0u) << d;
+// The links from the voxels to their basins' tops (a.uf held the labels), and
+// whether the basins came out.
+__global__ __launch_bounds__(256) void k_tree_links(TreeArgs a, TreeBasins t, int rounds) {
+    if (t.b.ctl->abort || t.b.ctl->abort_edges || t.b.ctl->live[rounds - 1]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->abort = 1;
+        return;
     }
-    // one walk per distinct first link
-#pragma unroll
-    for (int d = 1; d < 6; d++)
-#pragma unroll
-        for (int e = 0; e < d; e++)
-            if (((hi >> d) & 1u) && ((hi >> e) & 1u) && x[e] == x[d]) hi &= ~(1u << d);
-    open = hi;
-    while (open) {
-        uint32_t v[6];
-#pragma unroll
-        for (int d = 0; d < 6; d++) v[d] = (open >> d) & 1u ? ld(&a.uf[x[d]]) : 0u;
-#pragma unroll
-        for (int d = 0; d < 6; d++) {
-            if (!((open >> d) & 1u)) continue;
-            const uint32_t y = v[d] & ~kUfPeak;
-            if (y == x[d]) {
-                open &= ~(1u << d);
-            } else {
-                if (first[d] == kNone && (v[d] & kUfPeak)) {
-                    first[d] = x[d];
-                    to[d] = y;
-                }
-                x[d] = y;
-            }
-        }
-    }
-    // shorten the first merged peak's link on each walk (not where it leads to
-    // the root already: the link of a large component's peak is hot)
-#pragma unroll
-    for (int d = 0; d < 6; d++)
-        if (first[d] != kNone && to[d] != x[d]) st(&a.uf[first[d]], x[d] | kUfPeak);
-    uint32_t cur = kNone;  // root of u's component once known
-#pragma unroll
-    for (int d = 0; d < 6; d++) {
-        if (!((hi >> d) & 1u) || x[d] == cur) continue;
-        if (cur == kNone) {
-            // (the root lies above level t, so above u)
-            const uint32_t old = atomicCAS(&a.uf[u], u, x[d]);
-            cur = old == u ? x[d] : uf_union(a, uf_find(a.uf, old & ~kUfPeak), x[d], t);
-        } else {
-            cur = uf_union(a, cur, x[d], t);
-        }
-    }
-    // neighbours of the same rank, each pair once
-    uint32_t q[3];
-#pragma unroll
-    for (int j = 0; j < 3; j++) q[j] = kw[2 * j + 1] == t ? ld(&a.uf[w[2 * j + 1]]) & ~kUfPeak : kNone;
-#pragma unroll
-    for (int j = 0; j < 3; j++) {
-        if (q[j] == kNone || q[j] == cur) continue;
-        const uint32_t p = uf_find(a.uf, cur == kNone ? u : cur);
-        cur = uf_union(a, p, uf_find(a.uf, q[j]), t);
-    }
+    const uint32_t v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= a.n) return;
+    const uint32_t l = a.uf[v];
+    a.uf[v] = l == kBasinNone ? v : t.b.topv[l & ~kBasinTop];
 }
 
-__global__ __launch_bounds__(256) void k_tree_join(TreeArgs a, uint32_t t, uint32_t lo, uint32_t hi) {
-    const uint32_t i = lo + blockIdx.x * 256 + threadIdx.x;
-    if (i < hi) tree_join(a, a.list[i], t);
+// The edges between the basins that hold their graph together (a maximum spanning
+// forest) into their levels' slices; a workgroup takes a slot's, counts them
+// by level in LDS, and then reserves its part of each slice and places them.
+template <bool kPlace>
+__global__ __launch_bounds__(kWg) void k_tree_edges(TreeArgs a, TreeBasins t) {
+    if (a.ctl->abort) return;
+    extern __shared__ uint32_t cnt[];  // R + 1
+    for (uint32_t q = threadIdx.x; q <= a.R; q += kWg) cnt[q] = 0;
+    __syncthreads();
+    const uint32_t np = t.b.ctl->np[blockIdx.x * kBasinPad], p0 = blockIdx.x * t.b.pcap;
+    for (uint32_t i = threadIdx.x; i < np; i += kWg) {
+        const uint64_t e = t.b.mst[p0 + i];
+        if (e) atomicAdd(&cnt[e >> 32], 1u);
+    }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q <= a.R; q += kWg) {
+        const uint32_t c = cnt[q];
+        if (c) cnt[q] = atomicAdd(kPlace ? &t.at[q] : &t.cnt[q], c);
+    }
+    if (!kPlace) return;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < np; i += kWg) {
+        const uint64_t e = t.b.mst[p0 + i];
+        if (e) t.edge[atomicAdd(&cnt[e >> 32], 1u)] = make_uint2(t.b.topv[p0 + i], t.b.topv[(uint32_t)e]);
+    }
 }
-
-// levels t_hi down to t_lo in one workgroup
-__device__ inline void tree_join_levels(const TreeArgs& a, uint32_t t_hi, uint32_t t_lo) {
-    for (uint32_t t = t_hi; t >= t_lo; t--) {
-        const uint32_t i0 = a.off[t], i1 = a.off[t + 1];
-        for (uint32_t i = i0 + threadIdx.x; i < i1; i += kWg) tree_join(a, a.list[i], t);
+// at[r] = the first edge of level r, the levels descending; one workgroup.
+__global__ __launch_bounds__(kWg) void k_tree_slices(TreeArgs a, TreeBasins t) {
+    __shared__ uint32_t part[kWg];
+    if (a.ctl->abort) return;
+    const uint32_t per = a.R / kWg + 1, b0 = threadIdx.x * per;
+    uint32_t sum = 0;
+    for (uint32_t q = b0; q < b0 + per && q < a.R; q++) sum += t.cnt[a.R - q];
+    part[threadIdx.x] = sum;
+    __syncthreads();
+    for (uint32_t o = 1; o < (uint32_t)kWg; o <<= 1) {
+        const uint32_t before = threadIdx.x >= o ? part[threadIdx.x - o] : 0u;
+        __syncthreads();
+        part[threadIdx.x] += before;
         __syncthreads();
     }
+    uint32_t at = part[threadIdx.x] - sum;
+    for (uint32_t q = b0; q < b0 + per && q < a.R; q++) {
+        t.at[a.R - q] = at;
+        at += t.cnt[a.R - q];
+    }
 }
 
-__global__ __launch_bounds__(kWg) void k_tree_join_wg(TreeArgs a, uint32_t t_hi, uint32_t t_lo) {
-    tree_join_levels(a, t_hi, t_lo);
+// Phase 1's merges: level by level down, each level's edges join their basins'
+// components; one workgroup, since a level has few (512^3 blurred noise: 0.4 M in
+// 304 levels). (at[r] is the end of level r's slice now, cnt[r] its length.)
+__global__ __launch_bounds__(kWg) void k_tree_merge(TreeArgs a, TreeBasins t) {
+    if (a.ctl->abort) return;
+    __shared__ uint32_t cnt[kWg], end[kWg];  // the slices of the next levels
+    for (uint32_t r0 = a.R; r0 >= 1; r0 -= min(r0, (uint32_t)kWg)) {
+        if (threadIdx.x < r0) {
+            cnt[threadIdx.x] = t.cnt[r0 - threadIdx.x];
+            end[threadIdx.x] = t.at[r0 - threadIdx.x];
+        }
+        __syncthreads();
+        for (uint32_t q = 0; q < (uint32_t)kWg && q < r0; q++) {
+            const uint32_t c = cnt[q], e1 = end[q];
+            if (c == 0) continue;  // (the same in every thread)
+            for (uint32_t i = e1 - c + threadIdx.x; i < e1; i += kWg) {
+                const uint2 e = t.edge[i];
+                uf_union(a, uf_find(a.uf, e.x), uf_find(a.uf, e.y), r0 - q);
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+    }
 }
 
 // ids of the peaks: the merged ones in the order of their log, then the others
@@ -331,6 +327,7 @@ __device__ inline void peak_init(const TreeArgs& a, uint32_t i) {
 __global__ __launch_bounds__(256) void k_tree_peaks(TreeArgs a) {
     const uint32_t tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
     const uint32_t nm = a.ctl->nmerge;
+    if (a.ctl->abort) return;
     if (nm > a.pcap) {
         if (tid == 0) a.ctl->abort = 1;
         return;
@@ -370,9 +367,9 @@ __device__ inline uint32_t label_at(const TreeArgs& a, uint32_t pid, uint32_t lv
     }
 }
 
-// top of every voxel that is no peak: its links lead to a peak (through voxels
-// of its own level, whose tops are the same), then to the peak that labels
-// that component at the voxel's level
+// top of every voxel that is no peak: its links lead to a peak (through tops that
+// are no peaks, whose own tops label the component at their level), then to the
+// peak that labels that component at the voxel's level
 __global__ __launch_bounds__(256) void k_tree_tops(TreeArgs a) {
     if (a.ctl->abort) return;
     const uint32_t v = blockIdx.x * 256 + threadIdx.x;
@@ -1153,20 +1150,24 @@ hipError_t launch_tree_sort(const TreeArgs& a, uint32_t* cursor, uint32_t* list,
     return hipGetLastError();
 }
 
-hipError_t launch_tree_build(const TreeArgs& a, const uint32_t* off, hipStream_t s) {
-    auto size = [&](uint32_t t) { return off[t + 1] - off[t]; };
-    // phase 1
-    for (uint32_t t = a.R; t >= 1;) {
-        if (size(t) > kTreeSmallJoin) {
-            hipLaunchKernelGGL(k_tree_join, dim3(blocks(size(t))), dim3(256), 0, s, a, t, off[t], off[t + 1]);
-            t--;
-        } else {
-            uint32_t q = t;
-            while (q > 1 && size(q - 1) <= kTreeSmallJoin) q--;
-            hipLaunchKernelGGL(k_tree_join_wg, dim3(1), dim3(kWg), 0, s, a, t, q);
-            t = q - 1;
-        }
-    }
+hipError_t launch_tree_build(const TreeArgs& a, hipStream_t s) {
+    size_t bytes;
+    const TreeBasins t = tree_basins(a, a.basin, &bytes);
+    // a round at least halves the components with edges, and mostly leaves a
+    // tenth; an image of more than 2^16 basins that takes more rounds than this
+    // runs the step loop
+    int rounds = 1;
+    while (rounds < 16 && (a.n_pore >> rounds) != 0) rounds++;
+    hipError_t e;
+    if ((e = hipMemsetAsync(t.b.ctl, 0, (size_t)((char*)t.at - (char*)t.b.ctl), s)) != hipSuccess) return e;
+    if ((e = launch_basin_graph_keys(t.b, a.key, s)) != hipSuccess) return e;
+    if ((e = launch_basin_rounds(t.b, 0, rounds, s)) != hipSuccess) return e;
+    const size_t lds = sizeof(uint32_t) * ((size_t)a.R + 1);
+    hipLaunchKernelGGL(k_tree_links, dim3(blocks(a.n)), dim3(256), 0, s, a, t, rounds);
+    hipLaunchKernelGGL(k_tree_edges<false>, dim3(kBasinSlots), dim3(kWg), lds, s, a, t);
+    hipLaunchKernelGGL(k_tree_slices, dim3(1), dim3(kWg), 0, s, a, t);
+    hipLaunchKernelGGL(k_tree_edges<true>, dim3(kBasinSlots), dim3(kWg), lds, s, a, t);
+    hipLaunchKernelGGL(k_tree_merge, dim3(1), dim3(kWg), 0, s, a, t);
     hipLaunchKernelGGL(k_tree_peaks, dim3(std::min(blocks(a.n), 4096u)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_tree_parents, dim3(std::min(blocks(a.pcap), 1024u)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_tree_tops, dim3(blocks(a.n)), dim3(256), 0, s, a);
