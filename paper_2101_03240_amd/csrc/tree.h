@@ -58,7 +58,7 @@ struct TreeArgs {
     const uint32_t* key;
     const uint32_t* list;  // pore voxels by rank: rank r at off[r] .. off[r + 1]
     const uint32_t* off;
-    uint32_t* uf;          // N: union-find over voxels
+    uint32_t* uf;          // N: the voxels' basins
     uint32_t* top;         // N: the peak that labels a voxel's component at its own level
     uint32_t* idx;         // N: a voxel's place in the list (kTreeNone on solid), the step in the end
     // per place of the list
@@ -102,7 +102,8 @@ inline size_t tree_head_bytes(uint32_t njobs) { return align256(sizeof(TreeCtl) 
 struct TreeBasins {
     BasinArgs b;
     uint32_t *cnt, *at;  // R + 2 each
-    uint2* edge;         // [pall] the tops of the two basins
+    uint2* edge;         // [pall] the two basins
+    uint32_t* pk;        // [pall] a basin's peak (in the memory of b.best)
 };
 inline TreeBasins tree_basins(const TreeArgs& a, char* mem, size_t* bytes) {
     TreeBasins t{};
@@ -120,6 +121,7 @@ inline TreeBasins tree_basins(const TreeArgs& a, char* mem, size_t* bytes) {
     t.edge = (uint2*)take(8 * P);
     t.b.H = (uint64_t*)take(8 * P);
     t.b.best = (uint64_t*)take(16 * P);
+    t.pk = (uint32_t*)t.b.best;
     t.b.mst = (uint64_t*)take(8 * P);
     t.b.topv = (uint32_t*)take(4 * P);
     t.b.ends = (uint64_t*)take(8 * E);
