@@ -8,8 +8,8 @@ is the 512^3 blurred-noise image (invasion + trapping). On the 200^3 packing
 (and the 64^3 spheres) a step also runs the pressure-based morphological-
 opening drainage at 25 radii used for the equal-saturation comparison; the
 opening needs only the image and the inlets, so it runs from a second host
-thread on a second stream while the invasion (whose step loop occupies one
-compute unit) and the trapping run. The reported value is invaded voxels per
+thread on a second stream while the invasion (whose levels of few voxels occupy
+one compute unit) and the trapping run. The reported value is invaded voxels per
 second of wall time over the timed steps.
 
 Outside the timed region the default run also reports the equal-saturation
@@ -627,9 +627,9 @@ def main() -> int:
     # per-phase kernels and their algorithmic traffic per launch
     phases = {
         "edt (3 passes, inside invade)": (tm["edt_ms"] / S, EDT_BYTES_PER_VOXEL * n_vox, S),
-        "step loop (single-workgroup kernel)": (
+        "invasion by levels of the component tree": (
             tm["loop_kernel_ms"] / max(tm["loop_launches"], 1),
-            # centres of the steps this kernel ran (the wide steps' centres go to k_wide)
+            # (a step loop's wide steps are timed apart)
             LOOP_BYTES_PER_CENTRE * (tm["popped"] - tm["wide_centres"]) / max(tm["loop_launches"], 1),
             tm["loop_launches"]),
         "sphere insertion": (tm["paint_ms"] / S, PAINT_BYTES_PER_PORE * n_pore, S),
@@ -688,7 +688,7 @@ def main() -> int:
                  "ns_per_wide_centre": 1e6 * tm["wide_kernel_ms"] / max(tm["wide_centres"], 1),
                  "relax_sweeps_per_step": tm["relax_sweeps"] / S},
     }
-    # the latency the loop's steps are bound by: one claim (a returning
+    # the latency that a step loop's steps are bound by: one claim (a returning
     # atomic) per step at least, from L2 (a 256 KiB chain), from the
     # memory-side cache (64 MiB) or from HBM (1 GiB)
     lat = {f"{name}_ns": ibip.probe_claim_latency(span, 20000)
