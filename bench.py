@@ -63,7 +63,7 @@ OPENING_BYTES_PER_VOXEL = 25  # the ball dilation: 17 B (three EDT passes) + 8 B
 # Algorithmic bytes per unit of work for each phase.
 EDT_BYTES_PER_VOXEL = 5          # read 1 B image, write 4 B dt2 (the floor)
 EDT_BUDGET_BYTES_PER_VOXEL = 17  # three passes: 1+2, 2+4, 4+4
-LOOP_BYTES_PER_CENTRE = 20       # push 4 + pop 4 + state write 4 + claim 4 + key read 4
+TREE_BYTES_PER_PORE = 8          # read the rank 4, write the step 4
 PAINT_BYTES_PER_PORE = 12        # read state 4 + key 4, write seq 4
 TRAP_BYTES_PER_VOXEL = 14        # read seq 4 + outlets 1, W 4 + write W 4, trapped 1
 MIO_BYTES_PER_VOXEL_RADIUS = 13  # EDT of the kept set 5 + read K map 4 + update 4
@@ -628,10 +628,7 @@ def main() -> int:
     phases = {
         "edt (3 passes, inside invade)": (tm["edt_ms"] / S, EDT_BYTES_PER_VOXEL * n_vox, S),
         "invasion by levels of the component tree": (
-            tm["loop_kernel_ms"] / max(tm["loop_launches"], 1),
-            # (a step loop's wide steps are timed apart)
-            LOOP_BYTES_PER_CENTRE * (tm["popped"] - tm["wide_centres"]) / max(tm["loop_launches"], 1),
-            tm["loop_launches"]),
+            tm["loop_kernel_ms"] / S, TREE_BYTES_PER_PORE * n_pore, S),
         "sphere insertion": (tm["paint_ms"] / S, PAINT_BYTES_PER_PORE * n_pore, S),
         "trapping": (tm["trap_ms"] / S, TRAP_BYTES_PER_VOXEL * n_vox, S),
     }
@@ -677,26 +674,20 @@ def main() -> int:
             "paint": tm["paint_ms"] / S, "steps": tm["steps_ms"] / S, "trap": tm["trap_ms"] / S,
             "mio": tm["mio_ms"] / S},
         "loop": {"us_per_invasion_step": 1e3 * tm["loop_ms"] / max(tm["steps"], 1),
-                 # the loop's time outside its kernels: host synchronisation, state copies and
-                 # relaunches around the wide steps
+                 # the invasion's time outside its kernels
                  "host_overhead_ms_per_call": (tm["loop_ms"] - tm["loop_kernel_ms"] - tm["wide_kernel_ms"]) / S,
-                 "host_overhead_us_per_launch": 1e3 * (tm["loop_ms"] - tm["loop_kernel_ms"] - tm["wide_kernel_ms"])
-                 / max(tm["loop_launches"], 1),
                  "invasion_steps_per_s": tm["steps"] / (tm["loop_ms"] * 1e-3) if tm["loop_ms"] > 0 else 0.0,
                  "loop_launches_per_call": tm["loop_launches"] / S, "wide_launches_per_call": tm["wide_launches"] / S,
                  "wide_centres_per_call": tm["wide_centres"] / S,
                  "ns_per_wide_centre": 1e6 * tm["wide_kernel_ms"] / max(tm["wide_centres"], 1),
-                 "relax_sweeps_per_step": tm["relax_sweeps"] / S},
+                 "reconstruction_rounds_per_step": tm["relax_sweeps"] / S},
     }
-    # the latency that a step loop's steps are bound by: one claim (a returning
-    # atomic) per step at least, from L2 (a 256 KiB chain), from the
-    # memory-side cache (64 MiB) or from HBM (1 GiB)
+    # the latency of a dependent access (a returning atomic), which the search of
+    # a level's rounds is bound by: from L2 (a 256 KiB chain), from the memory-side
+    # cache (64 MiB) or from HBM (1 GiB)
     lat = {f"{name}_ns": ibip.probe_claim_latency(span, 20000)
            for name, span in (("l2", 256 << 10), ("mall", 64 << 20), ("hbm", 1 << 30))}
-    us_step = res["loop"]["us_per_invasion_step"]
     res["loop"]["claim_round_trip"] = lat
-    # how many L2 claim round trips one step takes
-    res["loop"]["step_in_l2_claim_round_trips"] = 1e3 * us_step / lat["l2_ns"]
     # the EDT alone at the 512^3 size, where it is not dominated by launches
     if with_mio:
         res["config"]["mio_radii"] = len(T)

@@ -68,23 +68,24 @@ const char* ibip_last_error(const ibip_ctx* ctx);
 int64_t ibip_ctx_scratch_bytes(const ibip_ctx* ctx);
 
 /* Phase timing, for measurement. When enabled, the calls record HIP events
-   on the context's stream around each phase and each launch of the step
-   loop, and add the elapsed times (milliseconds) to the counters below. */
+   on the context's stream around each phase, the component tree and each launch
+   of the step loop, and add the elapsed times (milliseconds) to the counters
+   below. A call whose steps the component tree gave launches no step loop. */
 typedef struct {
     double edt_ms;          /* distance transform kernels (ibip_edt, and inside ibip_invade) */
     double setup_ms;        /* histogram, ranks, buckets, seeding */
-    double loop_ms;         /* the whole step loop, host round trips included */
-    double loop_kernel_ms;  /* sum of the single-workgroup loop kernel durations */
+    double loop_ms;         /* the whole invasion by steps or levels, host round trips included */
+    double loop_kernel_ms;  /* component tree, and single-workgroup loop kernels */
     double wide_kernel_ms;  /* sum of the whole-GPU step kernel durations */
     double paint_ms;        /* sphere insertion */
     double steps_ms;        /* finalisation and per-step arrays */
     double trap_ms;         /* ibip_trap */
     double mio_ms;          /* ibip_opening_drainage */
-    int64_t loop_launches;  /* launches of the loop kernel */
+    int64_t loop_launches;  /* launches of the step loop's kernel */
     int64_t wide_launches;  /* launches of the whole-GPU step kernel */
     int64_t steps;          /* steps K summed over ibip_invade calls */
     int64_t popped;         /* centres summed over ibip_invade calls */
-    int64_t relax_sweeps;   /* reconstruction sweeps (trapping and MIO) */
+    int64_t relax_sweeps;   /* rounds of the reconstruction on the basins, or sweeps of its tiles (trapping and MIO) */
     int64_t wide_centres;   /* centres of the steps run by the whole-GPU kernel */
 } ibip_timing;
 

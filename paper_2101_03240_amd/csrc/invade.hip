@@ -1878,10 +1878,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
             h_st->k = h_job->K + 1;
             h_st->popped = 0;
             for (uint32_t c : h_ctl->popped) h_st->popped += c;
-            if (tm.on) {
-                ctx->timing.loop_kernel_ms += tm.ms(3, 4);
-                ctx->timing.loop_launches++;
-            }
+            if (tm.on) ctx->timing.loop_kernel_ms += tm.ms(3, 4);
         } else {
             // more peaks, events or rounds than there is room for: the step loop
             if ((rc = hip_check(ctx, launch_tree_undo(ta, seq, head, tail, s), "undo")) != IBIP_OK) return rc;
@@ -2534,10 +2531,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
         return rc;
     if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
-    if (tm.on) {
-        ctx->timing.loop_kernel_ms += tm.ms(3, 4);
-        ctx->timing.loop_launches++;
-    }
+    if (tm.on) ctx->timing.loop_kernel_ms += tm.ms(3, 4);
     if (h_ctl->abort) {
         alone.insert(alone.end(), g.job.begin(), g.job.end());
         return IBIP_OK;

@@ -1,0 +1,56 @@
+"""Which path an invasion takes, told by the timing counters (the component
+tree launches no step loop), and the same results on each, against the oracle.
+Everything is an integer: equality."""
+import numpy as np
+import pytest
+
+from paper_2101_03240_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch.device("cuda:0")
+
+
+def _loops(fn):
+    """fn's result and the step loops that it launched on this thread's context."""
+    import paper_2101_03240_amd as ibip
+
+    ibip.reset_timing()
+    ibip.enable_timing(True)
+    try:
+        r = fn()
+        return r, ibip.get_timing()["loop_launches"]
+    finally:
+        ibip.enable_timing(False)
+
+
+def _put(dev, a):
+    import torch
+    return torch.from_numpy(a).to(dev)
+
+
+def _same(r, ref):
+    assert r["K"] == ref["K"]
+    for k in ("centre_step", "seq", "rad2", "M"):
+        assert np.array_equal(r[k].cpu().numpy().view(np.uint32), np.asarray(ref[k]).astype(np.uint32)), k
+
+
+def test_the_tree_launches_no_step_loop(dev):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = synth.blurred_noise((90, 80, 100), 3.0, 0.6, 4)
+    inl = synth.face_mask(img.shape, 0, 0)
+    ref = oracle.invade(img, inl)
+    r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl)))
+    assert loops == 0
+    _same(r, ref)
+    r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl), max_steps=100))
+    assert loops > 0
+    _same(r, oracle.invade(img, inl, max_steps=100))
