@@ -73,7 +73,8 @@ struct TreeArgs {
     // block; per block of events: thread, first event, events, level, the
     // thread's block before it
     uint32_t *gm, *gbase, *lastb, *bg, *bbase, *bcnt, *blev, *bprev;
-    uint2 *rank0, *rank1;  // 2 ecap each: list ranking of the events' tour (next, steps)
+    uint2 *rank0, *rank1;  // 2 ecap each: list ranking of the events' tour (next, steps); over rec, which
+                           // phase 3 does not read
     uint32_t* blkoff;      // R + 2: first block of each level
     char* basin;           // the basins' scratch (phase 1, over what the others need later)
     // lists of one level: places that a round left (two in turn), places
@@ -91,9 +92,9 @@ constexpr uint32_t kTreeNone = 0xFFFFFFFFu;
 constexpr uint32_t kTreeClaimed = 0x80000000u;
 
 constexpr int kPeakWords = 9;   // words per peak: cpm 2, plo, mark, grp, er, head, lcnt, E
-constexpr int kEventWords = 16;  // words per event: gm .. bprev, and the two rank arrays
+constexpr int kEventWords = 8;  // words per event: gm .. bprev
+constexpr int kRankWords = 8;   // words per event in the list ranking, over the records (8 a pore voxel)
 constexpr int kLevelWords = 3;  // words per voxel of the largest level: U, U2, F
-constexpr int kPoreWords = 9;   // words per pore voxel: rec 8, dist
 // bytes of the control words and the images' entries, which start the scratch
 inline size_t tree_head_bytes(uint32_t njobs) { return align256(sizeof(TreeCtl) + sizeof(TreeJob) * (size_t)njobs); }
 // The basins of phase 1 (par in a.uf's memory) in the scratch at `mem`, which takes
@@ -130,13 +131,17 @@ inline TreeBasins tree_basins(const TreeArgs& a, char* mem, size_t* bytes) {
     *bytes = (size_t)(m - mem);
     return t;
 }
+// words of the records, which the two rank arrays share
+inline size_t tree_rec_words(const TreeArgs& a) {
+    return std::max(8 * (size_t)a.n_pore, (size_t)kRankWords * a.ecap);
+}
 // words of scratch for the caps of `a`
 inline size_t tree_words(const TreeArgs& a) {
     size_t basins;
     tree_basins(a, nullptr, &basins);
-    const size_t later = (size_t)a.ecap * kEventWords + (a.R + 2) + (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3 +
-                         (size_t)a.n_pore * kPoreWords + 2;
-    return tree_head_bytes(a.njobs) / 4 + (size_t)a.pcap * kPeakWords + 2 + std::max(later, basins / 4 + 4);
+    const size_t later = tree_rec_words(a) + (a.n_pore + 1u) / 2 * 2 + (size_t)a.ecap * kEventWords + (a.R + 2) +
+                         (size_t)a.lcap * kLevelWords + (size_t)a.xcap * 3;
+    return tree_head_bytes(a.njobs) / 4 + (size_t)a.pcap * kPeakWords + 3 + std::max(later, basins / 4);
 }
 // lays the control words, peaks, and the rest out in w, and sets a.kb
 inline void tree_carve(TreeArgs& a, uint32_t* w) {
@@ -152,13 +157,11 @@ inline void tree_carve(TreeArgs& a, uint32_t* w) {
     w += (4 - (w - (uint32_t*)a.ctl) % 4) % 4;  // (the records are read by 16 bytes)
     a.basin = (char*)w;
     a.rec = (uint4*)w;
-    w += 8 * (size_t)a.n_pore;
+    a.rank0 = (uint2*)w;
+    a.rank1 = a.rank0 + 2 * (size_t)a.ecap;
+    w += tree_rec_words(a);
     a.dist = w;
     w += (a.n_pore + 1u) / 2 * 2;
-    a.rank0 = (uint2*)w;
-    w += 4 * (size_t)a.ecap;
-    a.rank1 = (uint2*)w;
-    w += 4 * (size_t)a.ecap;
     for (uint32_t** p : {&a.gm, &a.gbase, &a.lastb, &a.bg, &a.bbase, &a.bcnt, &a.blev, &a.bprev}) {
         *p = w;
         w += a.ecap;
@@ -181,12 +184,16 @@ constexpr uint32_t kTreeSmall = 2048;
 
 // The scratch's caps for n_pore pore voxels in njobs images, the largest level
 // of lcap voxels. More peaks, events or candidates than that and the tree gives
-// up (a blurred-noise or grain image has 60 to 300 pore voxels per peak).
+// up. Pore voxels per peak: 130 to 260 in volumes of blurred noise or grains, 50
+// to 100 in such planes, 9 to 25 in noise of single voxels. Pore voxels per event
+// (step): 50 to 200 in volumes, but 9 to 16 in planes, 27 in plane noise of single
+// voxels. An image has no more of either than pore voxels; the 4,096 are its own.
 inline void tree_caps(TreeArgs& a, uint32_t n_pore, uint32_t njobs, uint32_t lcap) {
     a.n_pore = n_pore;
     a.njobs = njobs;
-    a.pcap = n_pore / 8 + 4096;
-    a.ecap = n_pore / 16 + 4096 + njobs;
+    const uint64_t own = 4096 * (uint64_t)njobs;
+    a.pcap = (uint32_t)std::min<uint64_t>(n_pore, n_pore / 8 + own);
+    a.ecap = (uint32_t)std::min<uint64_t>(n_pore, n_pore / 4 + own) + njobs;
     a.lcap = lcap;
     a.xcap = lcap + 4096;
     a.ncap = n_pore / 6;

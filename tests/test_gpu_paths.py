@@ -54,3 +54,18 @@ def test_the_tree_launches_no_step_loop(dev):
     r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl), max_steps=100))
     assert loops > 0
     _same(r, oracle.invade(img, inl, max_steps=100))
+
+
+# (numbers of steps above a sixteenth of the pore voxels + 4,096)
+@pytest.mark.parametrize("side, sigma", [(500, 3.0), (620, 2.0), (1000, 6.0)])
+def test_planes_of_many_steps_take_the_tree(dev, side, sigma):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = synth.blurred_noise((1, side, side), sigma, 0.6, 1)
+    inl = synth.face_mask(img.shape, 1, 0)
+    ref = oracle.invade(img, inl)
+    assert ref["K"] > int(img.sum()) // 16 + 4096
+    r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl)))
+    assert loops == 0
+    _same(r, ref)
