@@ -1869,10 +1869,15 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         if ((rc = hip_check(ctx, launch_tree_build(ta, s), "tree")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, launch_tree_seed(ta, 0, inlets, d, mask, s), "tree")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, launch_tree_levels(ta, h_off, seq, s), "tree")) != IBIP_OK) return rc;
-        tm.mark(4, s);
-        if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
-            return rc;
-        if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+        for (;;) {
+            tm.mark(4, s);
+            if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) !=
+                IBIP_OK)
+                return rc;
+            if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+            if (h_ctl->abort != TREE_STALL) break;
+            if ((rc = hip_check(ctx, launch_tree_more(ta, *h_ctl, h_off, seq, s), "tree")) != IBIP_OK) return rc;
+        }
         treed = !h_ctl->abort;
         if (treed) {
             h_st->k = h_job->K + 1;
@@ -2527,10 +2532,14 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     }
     int32_t* seq_c = (int32_t*)top;
     if ((rc = hip_check(ctx, launch_tree_levels(ta, h_off, seq_c, s), "tree")) != IBIP_OK) return rc;
-    tm.mark(4, s);
-    if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
-        return rc;
-    if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+    for (;;) {
+        tm.mark(4, s);
+        if ((rc = hip_check(ctx, hipMemcpyAsync(h_ctl, ta.ctl, head_bytes, hipMemcpyDeviceToHost, s), "copy")) != IBIP_OK)
+            return rc;
+        if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
+        if (h_ctl->abort != TREE_STALL) break;
+        if ((rc = hip_check(ctx, launch_tree_more(ta, *h_ctl, h_off, seq_c, s), "tree")) != IBIP_OK) return rc;
+    }
     if (tm.on) ctx->timing.loop_kernel_ms += tm.ms(3, 4);
     if (h_ctl->abort) {
         alone.insert(alone.end(), g.job.begin(), g.job.end());

@@ -246,6 +246,14 @@ bool advance(ibip_server* S, int si, hipError_t* e, std::unique_lock<std::mutex>
             if (r == hipSuccess) r = launch_loop(S, sl, J);
             sl.phase = P_LOOP;
         }
+    } else if (sl.phase == P_TREE && h_ctl->abort == TREE_STALL) {
+        const TreeCtl c = *h_ctl;
+        lk.unlock();
+        r = launch_tree_more(sl.tree, c, h_off, jb.seq, sl.stream);
+        if (r == hipSuccess)
+            r = hipMemcpyAsync(h_ctl, sl.tree.ctl, sizeof(TreeCtl) + sizeof(TreeJob), hipMemcpyDeviceToHost, sl.stream);
+        lk.lock();
+        state_back = false;
     } else if (sl.phase == P_TREE && h_ctl->abort) {
         // more peaks, steps or candidates than there is room for
         r = job_tree_undo(b, sl.tree, jb.inlets, jb.dims, jb.seq, sl.stream);

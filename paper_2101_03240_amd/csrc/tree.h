@@ -22,9 +22,25 @@ __device__ inline uint32_t nb_bits(uint32_t x, uint32_t y, uint32_t z, int X, in
            (y + 1 < (uint32_t)Y ? 8u : 0u) | (z > 0 ? 16u : 0u) | (z + 1 < (uint32_t)Z ? 32u : 0u);
 }
 
-// Rounds after the first that a level of many voxels runs over the whole GPU,
-// at most.
-constexpr int kTreePulls = 6;
+// Counts of the voxels that a level's rounds over the whole GPU left: round r's in
+// slot r % kTreeSlots (a round reads the one before it and clears the one after).
+constexpr uint32_t kTreeSlots = 8;
+// A level that leaves more voxels than this after its rounds over the whole GPU gets
+// more of them, since one workgroup goes through what is left. How many rounds a
+// level takes is known only as they go (a plateau, as between parallel plates, takes
+// one per voxel of its length), so the launches that follow stop short and the host
+// queues on (TreeStop). 512^3 blurred noise leaves at most 24 k in any level and
+// never comes back. ms, at 2^17, 2^16, 2^15 and 2^14: 256^3 noise of sigma 2 27.8, 20.9,
+// 16.7, 15.0; sigma 1 19.9, 16.2, 15.9, 16.0; plane 500^2 of sigma 1 15.5, 15.5, 4.3,
+// 4.3; 256^3 noise of single voxels 46 with any of them, 5,309 without.
+constexpr uint32_t kTreeStall = 1u << 15;
+constexpr uint32_t kTreeMore = 4096;  // rounds queued at a time, at most
+// Why the launches after a tree's kernel do nothing.
+enum TreeStop : uint32_t {
+    TREE_RUN = 0,
+    TREE_GIVE_UP = 1,  // a capacity was exceeded: the step loop runs instead
+    TREE_STALL = 2,    // level stall_t wants more rounds: launch_tree_more
+};
 
 // Counters of one tree, zeroed before its first kernel.
 struct TreeCtl {
@@ -32,9 +48,10 @@ struct TreeCtl {
     uint32_t nroot;   // peaks never merged (ids nmerge..nmerge+nroot-1)
     uint32_t nev;     // events, the root event 0 included
     uint32_t nblk;    // blocks of events
-    uint32_t ucnt[kTreePulls + 2];  // voxels that round r of the current level left
+    uint32_t ucnt[kTreeSlots];  // voxels that the rounds of the current level left
     uint32_t xcnt[2]; // candidates claimed at the current level; the two in turn
-    uint32_t abort;   // a capacity was exceeded: the step loop runs instead
+    uint32_t abort;   // TreeStop
+    uint32_t stall_t, stall_r;  // the level that wants more rounds, and its rounds so far
     uint32_t pad;
     uint32_t popped[kCountSlots];  // centres, by block
 };
@@ -215,6 +232,10 @@ hipError_t launch_tree_seed(const TreeArgs& a, uint32_t vox, const uint8_t* inle
 // in a.jobs (or ctl->abort), and seq (the memory of a.top) = INT_MAX on pore,
 // -1 on solid.
 hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off_host, int32_t* seq, hipStream_t s);
+// The same from the level on that `c`, the control words read back, says wants more
+// rounds (TREE_STALL): four times its rounds so far, so that a level of many rounds
+// comes back few times.
+hipError_t launch_tree_more(const TreeArgs& a, const TreeCtl& c, const uint32_t* off_host, int32_t* seq, hipStream_t s);
 // One job after job_setup_ranks, whose state and slice offsets the host has
 // read: the tree's arguments (tree_carve lays its own scratch out, tree_words
 // of them), the whole tree on s (head: zeroed control words and the job's

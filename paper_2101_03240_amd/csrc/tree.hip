@@ -240,7 +240,7 @@ __device__ inline void uf_union(const TreeArgs& a, uint64_t* uf, uint64_t p, uin
 template <bool kPlace>
 __global__ __launch_bounds__(kWg) void k_tree_edges(TreeArgs a, TreeBasins t, int rounds) {
     if (t.b.ctl->abort || t.b.ctl->abort_edges || t.b.ctl->live[rounds - 1]) {
-        if (threadIdx.x == 0) a.ctl->abort = 1;
+        if (threadIdx.x == 0) a.ctl->abort = TREE_GIVE_UP;
         return;
     }
     extern __shared__ uint32_t cnt[];  // R + 1
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256) void k_tree_peaks(TreeArgs a, TreeBasins t) {
     const uint32_t nm = a.ctl->nmerge;
     if (a.ctl->abort) return;
     if (nm > a.pcap) {
-        if (tid == 0) a.ctl->abort = 1;
+        if (tid == 0) a.ctl->abort = TREE_GIVE_UP;
         return;
     }
     for (uint32_t i = tid; i < nm; i += nth) {
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(256) void k_tree_peaks(TreeArgs a, TreeBasins t) {
                 a.cpm[i] = make_uint2(0u, i);
                 peak_init(a, i);
             } else {
-                a.ctl->abort = 1;
+                a.ctl->abort = TREE_GIVE_UP;
             }
         }
     }
@@ -528,7 +528,7 @@ __device__ inline bool tree_thread(const TreeArgs& a, uint32_t g, uint32_t code)
 }
 __device__ inline void tree_block(const TreeArgs& a, uint32_t b, uint32_t g) {
     if (b < a.ecap) st(&a.bg[b], g);
-    else st(&a.ctl->abort, 1u);
+    else st(&a.ctl->abort, (uint32_t)TREE_GIVE_UP);
 }
 // The same for the lanes with `want` of a whole wave: neighbouring lanes mostly
 // share a thread, and the first of a run raises its code to the run's highest
@@ -543,7 +543,7 @@ __device__ inline bool wave_thread(const TreeArgs& a, bool want, uint32_t g, uin
 // thread g: entry x of the level's list.
 __device__ inline void tree_edge(const TreeArgs& a, uint32_t x, uint32_t w, uint32_t pid, uint32_t g) {
     if (x >= a.xcap) {
-        st(&a.ctl->abort, 1u);
+        st(&a.ctl->abort, (uint32_t)TREE_GIVE_UP);
         return;
     }
     st(&a.X[3 * (uint64_t)x], w);
@@ -849,7 +849,7 @@ __device__ inline void tree_rounds(const TreeArgs& a, Lists& s, const uint32_t* 
         const uint32_t f1 = uniform(s.f), e1 = uniform(s.e);
         if (f0 == f1 && e0 == e1) break;
         if (r >= limit) {
-            if (tid == 0) st(&a.ctl->abort, 1u);
+            if (tid == 0) st(&a.ctl->abort, (uint32_t)TREE_GIVE_UP);
             break;
         }
         __syncthreads();  // every wave has read the lengths
@@ -916,7 +916,7 @@ __device__ inline void tree_events(const TreeArgs& a, uint32_t t) {
         const uint32_t g = ld(&a.bg[b]), cnt = ld(&a.gm[g]) & rm;
         const uint32_t base = atomicAdd(&a.ctl->nev, cnt);
         if (base > a.ecap || cnt > a.ecap - base) {
-            st(&a.ctl->abort, 1u);
+            st(&a.ctl->abort, (uint32_t)TREE_GIVE_UP);
             continue;
         }
         a.bbase[b] = base;
@@ -965,8 +965,14 @@ __global__ __launch_bounds__(kWg) void k_tree_round1(TreeArgs a, uint32_t t, uin
 __global__ __launch_bounds__(kWg) void k_tree_pull(TreeArgs a, uint32_t t, uint32_t side, uint32_t r) {
     if (a.ctl->abort) return;
     TreeCtl* c = a.ctl;
-    tree_pull<true>(a, r & 1u ? a.U2 : a.U, c->ucnt[r - 1], r & 1u ? a.U : a.U2, &c->ucnt[r], nullptr, nullptr,
-                    &c->xcnt[side], t, r, blockIdx.x * kWg + threadIdx.x, gridDim.x * kWg);
+    if (blockIdx.x == 0 && threadIdx.x == 0) st(&c->ucnt[(r + 1) % kTreeSlots], 0u);
+    tree_pull<true>(a, r & 1u ? a.U2 : a.U, c->ucnt[(r - 1) % kTreeSlots], r & 1u ? a.U : a.U2,
+                    &c->ucnt[r % kTreeSlots], nullptr, nullptr, &c->xcnt[side], t, r,
+                    blockIdx.x * kWg + threadIdx.x, gridDim.x * kWg);
+}
+
+__global__ void k_tree_go_on(TreeArgs a) {
+    if (a.ctl->abort == TREE_STALL) a.ctl->abort = TREE_RUN;
 }
 
 __global__ __launch_bounds__(256) void k_tree_claim(TreeArgs a, uint32_t t, uint32_t side, uint32_t lo, uint32_t hi) {
@@ -985,11 +991,20 @@ __device__ inline void tree_levels(const TreeArgs& a, Lists& s, uint32_t t_lo, u
     for (uint32_t t = t_lo; t <= t_hi; t++) {
         if (uniform(ld(&c->abort))) return;
         if (tid == 0) {
-            s.u = r0 ? c->ucnt[r0] : 0u;
+            s.u = r0 ? c->ucnt[r0 % kTreeSlots] : 0u;
             s.x = r0 ? c->xcnt[side] : 0u;
             s.u2 = s.f = s.e = s.scan = 0;
         }
         __syncthreads();
+        if (uniform(s.u) > kTreeStall) {
+            if (tid == 0) {
+                c->stall_t = t;
+                c->stall_r = r0;
+                // (the codes of rounds to come have to fit)
+                st(&c->abort, (uint32_t)(r0 + kTreeMore < (1u << a.kb) - 1u ? TREE_STALL : TREE_GIVE_UP));
+            }
+            return;
+        }
         const uint32_t i0 = a.off[t], i1 = a.off[t + 1];
         uint32_t r = r0;
         bool found = false;
@@ -1003,7 +1018,8 @@ __device__ inline void tree_levels(const TreeArgs& a, Lists& s, uint32_t t_lo, u
         }
         const uint32_t u = uniform(s.u);
         uint32_t* const in = r & 1u ? a.U : a.U2;
-        if (!found && u && !(u <= kLds && tree_search<false>(a, s, in, 0, u, t, r))) {
+        // (the search in LDS holds rounds in 16 bits, and adds at most kLds of them)
+        if (!found && u && !(u <= kLds && r <= 32768u && tree_search<false>(a, s, in, 0, u, t, r))) {
             uint32_t* const out = r & 1u ? a.U2 : a.U;
             tree_pull<false>(a, in, u, out, &s.u2, &s.f, &s.e, &s.x, t, r + 1, tid, kWg);
             __syncthreads();
@@ -1023,7 +1039,7 @@ __device__ inline void tree_levels(const TreeArgs& a, Lists& s, uint32_t t_lo, u
                 // are claimed by the next launch)
                 c->xcnt[side] = s.x;
                 c->xcnt[side ^ 1u] = 0;
-                for (int q = 0; q < kTreePulls + 2; q++) c->ucnt[q] = 0;
+                for (uint32_t q = 0; q < kTreeSlots; q++) c->ucnt[q] = 0;
             }
         }
         __syncthreads();
@@ -1181,20 +1197,25 @@ hipError_t launch_tree_seed(const TreeArgs& a, uint32_t vox, const uint8_t* inle
     return hipGetLastError();
 }
 
-hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off, int32_t* seq, hipStream_t s) {
+// Levels t0.. and phase 3; r > 0: level t0 has had r rounds and gets `more`.
+static hipError_t levels_from(const TreeArgs& a, const uint32_t* off, int32_t* seq, uint32_t t0, uint32_t r,
+                              uint32_t more, hipStream_t s) {
     auto size = [&](uint32_t t) { return off[t + 1] - off[t]; };
-    hipLaunchKernelGGL(k_tree_start, dim3(64), dim3(256), 0, s, a);
     uint32_t side = 0;
-    for (uint32_t t = 1; t <= a.R;) {
+    for (uint32_t t = 1; t < t0; t++) side ^= size(t) > kTreeSmall ? 1u : 0u;
+    for (uint32_t t = t0; t <= a.R;) {
         if (size(t) > kTreeSmall) {
             // further rounds over the whole GPU where round 1 may leave many
             const uint32_t n = size(t);
-            const uint32_t r0 = n > (1u << 19) ? 7u : n > (1u << 17) ? 5u : n > (1u << 15) ? 4u : n > (1u << 13) ? 2u : 1u;
-            hipLaunchKernelGGL(k_tree_round1, dim3(std::min(blocks(n, kWg), 4096u)), dim3(kWg), 0, s, a, t, side,
-                               off[t], off[t + 1]);
-            for (uint32_t r = 2; r <= r0; r++)
+            uint32_t r0 = n > (1u << 19) ? 7u : n > (1u << 17) ? 5u : n > (1u << 15) ? 4u : n > (1u << 13) ? 2u : 1u;
+            if (r) r0 = r + more;
+            else
+                hipLaunchKernelGGL(k_tree_round1, dim3(std::min(blocks(n, kWg), 4096u)), dim3(kWg), 0, s, a, t, side,
+                                   off[t], off[t + 1]);
+            for (uint32_t q = r ? r + 1 : 2; q <= r0; q++)
                 hipLaunchKernelGGL(k_tree_pull, dim3(std::min(blocks(n, 4 * kWg), 512u)), dim3(kWg), 0, s, a, t,
-                                   side, r);
+                                   side, q);
+            r = 0;
             hipLaunchKernelGGL(k_tree_levels, dim3(1), dim3(kWg), 0, s, a, t, t, r0, side);
             hipLaunchKernelGGL(k_tree_claim, dim3(std::min(blocks(size(t)), 4096u)), dim3(256), 0, s, a, t, side,
                                off[t], off[t + 1]);
@@ -1218,6 +1239,16 @@ hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off, int32_t* s
     hipLaunchKernelGGL(k_tree_steps, dim3(ge), dim3(256), 0, s, a, in);
     hipLaunchKernelGGL(k_tree_finish, dim3(std::min(blocks(a.n), 8192u)), dim3(256), 0, s, a, in, seq);
     return hipGetLastError();
+}
+
+hipError_t launch_tree_levels(const TreeArgs& a, const uint32_t* off, int32_t* seq, hipStream_t s) {
+    hipLaunchKernelGGL(k_tree_start, dim3(64), dim3(256), 0, s, a);
+    return levels_from(a, off, seq, 1, 0, 0, s);
+}
+
+hipError_t launch_tree_more(const TreeArgs& a, const TreeCtl& c, const uint32_t* off, int32_t* seq, hipStream_t s) {
+    hipLaunchKernelGGL(k_tree_go_on, dim3(1), dim3(1), 0, s, a);
+    return levels_from(a, off, seq, c.stall_t, c.stall_r, std::min(std::max(4 * c.stall_r, 64u), kTreeMore), s);
 }
 
 hipError_t launch_tree_undo(const TreeArgs& a, int32_t* seq, uint32_t* head, uint32_t* tail, hipStream_t s) {

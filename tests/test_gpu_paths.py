@@ -69,3 +69,35 @@ def test_planes_of_many_steps_take_the_tree(dev, side, sigma):
     r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl)))
     assert loops == 0
     _same(r, ref)
+
+
+def _plates(shape, width):
+    """Parallel plates `width` voxels apart: each distance is one plateau, and the
+    one in the middle is searched from the inlet face voxel by voxel."""
+    img = np.zeros(shape, np.uint8)
+    for i in range(width):
+        img[:, :, i::width + 1] = 1
+    img[-1, -1, -1] = 0
+    return img
+
+
+# levels that leave more than 2^15 voxels after their first rounds, for 40 to 240
+# rounds more (they come back for more rounds once, or twice)
+@pytest.mark.parametrize("name, shape", [("plates 1", (120, 90, 40)), ("plates 2", (60, 100, 63)),
+                                         ("plates 7", (250, 100, 64)), ("salt", (90, 100, 110))])
+def test_plateaus(dev, name, shape):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    rng = np.random.default_rng(3)
+    img = ((rng.random(shape) < 0.6).astype(np.uint8) if name == "salt"
+           else _plates(shape, int(name.split()[1])))
+    inl = synth.face_mask(img.shape, 0, 0)
+    ref = oracle.invade(img, inl)
+    r = ibip.invade(_put(dev, img), _put(dev, inl))
+    _same(r, ref)
+    b = ibip.invade_batch([_put(dev, img)] * 2, [_put(dev, inl)] * 2)
+    for x in b:
+        _same(x, ref)
+    with ibip.Server(dev, hbm_budget_bytes=1 << 30, max_inflight=2) as srv:
+        _same(srv.wait(srv.submit(_put(dev, img), _put(dev, inl))), ref)
