@@ -78,7 +78,15 @@ void* ensure(ibip_ctx* ctx, BufId id, size_t bytes) {
     void* p = nullptr;
     if (hipMalloc(&p, want) != hipSuccess) {
         (void)hipGetLastError();
-        return nullptr;
+        Buf& tree = ctx->buf[B_TREE];
+        if (id == B_TREE || ctx->tree_used || !tree.p) return nullptr;
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return nullptr;
+        (void)hipFree(tree.p);
+        tree = Buf{};
+        if (hipMalloc(&p, want) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
     }
     b.p = p;
     b.bytes = want;

@@ -264,6 +264,7 @@ struct ibip_ctx {
     int64_t last_K = -1;
     int64_t last_n_pore = 0;
     bool have_steps = false;
+    bool tree_used = false;        // work on B_TREE is queued or about to be (TreeUse)
     uint32_t readings = 0;         // IBIP_READ_* flags for the following calls
     ibip_tuning tuning = {};       // launch parameters (zero: defaults)
 };
@@ -274,8 +275,17 @@ namespace ibip {
 ibip_status fail(ibip_ctx* ctx, ibip_status st, const std::string& what);
 // Map a HIP error to IBIP_EDEVICE with a message; IBIP_OK if e == hipSuccess.
 ibip_status hip_check(ibip_ctx* ctx, hipError_t e, const char* what);
-// Ensure buffer `id` holds at least `bytes`; returns its pointer or nullptr.
+// Ensure buffer `id` holds at least `bytes`; returns its pointer or nullptr. Where
+// the device has no room, the tree's scratch (B_TREE), which no call needs, is given
+// back first unless it is in use.
 void* ensure(ibip_ctx* ctx, BufId id, size_t bytes);
+// B_TREE is in use while this lives.
+struct TreeUse {
+    ibip_ctx* ctx;
+    explicit TreeUse(ibip_ctx* c) : ctx(c) { ctx->tree_used = true; }
+    ~TreeUse() { ctx->tree_used = false; }
+    TreeUse(const TreeUse&) = delete;
+};
 void* pinned(ibip_ctx* ctx, size_t bytes);
 // ctx->done_host/done_dev with at least `words` words, zeroed; false on failure.
 bool done_records(ibip_ctx* ctx, size_t words);

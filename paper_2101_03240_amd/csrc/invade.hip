@@ -37,6 +37,7 @@
 // it, since a ball it skipped is covered by an earlier ball.
 #include <chrono>
 #include <climits>
+#include <optional>
 #include <thread>
 #include <vector>
 
@@ -1806,8 +1807,9 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
                        R, st);
     // The component tree takes every call that it can: not a resumption, and
     // not one stopped after so few steps that the step loop ends first.
-    const bool tree = n_pore > 0 && !big && !resume_cs && !(opts && opts->max_steps > 0 && opts->max_steps < kTreeMinSteps);
+    bool tree = n_pore > 0 && !big && !resume_cs && !(opts && opts->max_steps > 0 && opts->max_steps < kTreeMinSteps);
     TreeArgs ta{};
+    std::optional<TreeUse> tree_use;
     if (tree) {
         if (!ctx->copy_ev &&
             (rc = hip_check(ctx, hipEventCreateWithFlags(&ctx->copy_ev, hipEventDisableTiming), "event")) != IBIP_OK)
@@ -1837,9 +1839,14 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         uint32_t lcap = 0;
         for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
         tree_caps(ta, (uint32_t)n_pore, 1, lcap);
-        uint32_t* w = (uint32_t*)ensure(ctx, B_TREE, tree_words(ta) * sizeof(uint32_t));
-        if (!w) return fail(ctx, IBIP_ENOMEM, "invade: scratch allocation failed");
-        tree_carve(ta, w);
+        tree_use.emplace(ctx);
+        if (uint32_t* w = (uint32_t*)ensure(ctx, B_TREE, tree_words(ta) * sizeof(uint32_t))) {
+            tree_carve(ta, w);
+        } else {
+            // no room for the tree's own scratch: the step loop needs none of it
+            tree = false;
+            if ((rc = hip_check(ctx, launch_tree_undo(ta, seq, head, tail, s), "undo")) != IBIP_OK) return rc;
+        }
     } else {
         hipLaunchKernelGGL(k_convert, dim3(blocks(n)), dim3(256), 0, s, image, key, present, n, (uint32_t)(V - 1), state,
                            seq, d.X, d.Y, d.Z, make_fastdiv((uint32_t)d.Z), make_fastdiv((uint32_t)d.Y), R);
@@ -1891,6 +1898,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
                                (ctx->readings & IBIP_READ_MASK_INLETS) != 0, R);
         }
     }
+    tree_use.reset();  // (the tree's launches have ended, or none was made)
     if (!treed) {
         // loop control
         h_st->k = 1 + (uint32_t)(resume_cs ? k_done : 0);
@@ -2505,6 +2513,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     tree_caps(ta, n_pore, (uint32_t)m, lcap);
     // list, thread of each place (then the full balls), M; the tree's own
     const size_t pore_bytes = align256(4 * ((size_t)n_pore + 1));
+    TreeUse tree_use(ctx);
     uint8_t* tb = (uint8_t*)ensure(ctx, B_TREE, 3 * pore_bytes + 4 * tree_words(ta));
     if (!tb) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
     uint32_t* list = (uint32_t*)tb;

@@ -344,6 +344,7 @@ static ibip_status reconstruct_basins(ibip_ctx* ctx, const int32_t* seq, const u
     hipStream_t s = ctx->stream;
     BasinArgs a{};
     basin_caps(a, d);
+    TreeUse tree_use(ctx);
     void* mem = ensure(ctx, B_TREE, basin_bytes(a));
     uint32_t* h = (uint32_t*)pinned(ctx, 4096);
     if (!mem || !h) return IBIP_OK;

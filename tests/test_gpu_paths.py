@@ -101,3 +101,60 @@ def test_plateaus(dev, name, shape):
         _same(x, ref)
     with ibip.Server(dev, hbm_budget_bytes=1 << 30, max_inflight=2) as srv:
         _same(srv.wait(srv.submit(_put(dev, img), _put(dev, inl))), ref)
+
+
+def _in_thread(fn):
+    """fn on a thread of its own: a context that holds no scratch yet."""
+    import concurrent.futures as cf
+    with cf.ThreadPoolExecutor(1) as pool:
+        return pool.submit(fn).result()
+
+
+def _fill(dev, left):
+    """Tensors that leave `left` bytes of the device (what is free is known a little late)."""
+    import torch
+
+    fill = []
+    for _ in range(3):
+        room = torch.cuda.mem_get_info(dev)[0] - left
+        if room > 0:
+            fill.append(torch.empty(room, dtype=torch.uint8, device=dev))
+    return fill
+
+
+def test_no_room_for_the_tree(dev):
+    """On a device that is nearly full the invasion runs its step loop in the
+    scratch that it has; the tree's scratch, once there, makes room for other calls'."""
+    import torch
+
+    import paper_2101_03240_amd as ibip
+
+    img = synth.blurred_noise_device((256, 256, 256), 4.0, 0.6, 2, dev)
+    img[-1, -1, -1] = 0
+    inl = _put(dev, synth.face_mask(img.shape, 0, 0))
+    long_img = torch.cat([img, img])
+    d = _in_thread(lambda: ibip.edt(long_img))
+
+    def work():
+        ibip.invade(img, inl, max_steps=3)  # the step loop's scratch
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        keep = [torch.empty(img.numel() * 4, dtype=torch.uint8, device=dev) for _ in range(8)]
+        fill = _fill(dev, 96 << 20)  # (the tree takes 550 MB)
+        del keep  # (the results' memory)
+        r, loops = _loops(lambda: ibip.invade(img, inl))
+        del fill
+        torch.cuda.empty_cache()
+        r2, loops2 = _loops(lambda: ibip.invade(img, inl))
+        torch.cuda.empty_cache()
+        keep = torch.empty(long_img.numel() * 4, dtype=torch.uint8, device=dev)
+        fill = _fill(dev, 32 << 20)  # (the distances' scratch grows by 100 MB)
+        del keep
+        return r, loops, r2, loops2, ibip.edt(long_img)
+
+    r, loops, r2, loops2, d2 = _in_thread(work)
+    assert loops > 0 and loops2 == 0
+    assert r["K"] == r2["K"]
+    for k in ("centre_step", "seq", "rad2", "M"):
+        assert torch.equal(r[k], r2[k]), k
+    assert torch.equal(d, d2)
