@@ -52,8 +52,8 @@ struct BasinArgs {
     BasinCtl* ctl;   // zero before the launches
     uint64_t* H;     // [pall + 1] per basin (weight << 32 | basin above), itself at a root; O at pall
     uint64_t* best;  // [2][pall + 1] best edge offered (weight << 32 | edge), by the round's parity
-    uint64_t* ends;  // [slots * ecap] an edge's basins
-    uint32_t* wt;    // [slots * ecap] an edge's weight
+    uint64_t* ends;  // [eall] an edge's basins
+    uint32_t* wt;    // [eall] an edge's weight
     uint32_t* par;   // [n] climb, then label
     // for the component tree (else null): the edge by which a root was hooked
     // (weight << 32 | other root), and each basin's top voxel
@@ -62,7 +62,7 @@ struct BasinArgs {
     int64_t n;
     int X, Y, Z;
     int nty, ntz;    // tiles along y and z
-    uint32_t pcap, pall, ecap;
+    uint32_t pcap, pall, ecap, eall;  // places of a slot's list and of all: basins, edges
 };
 
 // Sizes of the lists for an image; the scratch they take; its layout at `mem`

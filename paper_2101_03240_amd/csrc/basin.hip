@@ -475,18 +475,25 @@ void basin_caps(BasinArgs& a, ibip_dims d) {
     const int ty = a.X == 1 ? Tile<true>::TY : Tile<false>::TY;
     a.nty = (a.Y + ty - 1) / ty;
     a.ntz = (a.Z + Tile<true>::TZ - 1) / Tile<true>::TZ;
-    // each slot takes every kBasinSlots-th tile's voxels
+    // Each slot takes every kBasinSlots-th tile's voxels, those of the image: a tile
+    // of an image one or a few voxels thick holds that share of its 2,048, and an
+    // image of few tiles uses that many slots. So the lists have room for an eighth
+    // and half of the voxels, 1.8 times that at most where the last tiles are mostly
+    // outside, and places in them fit 32 bits for any image (fewer than 2^31 voxels).
     const int64_t nt = a.X == 1 ? tiles<true>(a) : tiles<false>(a);
-    const int64_t per = (nt + kBasinSlots - 1) / kBasinSlots * kTileVoxels;
-    const bool all = per * kBasinSlots <= 1 << 20;  // room for whatever the image holds
+    const int64_t held = (int64_t)std::min(a.X, a.X == 1 ? 1 : Tile<false>::TX) * std::min(a.Y, ty) *
+                         std::min(a.Z, Tile<true>::TZ);
+    const int64_t slots = std::min<int64_t>(nt, kBasinSlots);
+    const int64_t per = (nt + slots - 1) / slots * held;
+    const bool all = per * slots <= 1 << 20;  // room for whatever the image holds
     a.pcap = (uint32_t)(all ? per : per / 8);
     a.ecap = (uint32_t)(all ? 4 * per : per / 2);
-    a.pall = a.pcap * kBasinSlots;
+    a.pall = a.pcap * (uint32_t)slots;
+    a.eall = a.ecap * (uint32_t)slots;
 }
 
 size_t basin_bytes(const BasinArgs& a) {
-    return sizeof(BasinCtl) + 8 * (3 * ((size_t)a.pall + 1) + (size_t)a.ecap * kBasinSlots) +
-           4 * ((size_t)a.ecap * kBasinSlots + (size_t)a.n);
+    return sizeof(BasinCtl) + 8 * (3 * ((size_t)a.pall + 1) + (size_t)a.eall) + 4 * ((size_t)a.eall + (size_t)a.n);
 }
 
 void basin_carve(BasinArgs& a, void* mem) {
@@ -496,8 +503,8 @@ void basin_carve(BasinArgs& a, void* mem) {
     a.H = (uint64_t*)m;
     a.best = a.H + a.pall + 1;
     a.ends = a.best + 2 * ((size_t)a.pall + 1);
-    a.wt = (uint32_t*)(a.ends + (size_t)a.ecap * kBasinSlots);
-    a.par = a.wt + (size_t)a.ecap * kBasinSlots;
+    a.wt = (uint32_t*)(a.ends + (size_t)a.eall);
+    a.par = a.wt + (size_t)a.eall;
 }
 
 hipError_t launch_basin_graph(const BasinArgs& a, const int32_t* seq, const uint32_t* cap32, bool conn26,

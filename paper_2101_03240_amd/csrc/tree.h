@@ -132,7 +132,7 @@ inline TreeBasins tree_basins(const TreeArgs& a, char* mem, size_t* bytes) {
         m += (k + 7) / 8 * 8;
         return p;
     };
-    const size_t P = (size_t)t.b.pall + 1, E = (size_t)t.b.ecap * kBasinSlots;
+    const size_t P = (size_t)t.b.pall + 1, E = (size_t)t.b.eall;
     t.b.ctl = (BasinCtl*)take(sizeof(BasinCtl));
     t.cnt = (uint32_t*)take(4 * ((size_t)a.R + 2));
     t.at = (uint32_t*)take(4 * ((size_t)a.R + 2));

@@ -152,9 +152,34 @@ def test_no_room_for_the_tree(dev):
         del keep
         return r, loops, r2, loops2, ibip.edt(long_img)
 
-    r, loops, r2, loops2, d2 = _in_thread(work)
+    try:
+        r, loops, r2, loops2, d2 = _in_thread(work)
+    finally:
+        torch.cuda.empty_cache()  # (the memory that filled the device)
     assert loops > 0 and loops2 == 0
     assert r["K"] == r2["K"]
     for k in ("centre_step", "seq", "rad2", "M"):
         assert torch.equal(r[k], r2[k]), k
     assert torch.equal(d, d2)
+
+
+# thin images, whose tiles hold few voxels: lists for whatever the image holds, and
+# for an eighth and half of the voxels
+@pytest.mark.parametrize("shape", [(900, 700, 1), (1500, 1000, 1), (1100, 1, 1200), (900, 800, 2), (4, 3, 30000)])
+def test_thin_images(dev, shape):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = np.ascontiguousarray(synth.blurred_noise((1, 1500, 1200), 3.0, 0.6, 6)[0].reshape(-1)[:np.prod(shape)]
+                               .reshape(shape))
+    img[-1, -1, -1] = 0
+    axis = 2 if shape[2] > 2 else 0
+    inl, out = synth.face_mask(shape, axis, 0), synth.face_mask(shape, axis, shape[axis] - 1)
+    ref = oracle.invade(img, inl)
+    r = ibip.invade(_put(dev, img), _put(dev, inl))
+    _same(r, ref)
+    t, rt = ibip.trap(r["seq"], _put(dev, out)), oracle.trap(ref["seq"], out)
+    assert np.array_equal(t["seq_trapped"].cpu().numpy(), rt["seq_trapped"])
+    T = [25, 9, 4, 1]
+    m, rm = ibip.opening_drainage(_put(dev, img), _put(dev, inl), T), oracle.mio(img, inl, np.array(T, np.uint32))
+    assert np.array_equal(m["mio_r2"].cpu().numpy().view(np.uint32), rm["mio_r2"])
