@@ -197,7 +197,7 @@ struct LoopState {
     uint32_t pad2;     // resumption: set when the checkpoint is not a valid one
     int64_t max_steps;
     uint32_t full_done;  // full-ball list entries painted by earlier insertion passes
-    uint32_t pad3;
+    uint32_t largest;    // voxels of the most frequent rank
 };
 
 enum LoopStatus : uint32_t { LS_RUN = 0, LS_DONE = 1, LS_WIDE = 2, LS_MAXSTEPS = 3, LS_CANCEL = 4 };

@@ -37,6 +37,7 @@
 // it, since a ball it skipped is covered by an earlier ball.
 #include <chrono>
 #include <climits>
+#include <cmath>
 #include <optional>
 #include <thread>
 #include <vector>
@@ -120,10 +121,14 @@ __global__ __launch_bounds__(256) void k_hist(const uint32_t* __restrict__ dt2,
     }
 }
 
-// present[v] = 1 if some pore voxel has dt2 == v (v >= 1)
-__global__ void k_present(const uint32_t* hist, uint32_t* present, int64_t V) {
-    int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < V) present[v] = (v >= 1 && hist[v] > 0) ? 1u : 0u;
+// present[v] = 1 if some pore voxel has dt2 == v (v >= 1); the largest count
+__global__ __launch_bounds__(256) void k_present(const uint32_t* hist, uint32_t* present, int64_t V, LoopState* st) {
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    uint32_t c = v >= 1 && v < V ? hist[v] : 0u;
+    if (v < V) present[v] = c > 0 ? 1u : 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c = max(c, (uint32_t)__shfl_xor(c, o, 64));
+    if ((threadIdx.x & 63) == 0 && c) atomicMax(&st->largest, c);
 }
 
 // After the scans: offv[v] = bucket offset of value v, rk[v] = rank - 1 of v.
@@ -1736,6 +1741,39 @@ hipError_t launch_finalise(int32_t* seq, int64_t n, const uint32_t* M, uint32_t*
 // ---------------------------------------------------------------------------
 // Host driver
 // ---------------------------------------------------------------------------
+// Expected times of an invasion with its distances, ranks, insertion and arrays, ms,
+// by the step loop and by the component tree. Measured on 70 images (cubes of 12 to
+// 512, planes of 60 to 2,000, slabs, noise of sigma 1.5 to 6, grains) and step limits
+// on them, each both ways. Steps per pore voxel fall with the number of ranks, which
+// tells how coarse the pore space is, and are ten times as many in a plane; a step
+// takes about 1 us in a plane and 1.3 in a volume; the tree's time is that of the
+// levels' searches, one after another, and of passes over the pore voxels. The rule
+// below took the slower path on one of them (40^3, sigma 1.5: 1.55 ms by steps, 1.32 by
+// the tree). ms by steps and by the tree: 16^3 0.39 and 1.09; 48^3 2.05, 2.08; 64^3 3.77,
+// 2.83; 128^3 16.9, 6.0; plane 90^2 0.89, 1.48; 260^2 4.37, 2.01; 512^3 502, 54.6; 512^3
+// stopped after 5,000 steps 11.6, 54.6.
+double loop_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R, int64_t max_steps) {
+    const bool plane = d.X == 1 || d.Y == 1 || d.Z == 1;
+    double steps = (plane ? 0.42 : 0.055) * (double)n_pore / std::cbrt((double)R);
+    if (max_steps > 0) steps = std::min(steps, (double)max_steps);
+    return 0.25 + (plane ? 0.97e-3 : 1.3e-3) * steps;
+}
+double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R) {
+    const bool plane = d.X == 1 || d.Y == 1 || d.Z == 1;
+    return 0.5 + 0.011 * R + (plane ? 0.8e-3 : 0.3e-3) * std::pow((double)n_pore, 2.0 / 3.0);
+}
+
+// Where one rank holds almost all of the pore space (27/32 of it or more), the steps
+// are few and each spreads over much of the image, and the tree's one level is
+// searched round by round: 256^3 noise of single voxels, porosity 0.6 (95 % at rank 1),
+// 18.9 ms by steps and 46 by the tree; its plane 700^2 (87 %) 11.2 and 21.0; 200^3 at
+// porosity 0.7 (88 %) 19.1 and 18.6; planes at 0.7 (76 %) 8.2 and 6.7; 200^3 blurred by
+// 0.7 voxels (76 %) 36.5 and 19.3.
+bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps) {
+    return n_pore > 0 && 32 * (int64_t)largest <= 27 * n_pore &&
+           loop_ms_expected(d, n_pore, R, max_steps) > tree_ms_expected(d, n_pore, R);
+}
+
 ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlets, ibip_dims d,
                        const ibip_invade_opts* opts, int32_t* seq, uint32_t* rad2, int32_t* centre_step,
                        int64_t* n_steps, const int32_t* resume_cs, int64_t k_done) {
@@ -1776,7 +1814,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     // a2: histogram -> ranks and bucket slices
     hipLaunchKernelGGL(k_hist, dim3(std::min<int64_t>(blocks(n), kHistBlocks)), dim3(256), 0, s, key, n,
                        (uint32_t)(V - 1), hist, st);
-    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, hist, present, V);
+    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, hist, present, V, st);
     hipLaunchKernelGGL(k_copy_u32, dim3(blocks(V)), dim3(256), 0, s, present, flags, V);
     if ((rc = hip_check(ctx, launch_scan_u32(hist, V, partials, dummy_total, s), "scan")) != IBIP_OK) return rc;
     if ((rc = hip_check(ctx, launch_scan_u32(present, V, partials, &st->R, s), "scan")) != IBIP_OK) return rc;
@@ -1805,9 +1843,9 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
     if ((rc = hip_check(ctx, hipMemsetAsync(tail, 0, sizeof(uint32_t) * (R + 2), s), "memset")) != IBIP_OK) return rc;
     hipLaunchKernelGGL(k_rank_tables, dim3(blocks(V)), dim3(256), 0, s, hist, present, flags, V, val, off, head, tail,
                        R, st);
-    // The component tree takes every call that it can: not a resumption, and
-    // not one stopped after so few steps that the step loop ends first.
-    bool tree = n_pore > 0 && !big && !resume_cs && !(opts && opts->max_steps > 0 && opts->max_steps < kTreeMinSteps);
+    // The component tree takes every call that it can (a resumption it cannot) where
+    // it is expected to take less time.
+    bool tree = !big && !resume_cs && tree_pays(d, n_pore, R, h_st->largest, opts ? opts->max_steps : 0);
     TreeArgs ta{};
     std::optional<TreeUse> tree_use;
     if (tree) {
@@ -2192,7 +2230,7 @@ hipError_t job_setup_ranks(const JobBufs& j, LoopState* st, const uint8_t* image
     uint32_t* flags = j.hist + 2 * V;
     hipLaunchKernelGGL(k_hist, dim3(std::min<int64_t>(blocks(n), kHistBlocks)), dim3(256), 0, s, j.key, n,
                        (uint32_t)(V - 1), j.hist, st);
-    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, j.hist, present, V);
+    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, j.hist, present, V, st);
     hipLaunchKernelGGL(k_copy_u32, dim3(blocks(V)), dim3(256), 0, s, present, flags, V);
     if ((e = launch_scan_u32(j.hist, V, j.partials, j.scan_total, s)) != hipSuccess) return e;
     if ((e = launch_scan_u32(present, V, j.partials, &st->R, s)) != hipSuccess) return e;
@@ -2473,7 +2511,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
                            (uint32_t)(V - 1), hist, st + j);
     }
     if ((rc = join()) != IBIP_OK) return rc;
-    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, hist, present, V);
+    hipLaunchKernelGGL(k_present, dim3(blocks(V)), dim3(256), 0, s, hist, present, V, all);
     hipLaunchKernelGGL(k_copy_u32, dim3(blocks(V)), dim3(256), 0, s, present, flags, V);
     if ((rc = hip_check(ctx, launch_scan_u32(hist, V, partials, &all->n_pore, s), "scan")) != IBIP_OK) return rc;
     if ((rc = hip_check(ctx, launch_scan_u32(present, V, partials, &all->R, s), "scan")) != IBIP_OK) return rc;

@@ -194,8 +194,13 @@ inline void tree_carve(TreeArgs& a, uint32_t* w) {
     while ((a.R >> levels) != 0) levels++;
     a.kb = 32 - levels;
 }
-// Calls stopped after fewer steps run the step loop.
+// Jobs of a batch or the server stopped after fewer steps run the step loop.
 constexpr int64_t kTreeMinSteps = 1024;
+// Whether an invasion is expected to take less time by the tree than by the step loop
+// (largest: the voxels of the most frequent rank; max_steps 0: no limit).
+bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps);
+double loop_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R, int64_t max_steps);
+double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R);
 // Levels of at most this many voxels are searched in one workgroup.
 constexpr uint32_t kTreeSmall = 2048;
 

@@ -183,3 +183,95 @@ def test_thin_images(dev, shape):
     T = [25, 9, 4, 1]
     m, rm = ibip.opening_drainage(_put(dev, img), _put(dev, inl), T), oracle.mio(img, inl, np.array(T, np.uint32))
     assert np.array_equal(m["mio_r2"].cpu().numpy().view(np.uint32), rm["mio_r2"])
+
+
+def _beside(a, b):
+    """Two images side by side along x or y, a wall of solid between them, and
+    inlets: the first face of `a` along that axis, of `b` along the last axis."""
+    axis = 1 if a.shape[0] == 1 else 0
+    wall = np.zeros([1 if i == axis else n for i, n in enumerate(a.shape)], np.uint8)
+    return (np.concatenate([a, wall, b], axis=axis),
+            np.concatenate([synth.face_mask(a.shape, axis, 0), wall, synth.face_mask(b.shape, 2, 0)], axis=axis))
+
+
+def _serpentine(n):
+    """One channel of width 1 that runs through n x n pixels, from y = 1, z = 0."""
+    img = np.zeros((1, n, n), np.uint8)
+    img[0, 1::2] = 1
+    for i, y in enumerate(range(2, n, 2)):
+        img[0, y, n - 1 if i % 2 == 0 else 0] = 1
+    return img
+
+
+def _comb(n, depth):
+    """A corridor of width 1 with a dead-end chamber of width 3 every six pixels."""
+    img = np.zeros((1, depth + 8, n), np.uint8)
+    img[0, 1] = 1
+    for x in range(2, n - 4, 6):
+        img[0, 2:4, x + 1] = 1
+        img[0, 4:4 + depth, x:x + 3] = 1
+    return img
+
+
+def _form(name):
+    rng = np.random.default_rng(11)
+    if name == "serpentine":  # as many rounds of one level as it has pixels
+        return _beside(_serpentine(161), synth.blurred_noise((1, 700, 161), 2.0, 0.6, 3))
+    if name == "long serpentine":  # more steps than a quarter of the pore voxels
+        return _beside(_serpentine(401), synth.blurred_noise((1, 160, 401), 2.0, 0.6, 3))
+    if name == "comb":  # components entered one by one in the rounds of one level
+        return _beside(_comb(2000, 9), synth.blurred_noise((1, 90, 2000), 2.0, 0.6, 4))
+    if name == "salt":  # levels of many voxels, long searches
+        return _beside((rng.random((48, 60, 62)) < 0.62).astype(np.uint8),
+                       synth.blurred_noise((90, 60, 62), 2.0, 0.6, 5))
+    if name == "isolated":  # more peaks than an eighth of the pore voxels
+        img = np.zeros((80, 80, 100), np.uint8)
+        img[::2, ::2, ::2] = 1
+        img[0] = 1
+        return _beside(img, synth.blurred_noise((60, 80, 100), 2.0, 0.6, 6))
+    if name == "wide levels":
+        img = synth.blurred_noise((120, 130, 140), 3.0, 0.6, 3)
+    else:
+        img = synth.overlapping_spheres((130, 110, 100), r2=40, porosity=0.5, seed=2)
+    return img, synth.face_mask(img.shape, 2, 0)
+
+
+# (gives up: the tree starts, runs out of room for peaks or for steps, and the step
+# loop takes over)
+@pytest.mark.parametrize("name, gives_up", [("serpentine", False), ("long serpentine", True), ("comb", False),
+                                            ("salt", False), ("isolated", True), ("wide levels", False),
+                                            ("grains", False)])
+def test_forms_of_the_tree(dev, name, gives_up):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img, inl = _form(name)
+    ref = oracle.invade(img, inl)
+    r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl)))
+    assert (loops > 0) == gives_up
+    _same(r, ref)
+    K = ref["K"]
+    for lim in (K - 1, K, 10 ** 9):
+        r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl), max_steps=lim))
+        if lim > K or K > 3000:  # (below, the loop ends sooner)
+            assert (loops > 0) == gives_up
+        _same(r, oracle.invade(img, inl, max_steps=lim))
+
+
+# small images, step limits that come before the tree would be done, and images of
+# one rank, or of one rank for almost all of them
+@pytest.mark.parametrize("name, limit", [("small", 0), ("small plane", 0), ("limit", 1023), ("limit", 1024),
+                                         ("limit", 6000), ("plates", 0), ("salt", 0)])
+def test_calls_that_the_step_loop_does_sooner(dev, name, limit):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = {"small": lambda: synth.blurred_noise((24, 30, 28), 2.0, 0.6, 1),
+           "small plane": lambda: synth.blurred_noise((1, 90, 88), 4.0, 0.6, 2),
+           "limit": lambda: synth.blurred_noise((180, 180, 180), 4.0, 0.6, 3),
+           "plates": lambda: _plates((120, 90, 40), 2),
+           "salt": lambda: (np.random.default_rng(3).random((60, 70, 80)) < 0.6).astype(np.uint8)}[name]()
+    inl = synth.face_mask(img.shape, 2, 0)
+    r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl), max_steps=limit))
+    assert loops > 0
+    _same(r, oracle.invade(img, inl, max_steps=limit))
