@@ -1769,8 +1769,10 @@ double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R) {
 // 18.9 ms by steps and 46 by the tree; its plane 700^2 (87 %) 11.2 and 21.0; 200^3 at
 // porosity 0.7 (88 %) 19.1 and 18.6; planes at 0.7 (76 %) 8.2 and 6.7; 200^3 blurred by
 // 0.7 voxels (76 %) 36.5 and 19.3.
+bool tree_crowded(int64_t n_pore, uint32_t largest) { return 32 * (int64_t)largest > 27 * n_pore; }
+
 bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps) {
-    return n_pore > 0 && 32 * (int64_t)largest <= 27 * n_pore &&
+    return n_pore > 0 && !tree_crowded(n_pore, largest) &&
            loop_ms_expected(d, n_pore, R, max_steps) > tree_ms_expected(d, n_pore, R);
 }
 
@@ -2427,9 +2429,9 @@ static __global__ __launch_bounds__(256) void k_crop(const int32_t* __restrict__
     if (centre_step) centre_step[v] = (int32_t)step_c[c];
 }
 
-// One group. Jobs whose results it cannot give (too many ranks or peaks for
-// the tree) are left in `alone`.
-static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g, std::vector<int32_t>& alone) {
+// One group. *done unless the tree cannot take it (too many ranks, peaks or steps,
+// one rank for almost all of it, no room for the scratch).
+static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g, bool* done) {
     hipStream_t s = ctx->stream;
     const int32_t m = (int32_t)g.job.size();
     const int S = kBatchStreams;
@@ -2454,7 +2456,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     const size_t st_bytes = sizeof(LoopState) * ((size_t)m + 1), off_bytes = sizeof(uint32_t) * (kMaxRanks + 2);
     uint8_t* h = (uint8_t*)pinned(ctx, std::max<size_t>(4096, align256(st_bytes) + align256(off_bytes) +
                                                                   tree_head_bytes((uint32_t)m)));
-    if (!base || !h) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
+    if (!base || !h) return IBIP_OK;
     size_t wi = 0;
     auto take = [&]() {
         uint32_t* p = (uint32_t*)base;
@@ -2519,10 +2521,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
         return rc;
     if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
     const uint32_t R = h_st[m].R, n_pore = h_st[m].n_pore;
-    if (R == 0 || R > (uint32_t)kMaxRanks) {
-        alone.insert(alone.end(), g.job.begin(), g.job.end());
-        return IBIP_OK;
-    }
+    if (R == 0 || R > (uint32_t)kMaxRanks || tree_crowded(n_pore, h_st[m].largest)) return IBIP_OK;
     // common ranks, the common key, the sorted list
     hipLaunchKernelGGL(k_rank_tables, dim3(blocks(V)), dim3(256), 0, s, hist, present, flags, V, val, off, head, tail,
                        (uint32_t)kMaxRanks, all);
@@ -2553,7 +2552,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     const size_t pore_bytes = align256(4 * ((size_t)n_pore + 1));
     TreeUse tree_use(ctx);
     uint8_t* tb = (uint8_t*)ensure(ctx, B_TREE, 3 * pore_bytes + 4 * tree_words(ta));
-    if (!tb) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
+    if (!tb) return IBIP_OK;
     uint32_t* list = (uint32_t*)tb;
     ta.list = list;
     ta.gu = (uint32_t*)(tb + pore_bytes);
@@ -2588,10 +2587,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
         if ((rc = hip_check(ctx, launch_tree_more(ta, *h_ctl, h_off, seq_c, s), "tree")) != IBIP_OK) return rc;
     }
     if (tm.on) ctx->timing.loop_kernel_ms += tm.ms(3, 4);
-    if (h_ctl->abort) {
-        alone.insert(alone.end(), g.job.begin(), g.job.end());
-        return IBIP_OK;
-    }
+    if (h_ctl->abort) return IBIP_OK;
     // insertion, in each image's part of the common array, and its outputs
     std::vector<size_t> cnt_at(m, 0);
     size_t cnt_words = 64;
@@ -2605,7 +2601,7 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
         cnt_words += 2 * (size_t)K + (count_copies(K, n) > 1 ? (size_t)kCntCopies * K : 0) + K / 1000 + 64;
     }
     uint32_t* cnt = (uint32_t*)ensure(ctx, B_TMP2, sizeof(uint32_t) * cnt_words);
-    if (!cnt) return fail(ctx, IBIP_ENOMEM, "invade_batch: scratch allocation failed");
+    if (!cnt) return IBIP_OK;
     if ((rc = fork()) != IBIP_OK) return rc;
     for (int32_t j = 0; j < m; j++) {
         ibip_job& jb = jobs[g.job[j]];
@@ -2641,13 +2637,14 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
         if ((rc = hip_check(ctx, hipGetLastError(), "batch post")) != IBIP_OK) return rc;
     }
     if ((rc = join()) != IBIP_OK) return rc;
+    *done = true;
     return hip_check(ctx, hipStreamSynchronize(s), "sync");
 }
 
 // Jobs that the batched paths leave, one after another on the context's
 // stream with the batch's readings (none); that replaces the context's
 // per-step arrays, so ibip_get_steps then refers to no call.
-static void run_alone(ibip_ctx* ctx, ibip_job* jobs, const std::vector<int32_t>& alone, ibip_status& first) {
+static void run_alone(ibip_ctx* ctx, ibip_job* jobs, const std::vector<int32_t>& alone) {
     hipStream_t s = ctx->stream;
     const uint32_t readings = ctx->readings;
     ctx->readings = 0;
@@ -2666,18 +2663,19 @@ static void run_alone(ibip_ctx* ctx, ibip_job* jobs, const std::vector<int32_t>&
         if (r == IBIP_OK) r = hip_check(ctx, hipStreamSynchronize(s), "sync");
         jb.status = r;
         jb.n_steps = r == IBIP_OK ? K : 0;
-        if (r != IBIP_OK && first == IBIP_OK) first = r;
     }
     ctx->readings = readings;
     ctx->have_steps = false;
 }
 
-// The step loops of a batch whose jobs all stop after few steps.
-static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
+// The step loops of the jobs `which`, side by side. Jobs that they cannot take are
+// left in `alone`.
+static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, const std::vector<int32_t>& which,
+                                   std::vector<int32_t>& left_alone) {
     hipStream_t s0 = ctx->stream;
+    const int32_t nj = (int32_t)which.size();
     // largest jobs first: their loops are the longest
-    std::vector<int32_t> order(nj);
-    for (int32_t i = 0; i < nj; i++) order[i] = i;
+    std::vector<int32_t> order = which;
     std::stable_sort(order.begin(), order.end(),
                      [&](int32_t a, int32_t b) { return nvox(jobs[a].dims) > nvox(jobs[b].dims); });
     std::vector<size_t> offs(nj);
@@ -2821,10 +2819,6 @@ static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
         (rc = hip_check(ctx, hipEventCreateWithFlags(&ctx->copy_ev, hipEventDisableTiming), "event")) != IBIP_OK)
         return rc;
     if ((rc = hip_check(ctx, hipEventRecord(ctx->copy_ev, s0), "event")) != IBIP_OK) return rc;
-    ibip_status first = IBIP_OK;
-    // jobs with more distinct distance values than a job's rank tables hold
-    // (their loop stopped before its first step): run alone afterwards
-    std::vector<int32_t> alone;
     auto post = [&](int32_t q, uint32_t k, uint32_t err) -> ibip_status {
         ibip_job& jb = jobs[order[q]];
         jb.status = IBIP_OK;
@@ -2832,14 +2826,10 @@ static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
         if (err == 2) jb.status = IBIP_ENOSOLID;
         else if (err == 3) jb.status = IBIP_ECAPACITY;
         else if (err) jb.status = IBIP_EDEVICE;
-        if (err == 3) {
-            alone.push_back(q);
-            return IBIP_OK;
-        }
-        if (jb.status != IBIP_OK) {
-            if (first == IBIP_OK) first = (ibip_status)jb.status;
-            return IBIP_OK;
-        }
+        // more distinct distance values than a job's rank tables hold: its loop
+        // stopped before the first step
+        if (err == 3) left_alone.push_back(order[q]);
+        if (jb.status != IBIP_OK) return IBIP_OK;
         const int64_t K = (int64_t)k - 1;
         jb.n_steps = K;
         return hip_check(ctx, job_post(bufs[q], states + q, jb.dims, K, jb.seq, jb.rad2, jb.M, jb.sat,
@@ -2921,40 +2911,47 @@ static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
         if ((rc = hip_check(ctx, hipEventRecord(ctx->bev[i], ctx->bstream[i]), "event")) != IBIP_OK) return rc;
         if ((rc = hip_check(ctx, hipStreamWaitEvent(s0, ctx->bev[i], 0), "wait")) != IBIP_OK) return rc;
     }
-    if ((rc = hip_check(ctx, hipStreamSynchronize(s0), "sync")) != IBIP_OK) return rc;
-    // the jobs with too many ranks for the batch's tables
-    for (int32_t& q : alone) q = order[q];
-    if (!alone.empty()) run_alone(ctx, jobs, alone, first);
-    if (first != IBIP_OK) return fail(ctx, first, "invade_batch: at least one job failed (see its status)");
-    return IBIP_OK;
+    return hip_check(ctx, hipStreamSynchronize(s0), "sync");
 }
 
 ibip_status run_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
     bool few = true;
     for (int32_t i = 0; i < nj; i++) few = few && jobs[i].max_steps > 0 && jobs[i].max_steps < kTreeMinSteps;
-    if (few) return run_batch_loops(ctx, jobs, nj);
     // largest first, so that a group's images are of like size
-    std::vector<int32_t> order(nj), alone;
+    std::vector<int32_t> order(nj), loops, alone;
     for (int32_t i = 0; i < nj; i++) order[i] = i;
     std::stable_sort(order.begin(), order.end(),
                      [&](int32_t a, int32_t b) { return nvox(jobs[a].dims) > nvox(jobs[b].dims); });
-    Group g;
     ibip_status rc;
-    for (int32_t q : order) {
-        if (!g.job.empty() && g.voxels_with(jobs[q].dims) > kGroupVoxels) {
-            if ((rc = run_batch_group(ctx, jobs, g, alone)) != IBIP_OK) return rc;
+    if (few) {
+        loops = order;
+    } else {
+        Group g;
+        auto run = [&]() -> ibip_status {
+            bool done = false;
+            ibip_status r = run_batch_group(ctx, jobs, g, &done);
+            // A group that the tree cannot take runs its step loops side by side: 20
+            // planes 500 x 500 33 ms so, 361 one call after another.
+            if (r == IBIP_OK && !done) loops.insert(loops.end(), g.job.begin(), g.job.end());
             g = Group{};
+            return r;
+        };
+        for (int32_t q : order) {
+            if (!g.job.empty() && g.voxels_with(jobs[q].dims) > kGroupVoxels && (rc = run()) != IBIP_OK) return rc;
+            if (g.voxels_with(jobs[q].dims) > kGroupVoxels) alone.push_back(q);
+            else g.add(q, jobs[q].dims);
         }
-        if (g.voxels_with(jobs[q].dims) > kGroupVoxels) alone.push_back(q);
-        else g.add(q, jobs[q].dims);
+        if (!g.job.empty() && (rc = run()) != IBIP_OK) return rc;
     }
-    if (!g.job.empty() && (rc = run_batch_group(ctx, jobs, g, alone)) != IBIP_OK) return rc;
-    ibip_status first = IBIP_OK;
-    if (!alone.empty()) run_alone(ctx, jobs, alone, first);
-    first = IBIP_OK;
-    for (int32_t q : order)
-        if (jobs[q].status != IBIP_OK && first == IBIP_OK) first = (ibip_status)jobs[q].status;
-    if (first != IBIP_OK) return fail(ctx, first, "invade_batch: at least one job failed (see its status)");
+    if (!loops.empty()) {
+        rc = run_batch_loops(ctx, jobs, loops, alone);
+        if (rc == IBIP_ENOMEM) alone.insert(alone.end(), loops.begin(), loops.end());  // (none of them has started)
+        else if (rc != IBIP_OK) return rc;
+    }
+    if (!alone.empty()) run_alone(ctx, jobs, alone);
+    for (int32_t q = 0; q < nj; q++)
+        if (jobs[q].status != IBIP_OK)
+            return fail(ctx, (ibip_status)jobs[q].status, "invade_batch: at least one job failed (see its status)");
     return IBIP_OK;
 }
 

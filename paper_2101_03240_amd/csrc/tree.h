@@ -199,6 +199,7 @@ constexpr int64_t kTreeMinSteps = 1024;
 // Whether an invasion is expected to take less time by the tree than by the step loop
 // (largest: the voxels of the most frequent rank; max_steps 0: no limit).
 bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps);
+bool tree_crowded(int64_t n_pore, uint32_t largest);  // one rank holds almost all of it
 double loop_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R, int64_t max_steps);
 double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R);
 // Levels of at most this many voxels are searched in one workgroup.

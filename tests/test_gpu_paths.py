@@ -275,3 +275,75 @@ def test_calls_that_the_step_loop_does_sooner(dev, name, limit):
     r, loops = _loops(lambda: ibip.invade(_put(dev, img), _put(dev, inl), max_steps=limit))
     assert loops > 0
     _same(r, oracle.invade(img, inl, max_steps=limit))
+
+
+def _corner(shape):
+    """One solid voxel, in the corner: as many ranks as its box has distances."""
+    img = np.ones(shape, np.uint8)
+    img[0, 0, 0] = 0
+    return img
+
+
+def _batch_form(name):
+    noise = [synth.blurred_noise((30 + 3 * i, 40, 50 - 2 * i), 2.5, 0.6, i) for i in range(5)]
+    if name == "isolated":  # more peaks than the group has room for
+        img = np.zeros((90, 90, 100), np.uint8)
+        img[::2, ::2, ::2] = 1
+        img[0] = 1
+        return noise + [img]
+    if name == "ranks":  # each has fewer than 8,192, all together more
+        return [_corner((1, 120, 120)), _corner((24, 24, 90))]
+    if name == "plates":
+        return [_plates((60, 50, 40), 1), _plates((40, 30, 50), 2), _plates((1, 70, 60), 1)]
+    return noise
+
+
+# (which the tree gives up or does not take: one launch runs all step loops)
+@pytest.mark.parametrize("name, gives_up", [("noise", False), ("isolated", True), ("ranks", True), ("plates", True)])
+def test_batches_that_give_up_stay_batches(dev, name, gives_up):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    imgs = _batch_form(name)
+    inls = [synth.face_mask(i.shape, 2, 0) for i in imgs]
+    out, loops = _loops(lambda: ibip.invade_batch([_put(dev, i) for i in imgs], [_put(dev, i) for i in inls], sat=True))
+    assert loops == (1 if gives_up else 0)
+    for img, inl, b in zip(imgs, inls, out):
+        ref = oracle.invade(img, inl)
+        assert b["status"] == 0
+        _same(b, ref)
+        n = np.bincount(ref["seq"][ref["seq"] > 0], minlength=ref["K"] + 1)[1:]
+        assert np.array_equal(b["sat"].cpu().numpy(), np.cumsum(n) / float((img != 0).sum()))
+
+
+def test_a_batch_without_room_for_its_tree(dev):
+    import torch
+
+    import paper_2101_03240_amd as ibip
+
+    imgs = [synth.blurred_noise_device((128, 128, 128), 3.0, 0.6, i, dev) for i in range(4)]
+    for i in imgs:
+        i[-1, -1, -1] = 0
+    inls = [_put(dev, synth.face_mask((128, 128, 128), 0, 0))] * 4
+
+    def work():
+        ibip.invade_batch(imgs, inls, max_steps=9)  # the step loops' scratch
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        keep = [torch.empty(4 * imgs[0].numel(), dtype=torch.uint8, device=dev) for _ in range(20)]
+        fill = _fill(dev, 64 << 20)  # (the tree takes 250 MB)
+        del keep
+        a = _loops(lambda: ibip.invade_batch(imgs, inls))
+        del fill
+        torch.cuda.empty_cache()
+        return a, _loops(lambda: ibip.invade_batch(imgs, inls))
+
+    try:
+        (a, la), (b, lb) = _in_thread(work)
+    finally:
+        torch.cuda.empty_cache()
+    assert (la, lb) == (1, 0)
+    for x, y in zip(a, b):
+        assert x["K"] == y["K"]
+        for k in ("centre_step", "seq", "rad2", "M"):
+            assert torch.equal(x[k], y[k]), k
