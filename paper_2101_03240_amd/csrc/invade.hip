@@ -2398,23 +2398,96 @@ void fill_loop_args(void* out, const JobBufs& j, LoopState* st, ibip_dims d, uin
 // ---------------------------------------------------------------------------
 // Voxels of one common array; a larger batch is taken in several groups.
 constexpr int64_t kGroupVoxels = (int64_t)1 << 29;
+// What a group costs besides its voxels, in voxels of the common array, solid ones
+// that pad an image to the largest rows and planes of its group included. A group's
+// levels are a chain of their own, 2 to 4 ms, for which a hundred million such voxels
+// are passed over (512^3 with 48 images of 32^3: 58.5 ms for the large one alone, 71.6
+// together with 403 M voxels of padding), but they take 28 B of scratch each, 11 GB
+// there: 2^25 is about 1 GB.
+constexpr int64_t kGroupCost = (int64_t)1 << 25;
 
 struct Group {
     std::vector<int32_t> job;  // indices into the caller's jobs
-    int32_t Y = 0, Z = 0;      // of the common array: rows and planes of the largest, rounded up to 8
+    int32_t Y = 0, Z = 0;      // of the common array: rows and planes of the largest
     int64_t planes = 0;
-    static int32_t up8(int32_t v) { return (v + 7) / 8 * 8; }
-    int64_t voxels_with(ibip_dims d) const {
-        return (planes + d.X) * std::max(Y, up8(d.Y)) * (int64_t)std::max(Z, up8(d.Z));
-    }
     void add(int32_t q, ibip_dims d) {
         job.push_back(q);
         planes += d.X;
-        Y = std::max(Y, up8(d.Y));
-        Z = std::max(Z, up8(d.Z));
+        Y = std::max(Y, d.Y);
+        Z = std::max(Z, d.Z);
+    }
+    // a multiple of 8 voxels to a plane, so that each image's part is aligned: rows
+    // of a multiple of 8 (which wide loads take too) or, if that pads less, Y of 8 rows
+    // (without the jobs)
+    Group rounded() const {
+        Group r;
+        r.planes = planes;
+        r.Y = Y;
+        r.Z = Z;
+        const int32_t z8 = (Z + 7) / 8 * 8, y8 = (Y + 7) / 8 * 8;
+        if ((int64_t)y8 * Z < (int64_t)Y * z8) r.Y = y8;
+        else r.Z = z8;
+        return r;
     }
     int64_t voxels() const { return planes * Y * (int64_t)Z; }
 };
+
+// The jobs in groups of images of like rows and planes: in the order of the shape
+// of their planes, then of the size of these, cut so that the groups' costs add up to
+// the least. A job too large for a group gets one of its own.
+static std::vector<Group> batch_groups(const ibip_job* jobs, int32_t nj) {
+    struct Item {
+        int32_t q;
+        int shape;  // log2(Y / Z), rounded
+        int64_t plane;
+    };
+    std::vector<Item> it(nj);
+    for (int32_t q = 0; q < nj; q++) {
+        const ibip_dims d = jobs[q].dims;
+        it[q] = Item{q, (int)std::lround(std::log2((double)d.Y / d.Z)), (int64_t)d.Y * d.Z};
+    }
+    std::stable_sort(it.begin(), it.end(), [](const Item& a, const Item& b) {
+        return a.shape != b.shape ? a.shape < b.shape : a.plane > b.plane;
+    });
+    // in units of one job, or of a few where there are thousands
+    const int32_t step = (nj + 511) / 512, nu = (nj + step - 1) / step;
+    auto add = [&](Group& g, int32_t u, int64_t* held) {
+        for (int32_t k = u * step; k < std::min(nj, (u + 1) * step); k++) {
+            g.add(it[k].q, jobs[it[k].q].dims);
+            *held += nvox(jobs[it[k].q].dims);
+        }
+    };
+    // cost[u]: of the first u units; cut[u]: where their last group begins. A group
+    // of several has no more padding than voxels, or than kGroupCost.
+    std::vector<int64_t> cost(nu + 1, INT64_MAX);
+    std::vector<int32_t> cut(nu + 1, 0);
+    cost[0] = 0;
+    for (int32_t i = 0; i < nu; i++) {
+        Group g;
+        int64_t held = 0;
+        for (int32_t j = i; j < nu; j++) {
+            add(g, j, &held);
+            const Group r = g.rounded();
+            const int64_t n = r.voxels();
+            if (j > i && (n > kGroupVoxels || n - held > std::max(held, kGroupCost))) break;
+            if (cost[i] + kGroupCost + n < cost[j + 1]) {
+                cost[j + 1] = cost[i] + kGroupCost + n;
+                cut[j + 1] = i;
+            }
+        }
+    }
+    std::vector<Group> out;
+    for (int32_t e = nu; e > 0; e = cut[e]) {
+        Group g;
+        int64_t held = 0;
+        for (int32_t j = cut[e]; j < e; j++) add(g, j, &held);
+        const Group r = g.rounded();
+        g.Y = r.Y;
+        g.Z = r.Z;
+        out.push_back(std::move(g));
+    }
+    return out;
+}
 
 // The image's part of the common array (its voxels, CY x CZ planes) to its own
 // layout: seq (still INT_MAX where nothing was painted) and, if wanted, the steps.
@@ -2917,31 +2990,22 @@ static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, const std::vec
 ibip_status run_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t nj) {
     bool few = true;
     for (int32_t i = 0; i < nj; i++) few = few && jobs[i].max_steps > 0 && jobs[i].max_steps < kTreeMinSteps;
-    // largest first, so that a group's images are of like size
-    std::vector<int32_t> order(nj), loops, alone;
-    for (int32_t i = 0; i < nj; i++) order[i] = i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return nvox(jobs[a].dims) > nvox(jobs[b].dims); });
+    std::vector<int32_t> loops, alone;
     ibip_status rc;
     if (few) {
-        loops = order;
+        for (int32_t i = 0; i < nj; i++) loops.push_back(i);
     } else {
-        Group g;
-        auto run = [&]() -> ibip_status {
+        for (const Group& g : batch_groups(jobs, nj)) {
+            if (g.voxels() > kGroupVoxels) {  // (one job)
+                alone.insert(alone.end(), g.job.begin(), g.job.end());
+                continue;
+            }
             bool done = false;
-            ibip_status r = run_batch_group(ctx, jobs, g, &done);
+            if ((rc = run_batch_group(ctx, jobs, g, &done)) != IBIP_OK) return rc;
             // A group that the tree cannot take runs its step loops side by side: 20
             // planes 500 x 500 33 ms so, 361 one call after another.
-            if (r == IBIP_OK && !done) loops.insert(loops.end(), g.job.begin(), g.job.end());
-            g = Group{};
-            return r;
-        };
-        for (int32_t q : order) {
-            if (!g.job.empty() && g.voxels_with(jobs[q].dims) > kGroupVoxels && (rc = run()) != IBIP_OK) return rc;
-            if (g.voxels_with(jobs[q].dims) > kGroupVoxels) alone.push_back(q);
-            else g.add(q, jobs[q].dims);
+            if (!done) loops.insert(loops.end(), g.job.begin(), g.job.end());
         }
-        if (!g.job.empty() && (rc = run()) != IBIP_OK) return rc;
     }
     if (!loops.empty()) {
         rc = run_batch_loops(ctx, jobs, loops, alone);

@@ -347,3 +347,41 @@ def test_a_batch_without_room_for_its_tree(dev):
         assert x["K"] == y["K"]
         for k in ("centre_step", "seq", "rad2", "M"):
             assert torch.equal(x[k], y[k]), k
+
+
+def _scratch():
+    """Bytes of scratch that this thread's context holds."""
+    import torch
+
+    import paper_2101_03240_amd as ibip
+    return ibip.load_library().ibip_ctx_scratch_bytes(ibip._context(torch.device("cuda", torch.cuda.current_device())))
+
+
+# images of other rows, planes and orientations than their neighbours': groups of
+# their own instead of up to 256 times their voxels of padding, each in its layout
+@pytest.mark.parametrize("shapes", [[(8, 400, 400), (400, 400, 8), (400, 8, 400)],
+                                    [(1, 300, 310), (300, 1, 310), (310, 300, 1), (1, 7, 9), (61, 1, 1), (1, 1, 53)],
+                                    [(200, 200, 200)] + [(20, 21, 22)] * 20,
+                                    [(13, 33, 35), (35, 13, 33), (33, 35, 13), (40, 9, 200), (200, 40, 9)]])
+def test_batches_of_uneven_shapes(dev, shapes):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    rng = np.random.default_rng(5)
+    imgs = [synth.blurred_noise(s, 1.5, 0.65, i) if min(s) > 5 else (rng.random(s) < 0.85).astype(np.uint8)
+            for i, s in enumerate(shapes)]
+    inls = [(rng.random(s) < 0.01).astype(np.uint8) for s in shapes]
+    for i in imgs:
+        i[-1, -1, -1] = 0
+
+    def work():
+        return ibip.invade_batch([_put(dev, i) for i in imgs], [_put(dev, i) for i in inls], sat=True), _scratch()
+
+    out, scratch = _in_thread(work)
+    assert scratch < 200 * sum(i.size for i in imgs) + (1100 << 20)
+    for img, inl, b in zip(imgs, inls, out):
+        ref = oracle.invade(img, inl)
+        assert b["status"] == 0
+        _same(b, ref)
+        n = np.bincount(ref["seq"][ref["seq"] > 0], minlength=ref["K"] + 1)[1:]
+        assert np.array_equal(b["sat"].cpu().numpy(), np.cumsum(n) / float((img != 0).sum()))
