@@ -285,16 +285,16 @@ def _corner(shape):
 
 
 def _batch_form(name):
-    noise = [synth.blurred_noise((30 + 3 * i, 40, 50 - 2 * i), 2.5, 0.6, i) for i in range(5)]
+    noise = [synth.blurred_noise((90 + 3 * i, 80, 90 - 2 * i), 2.5, 0.6, i) for i in range(5)]
     if name == "isolated":  # more peaks than the group has room for
-        img = np.zeros((90, 90, 100), np.uint8)
+        img = np.zeros((160, 120, 120), np.uint8)
         img[::2, ::2, ::2] = 1
         img[0] = 1
-        return noise + [img]
+        return noise[:2] + [img]
     if name == "ranks":  # each has fewer than 8,192, all together more
-        return [_corner((1, 120, 120)), _corner((24, 24, 90))]
+        return noise + [_corner((1, 120, 120)), _corner((24, 24, 90))]
     if name == "plates":
-        return [_plates((60, 50, 40), 1), _plates((40, 30, 50), 2), _plates((1, 70, 60), 1)]
+        return [_plates((160, 90, 80), 1), _plates((140, 80, 90), 2), _plates((1, 70, 60), 1)]
     return noise
 
 
@@ -360,9 +360,10 @@ def _scratch():
 # images of other rows, planes and orientations than their neighbours': groups of
 # their own instead of up to 256 times their voxels of padding, each in its layout
 @pytest.mark.parametrize("shapes", [[(8, 400, 400), (400, 400, 8), (400, 8, 400)],
-                                    [(1, 300, 310), (300, 1, 310), (310, 300, 1), (1, 7, 9), (61, 1, 1), (1, 1, 53)],
+                                    [(1, 900, 910), (900, 1, 910), (910, 900, 1), (1, 7, 9), (61, 1, 1), (1, 1, 53)],
                                     [(200, 200, 200)] + [(20, 21, 22)] * 20,
-                                    [(13, 33, 35), (35, 13, 33), (33, 35, 13), (40, 9, 200), (200, 40, 9)]])
+                                    [(40, 100, 105), (105, 40, 100), (100, 105, 40), (120, 27, 600), (600, 120, 27)],
+                                    [(13, 33, 35), (35, 13, 33), (33, 35, 13)]])
 def test_batches_of_uneven_shapes(dev, shapes):
     import oracle
     import paper_2101_03240_amd as ibip
