@@ -265,12 +265,15 @@ ibip_status ibip_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t n);
  * invasion loop of Section 2.1). Jobs are submitted at any time; a worker
  * thread admits a pending job as soon as an execution slot is free and the
  * job's scratch (about 26 bytes per voxel) fits in the server's HBM pool, and
- * runs it on its slot's stream: setup, the component tree (whose own scratch,
- * about 45 bytes per pore voxel, comes from the pool as well; without room for
- * it, and for jobs stopped after fewer than 1,024 steps, the step loop in one
- * workgroup), sphere insertion and finalisation. Admitted jobs overlap on the
- * device. A job behind one that does not fit yet may start first (within
- * `lookahead` places), so a huge job does not block the queue.
+ * runs it on its slot's stream: setup, then the component tree or, where that is
+ * expected to end sooner (small images, jobs stopped after few steps, images of
+ * almost one rank), the step loop in one workgroup; sphere insertion and
+ * finalisation. The tree's own scratch comes from the pool as well: 51 to 54 bytes
+ * per pore voxel, and at least 97 per voxel for images of up to a million voxels, 12
+ * to 17 for larger ones; without room for it when the job's pore voxels are known, and where
+ * it gives up, the step loop runs. Admitted jobs overlap on the device. A job
+ * behind one that does not fit yet may start first (within `lookahead` places), so
+ * a huge job does not block the queue.
  * A job's results are those of ibip_invade on the same inputs.
  * The job's input buffers must hold their data when it is submitted, and its
  * output buffers must stay valid until ibip_server_wait returns for it.

@@ -1776,6 +1776,11 @@ bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_
            loop_ms_expected(d, n_pore, R, max_steps) > tree_ms_expected(d, n_pore, R);
 }
 
+bool sizes_by_loop(ibip_dims d, int64_t max_steps) {
+    const int64_t n = (int64_t)(kGuessPore * (double)nvox(d));
+    return loop_ms_expected(d, n, kGuessRanks, max_steps) < tree_ms_expected(d, n, kGuessRanks);
+}
+
 ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlets, ibip_dims d,
                        const ibip_invade_opts* opts, int32_t* seq, uint32_t* rad2, int32_t* centre_step,
                        int64_t* n_steps, const int32_t* resume_cs, int64_t k_done) {
@@ -2988,23 +2993,20 @@ static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, const std::vec
 }
 
 // Whether the step loops of a batch, side by side, are expected to end before the
-// groups' trees. Nothing is known of the images yet but their sizes: taken as 60 % pore
-// with 80 ranks. Each job's setup and results take 0.135 ms with a loop and 0.08
+// groups' trees, by their sizes alone (see sizes_by_loop). Each job's setup and results take 0.135 ms with a loop and 0.08
 // without; the loops share the memory (20 planes 300^2 take 2 times as long as one, 64
 // images of 64^3 3 times, of 128^3 6 times, 256 of 64^3 10 times).
 static bool batch_by_loops(const ibip_job* jobs, int32_t nj, const std::vector<Group>& groups) {
-    constexpr double kPore = 0.6;
-    constexpr uint32_t kRanks = 80;
     double longest = 0, loops = 0.135 * nj, trees = 0.08 * nj;
     for (int32_t i = 0; i < nj; i++) {
         const ibip_dims d = jobs[i].dims;
-        longest = std::max(longest, loop_ms_expected(d, (int64_t)(kPore * (double)nvox(d)), kRanks, jobs[i].max_steps));
+        longest = std::max(longest, loop_ms_expected(d, (int64_t)(kGuessPore * (double)nvox(d)), kGuessRanks, jobs[i].max_steps));
     }
     loops += longest * (1 + nj / 16.0);
     for (const Group& g : groups) {
         int64_t n = 0;
         for (int32_t q : g.job) n += nvox(jobs[q].dims);
-        trees += tree_ms_expected(jobs[g.job[0]].dims, (int64_t)(kPore * (double)n), kRanks);
+        trees += tree_ms_expected(jobs[g.job[0]].dims, (int64_t)(kGuessPore * (double)n), kGuessRanks);
     }
     return loops < trees;
 }

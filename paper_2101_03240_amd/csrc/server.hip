@@ -147,41 +147,6 @@ void launch_failed(ibip_server* S, Slot& sl, hipError_t e) {
     }
 }
 
-// Start job `t` on slot `si` (mu held). Returns false if a HIP call failed.
-bool start_job(ibip_server* S, int64_t t, int si) {
-    Job& J = S->jobs[t];
-    Slot& sl = S->slots[si];
-    const ibip_job& jb = J.job;
-    const JobBufs b = job_bufs(S, J);
-    LoopState* st = (LoopState*)sl.dev_small;
-    hipError_t e = job_setup_ranks(b, st, jb.image, jb.dims, jb.max_steps, sl.stream, edt_tiles(S->tuning));
-    if (e == hipSuccess) e = hipMemcpyAsync(sl.host_small, st, sizeof(LoopState), hipMemcpyDeviceToHost, sl.stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(sl.host_small + kSlotSmall, b.off, sizeof(uint32_t) * (kMaxRanks + 2),
-                           hipMemcpyDeviceToHost, sl.stream);
-    if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);
-    if (e != hipSuccess) {
-        launch_failed(S, sl, e);
-        return false;
-    }
-    __atomic_store_n(sl.cancel_host, 0u, __ATOMIC_RELEASE);
-    J.slot = si;
-    J.state = J_RUNNING;
-    sl.ticket = t;
-    sl.phase = P_SETUP;
-    S->stats.running++;
-    S->stats.pending--;
-    if (S->stats.running > S->stats.peak_running) S->stats.peak_running = S->stats.running;
-    return true;
-}
-
-void release_tree(ibip_server* S, Job& J) {
-    if (!J.tree_bytes) return;
-    S->pool.release(J.tree_off, J.tree_bytes);
-    S->stats.bytes_in_use -= (int64_t)J.tree_bytes;
-    J.tree_bytes = 0;
-}
-
 // The step loop of a job in one workgroup, to its first wide step or its end.
 hipError_t launch_loop(ibip_server* S, Slot& sl, const Job& J) {
     const JobBufs b = job_bufs(S, J);
@@ -193,6 +158,48 @@ hipError_t launch_loop(ibip_server* S, Slot& sl, const Job& J) {
     set_loop_cancel(sl.host_small + 512, sl.cancel_dev);
     const hipError_t e = hipMemcpyAsync(dargs, sl.host_small + 512, loop_args_bytes(), hipMemcpyHostToDevice, sl.stream);
     return e == hipSuccess ? launch_loop_jobs(dargs, 1, sl.stream) : e;
+}
+
+// Start job `t` on slot `si` (mu held). Returns false if a HIP call failed.
+bool start_job(ibip_server* S, int64_t t, int si) {
+    Job& J = S->jobs[t];
+    Slot& sl = S->slots[si];
+    const ibip_job& jb = J.job;
+    const JobBufs b = job_bufs(S, J);
+    LoopState* st = (LoopState*)sl.dev_small;
+    // A small job, or one stopped after few steps, by its size alone (see
+    // sizes_by_loop): its step loop is queued at once, without the host between
+    // (64 jobs of 48^3 36 to 40 ms so, 44 in parts, 52 to 55 by trees; of 64^3 38 in
+    // parts, 32 by trees).
+    const bool loop = sizes_by_loop(jb.dims, jb.max_steps);
+    hipError_t e = job_setup_ranks(b, st, jb.image, jb.dims, jb.max_steps, sl.stream, edt_tiles(S->tuning));
+    __atomic_store_n(sl.cancel_host, 0u, __ATOMIC_RELEASE);
+    if (loop && e == hipSuccess) e = job_setup_loop(b, jb.image, jb.inlets, jb.dims, jb.seq, sl.stream);
+    if (loop && e == hipSuccess) e = launch_loop(S, sl, J);
+    if (e == hipSuccess) e = hipMemcpyAsync(sl.host_small, st, sizeof(LoopState), hipMemcpyDeviceToHost, sl.stream);
+    if (!loop && e == hipSuccess)
+        e = hipMemcpyAsync(sl.host_small + kSlotSmall, b.off, sizeof(uint32_t) * (kMaxRanks + 2),
+                           hipMemcpyDeviceToHost, sl.stream);
+    if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);
+    if (e != hipSuccess) {
+        launch_failed(S, sl, e);
+        return false;
+    }
+    J.slot = si;
+    J.state = J_RUNNING;
+    sl.ticket = t;
+    sl.phase = loop ? P_LOOP : P_SETUP;
+    S->stats.running++;
+    S->stats.pending--;
+    if (S->stats.running > S->stats.peak_running) S->stats.peak_running = S->stats.running;
+    return true;
+}
+
+void release_tree(ibip_server* S, Job& J) {
+    if (!J.tree_bytes) return;
+    S->pool.release(J.tree_off, J.tree_bytes);
+    S->stats.bytes_in_use -= (int64_t)J.tree_bytes;
+    J.tree_bytes = 0;
 }
 
 // The slot's queued work ended (mu held through lk): queue the job's next
@@ -217,8 +224,7 @@ bool advance(ibip_server* S, int si, hipError_t* e, std::unique_lock<std::mutex>
             hs->err = !hs->solid_seen ? 2u : 3u;
             return false;
         }
-        const bool few = jb.max_steps > 0 && jb.max_steps < kTreeMinSteps;
-        if (!few && hs->n_pore > 0) {
+        if (tree_pays(jb.dims, hs->n_pore, hs->R, hs->largest, jb.max_steps)) {
             sl.tree = job_tree_args(b, *hs, h_off, jb.dims, jb.seq);
             const size_t bytes = align256(4 * tree_words(sl.tree));
             if (S->pool.alloc(bytes, &J.tree_off)) {

@@ -194,11 +194,13 @@ inline void tree_carve(TreeArgs& a, uint32_t* w) {
     while ((a.R >> levels) != 0) levels++;
     a.kb = 32 - levels;
 }
-// Jobs of a batch or the server stopped after fewer steps run the step loop.
-constexpr int64_t kTreeMinSteps = 1024;
 // Whether an invasion is expected to take less time by the tree than by the step loop
 // (largest: the voxels of the most frequent rank; max_steps 0: no limit).
 bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps);
+// The same of an image of which nothing is known yet, taken as 60 % pore with 80 ranks.
+constexpr double kGuessPore = 0.6;
+constexpr uint32_t kGuessRanks = 80;
+bool sizes_by_loop(ibip_dims d, int64_t max_steps);
 bool tree_crowded(int64_t n_pore, uint32_t largest);  // one rank holds almost all of it
 double loop_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R, int64_t max_steps);
 double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R);

@@ -386,3 +386,32 @@ def test_batches_of_uneven_shapes(dev, shapes):
         _same(b, ref)
         n = np.bincount(ref["seq"][ref["seq"] > 0], minlength=ref["K"] + 1)[1:]
         assert np.array_equal(b["sat"].cpu().numpy(), np.cumsum(n) / float((img != 0).sum()))
+
+
+# served jobs: by the step loop at once (small), by the tree, by a tree that gives up
+# (the loop takes over), by the loop after their ranks are known, and without room for
+# the tree; told by the pool's peak
+@pytest.mark.parametrize("name, room, tree", [("small", 1 << 30, False), ("wide levels", 1 << 30, True),
+                                              ("isolated", 1 << 30, True), ("long serpentine", 1 << 30, True),
+                                              ("plates", 1 << 30, False), ("wide levels", 80 << 20, False)])
+def test_served_paths(dev, name, room, tree):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    if name == "small":
+        img = synth.blurred_noise((20, 24, 26), 2.0, 0.6, 1)
+        inl = synth.face_mask(img.shape, 0, 0)
+    elif name == "plates":
+        img = _plates((160, 90, 80), 1)
+        inl = synth.face_mask(img.shape, 0, 0)
+    else:
+        img, inl = _form(name)
+    d_img, d_inl = _put(dev, img), _put(dev, inl)
+    with ibip.Server(dev, hbm_budget_bytes=room, max_inflight=2) as srv:
+        srv.wait(srv.submit(d_img, d_inl, max_steps=2))
+        loop_peak = srv.stats()["peak_bytes"]
+        b = srv.wait(srv.submit(d_img, d_inl))
+        assert (srv.stats()["peak_bytes"] > loop_peak) == tree
+        assert srv.stats()["bytes_in_use"] == 0
+    assert b["status"] == 0
+    _same(b, oracle.invade(img, inl))
