@@ -63,6 +63,7 @@ struct BasinArgs {
     int X, Y, Z;
     int nty, ntz;    // tiles along y and z
     uint32_t pcap, pall, ecap, eall;  // places of a slot's list and of all: basins, edges
+    bool whole;                       // one place for each voxel and four for its edges
 };
 
 // Sizes of the lists for an image; the scratch they take; its layout at `mem`

@@ -485,9 +485,9 @@ void basin_caps(BasinArgs& a, ibip_dims d) {
                          std::min(a.Z, Tile<true>::TZ);
     const int64_t slots = std::min<int64_t>(nt, kBasinSlots);
     const int64_t per = (nt + slots - 1) / slots * held;
-    const bool all = per * slots <= 1 << 20;  // room for whatever the image holds
-    a.pcap = (uint32_t)(all ? per : per / 8);
-    a.ecap = (uint32_t)(all ? 4 * per : per / 2);
+    a.whole = per * slots <= 1 << 20;
+    a.pcap = (uint32_t)(a.whole ? per : per / 8);
+    a.ecap = (uint32_t)(a.whole ? 4 * per : per / 2);
     a.pall = a.pcap * (uint32_t)slots;
     a.eall = a.ecap * (uint32_t)slots;
 }

@@ -336,14 +336,20 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 }  // namespace
 
 // By basins: *done unless there is no scratch (13 B a voxel, in the buffer that
-// the invasion's tree has had) or the image, of more than 2^20 voxels, has more
-// basins than an eighth of them or more edges than half (noise of single voxels;
-// blurred noise and grains have 1/60 and 1/6): those take the sweeps.
+// the invasion's tree has had) or the image, of more than about 2^20 voxels, has more
+// basins than an eighth of them or more edges than half: those take the sweeps.
+// Basins and edges per voxel, 6-connected: 0.03 to 0.05 and 0.25 to 0.41 in volumes
+// of blurred noise, 0.08 and 0.32 in noise of single voxels, 0.04 and 0.13 in planes.
+// 26-connected volumes have more than 2 edges a voxel and would always come back, so
+// they take the sweeps at once (ms, 256^3 noise of sigma 6 7.1 so, 7.9 after the basins;
+// 360^3 18.2 and 20.4); those with room for them, and planes (0.4), are as fast as ever
+// by basins (64^3 0.65, by sweeps 0.95; plane 500^2 0.32 and 1.46).
 static ibip_status reconstruct_basins(ibip_ctx* ctx, const int32_t* seq, const uint32_t* cap32, bool conn26,
                                       ibip_dims d, uint32_t* w, int* n_iter, bool* done) {
     hipStream_t s = ctx->stream;
     BasinArgs a{};
     basin_caps(a, d);
+    if (conn26 && !a.whole && d.X > 1 && d.Y > 1 && d.Z > 1) return IBIP_OK;
     TreeUse tree_use(ctx);
     void* mem = ensure(ctx, B_TREE, basin_bytes(a));
     uint32_t* h = (uint32_t*)pinned(ctx, 4096);

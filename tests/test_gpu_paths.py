@@ -415,3 +415,17 @@ def test_served_paths(dev, name, room, tree):
         assert srv.stats()["bytes_in_use"] == 0
     assert b["status"] == 0
     _same(b, oracle.invade(img, inl))
+
+
+# 26-connected: with room for all edges, and (volumes of more) by the tiles' sweeps
+@pytest.mark.parametrize("shape", [(60, 70, 80), (110, 100, 104), (2, 800, 900), (1, 1100, 1000)])
+def test_trapping_26_connected(dev, shape):
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = synth.blurred_noise(shape, 2.0, 0.6, 9)
+    inl, out = synth.face_mask(shape, 2, 0), synth.face_mask(shape, 2, shape[2] - 1)
+    seq = oracle.invade(img, inl)["seq"]
+    t, r = ibip.trap(_put(dev, seq), _put(dev, out), connectivity=26), oracle.trap(seq, out, conn=26)
+    assert np.array_equal(t["trapped"].cpu().numpy(), r["trapped"])
+    assert np.array_equal(t["seq_trapped"].cpu().numpy(), r["seq_trapped"])
