@@ -2403,13 +2403,13 @@ void fill_loop_args(void* out, const JobBufs& j, LoopState* st, ibip_dims d, uin
 // ---------------------------------------------------------------------------
 // Voxels of one common array; a larger batch is taken in several groups.
 constexpr int64_t kGroupVoxels = (int64_t)1 << 29;
-// What a group costs besides its voxels, in voxels of the common array, solid ones
-// that pad an image to the largest rows and planes of its group included. A group's
-// levels are a chain of their own, 2 to 4 ms, for which a hundred million such voxels
-// are passed over (512^3 with 48 images of 32^3: 58.5 ms for the large one alone, 71.6
-// together with 403 M voxels of padding), but they take 28 B of scratch each, 11 GB
-// there: 2^25 is about 1 GB.
-constexpr int64_t kGroupCost = (int64_t)1 << 25;
+// A group's levels are a chain of launches of their own, 2 to 9 ms, in which 2^28 solid
+// voxels and more of the common array are passed over (512^3 with 48 images of 32^3:
+// 58.5 ms for the large one alone, 71.6 together with 403 M voxels of padding; 20 cubes
+// of 32 to 192 26.4 ms in one group, 35.5 in two). But these take 28 B of scratch
+// each, 11 GB there: images are padded to the rows and planes of the largest of their
+// group by no more than the group's own voxels, or 2^26 of them (1.9 GB).
+constexpr int64_t kGroupCost = (int64_t)1 << 28, kGroupPadding = (int64_t)1 << 26;
 
 struct Group {
     std::vector<int32_t> job;  // indices into the caller's jobs
@@ -2462,8 +2462,7 @@ static std::vector<Group> batch_groups(const ibip_job* jobs, int32_t nj) {
             *held += nvox(jobs[it[k].q].dims);
         }
     };
-    // cost[u]: of the first u units; cut[u]: where their last group begins. A group
-    // of several has no more padding than voxels, or than kGroupCost.
+    // cost[u]: of the first u units; cut[u]: where their last group begins
     std::vector<int64_t> cost(nu + 1, INT64_MAX);
     std::vector<int32_t> cut(nu + 1, 0);
     cost[0] = 0;
@@ -2474,7 +2473,7 @@ static std::vector<Group> batch_groups(const ibip_job* jobs, int32_t nj) {
             add(g, j, &held);
             const Group r = g.rounded();
             const int64_t n = r.voxels();
-            if (j > i && (n > kGroupVoxels || n - held > std::max(held, kGroupCost))) break;
+            if (j > i && (n > kGroupVoxels || n - held > std::max(held, kGroupPadding))) break;
             if (cost[i] + kGroupCost + n < cost[j + 1]) {
                 cost[j + 1] = cost[i] + kGroupCost + n;
                 cut[j + 1] = i;

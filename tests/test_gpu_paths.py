@@ -379,7 +379,7 @@ def test_batches_of_uneven_shapes(dev, shapes):
         return ibip.invade_batch([_put(dev, i) for i in imgs], [_put(dev, i) for i in inls], sat=True), _scratch()
 
     out, scratch = _in_thread(work)
-    assert scratch < 200 * sum(i.size for i in imgs) + (1100 << 20)
+    assert scratch < 200 * sum(i.size for i in imgs) + (2200 << 20)
     for img, inl, b in zip(imgs, inls, out):
         ref = oracle.invade(img, inl)
         assert b["status"] == 0
