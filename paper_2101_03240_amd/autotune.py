@@ -5,11 +5,14 @@ Results never depend on these parameters, only speed does:
 * ``edt_tile_y`` / ``edt_tile_x``: z columns per LDS tile of the exact EDT's
   passes y (32 or 64) and x (16 or 32), chosen per size class of the image
   (largest side up to 96, 256 and 512; longer lines take the untiled passes);
-* ``batch_wide``: the step size above which a batch job leaves the batched
-  launch and continues with its wide steps over the whole GPU (never, or
-  32768 / 131072 / 524288 centres);
-* ``serve_wide``: the same threshold for the server's jobs (2048, 8192,
-  32768 centres, or never).
+* ``batch_wide``: where a batch runs step loops, the step size above which a
+  job leaves the batched launch and continues with its wide steps over the
+  whole GPU (never, or 32768 / 131072 / 524288 centres);
+* ``serve_wide``: the same threshold for the server's jobs that run step loops
+  (2048, 8192, 32768 centres, or never).
+
+The last two are timed on calls with a step limit, which step loops run (most
+calls without one go by the component tree, which knows no such threshold).
 
 ``python -m paper_2101_03240_amd.autotune`` times every candidate on seeded
 synthetic images of each class on the current GPU (HIP-event kernel time for
@@ -36,6 +39,8 @@ CLASSES = (("small", 96), ("medium", 256), ("large", 512), ("xlarge", 1 << 30))
 EDT_TILES = [(32, 32), (32, 16), (64, 32), (64, 16)]
 BATCH_WIDE = [-1, 32768, 131072, 524288]
 SERVE_WIDE = [8192, 2048, 32768, -1]
+BATCH_STEPS = 1000
+SERVE_STEPS = 4000
 MARGIN = 0.05
 MARGIN_EDT = 0.02
 
@@ -101,7 +106,7 @@ def _batch_images(n: int):
         return list(ex.map(synth.image_for_spec, specs))
 
 
-def tune_batch(dev, n: int = 96, reps: int = 3) -> dict:
+def tune_batch(dev, n: int = 96, reps: int = 7) -> dict:
     import torch
 
     import paper_2101_03240_amd as ibip
@@ -110,21 +115,22 @@ def tune_batch(dev, n: int = 96, reps: int = 3) -> dict:
     imgs = _batch_images(n)
     d_imgs = [torch.from_numpy(a).to(dev) for a in imgs]
     d_inls = [torch.from_numpy(synth.face_mask(a.shape, 0, 0)).to(dev) for a in imgs]
-    times = {}
-    for w in BATCH_WIDE:
-        ibip.invade_batch(d_imgs, d_inls, tuning={"batch_wide": w})
-        torch.cuda.synchronize()
-        t0 = time.perf_counter()
-        for _ in range(reps):
-            ibip.invade_batch(d_imgs, d_inls, tuning={"batch_wide": w})
-        torch.cuda.synchronize()
-        times[str(w)] = 1e3 * (time.perf_counter() - t0) / reps
+    runs = {str(w): [] for w in BATCH_WIDE}
+    for r in range(reps + 1):  # the candidates in turn; the first round warms up
+        for w in BATCH_WIDE:
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            ibip.invade_batch(d_imgs, d_inls, max_steps=BATCH_STEPS, tuning={"batch_wide": w})
+            torch.cuda.synchronize()
+            if r:
+                runs[str(w)].append(1e3 * (time.perf_counter() - t0))
+    times = {w: sorted(t)[len(t) // 2] for w, t in runs.items()}
     best = pick(times, str(BATCH_WIDE[0]), MARGIN)
     _log("batch_wide", best, {k: round(v, 2) for k, v in times.items()})
-    return {"batch_wide": int(best), "images": n, "ms": times}
+    return {"batch_wide": int(best), "images": n, "max_steps": BATCH_STEPS, "ms": times}
 
 
-def tune_serve(dev, sides=(192, 320, 448, 576), reps: int = 1) -> dict:
+def tune_serve(dev, sides=(192, 320, 448, 576), reps: int = 7) -> dict:
     import torch
 
     import paper_2101_03240_amd as ibip
@@ -137,20 +143,21 @@ def tune_serve(dev, sides=(192, 320, 448, 576), reps: int = 1) -> dict:
         m[0] = 1
         inls.append(m)
     torch.cuda.synchronize()
-    times = {}
-    for w in SERVE_WIDE:
-        with ibip.Server(dev, hbm_budget_bytes=32 << 30, max_inflight=len(imgs)) as srv:
-            srv.set_tuning({"batch_wide": w})
-            srv.wait(srv.submit(imgs[0], inls[0]))
-            t0 = time.perf_counter()
-            for _ in range(reps):
-                tickets = [srv.submit(a, b) for a, b in zip(imgs, inls)]
+    runs = {str(w): [] for w in SERVE_WIDE}
+    with ibip.Server(dev, hbm_budget_bytes=32 << 30, max_inflight=len(imgs)) as srv:
+        for r in range(reps + 1):
+            for w in SERVE_WIDE:
+                srv.set_tuning({"batch_wide": w})
+                t0 = time.perf_counter()
+                tickets = [srv.submit(a, b, max_steps=SERVE_STEPS) for a, b in zip(imgs, inls)]
                 for t in tickets:
                     srv.wait(t)
-            times[str(w)] = 1e3 * (time.perf_counter() - t0) / reps
+                if r:
+                    runs[str(w)].append(1e3 * (time.perf_counter() - t0))
+    times = {w: sorted(t)[len(t) // 2] for w, t in runs.items()}
     best = pick(times, str(SERVE_WIDE[0]), MARGIN)
     _log("serve_wide", best, {k: round(v, 2) for k, v in times.items()})
-    return {"serve_wide": int(best), "sides": list(sides), "ms": times}
+    return {"serve_wide": int(best), "sides": list(sides), "max_steps": SERVE_STEPS, "ms": times}
 
 
 def main() -> int:
