@@ -2,6 +2,7 @@
 // argument checks and error plumbing around the kernels of edt.hip,
 // invade.hip, trap.hip and mio.hip.
 #include <atomic>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -154,6 +155,12 @@ ibip_status batch_streams(ibip_ctx* ctx) {
         return fail(ctx, IBIP_EDEVICE, "cannot create batch streams");
     ctx->have_bstreams = true;
     return IBIP_OK;
+}
+
+int hw_queues() {
+    const char* v = std::getenv("GPU_MAX_HW_QUEUES");
+    const int q = v ? std::atoi(v) : 0;
+    return q > 0 ? q : 4;
 }
 
 bool dims_ok(ibip_dims d) {

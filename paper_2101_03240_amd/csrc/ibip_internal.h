@@ -290,6 +290,8 @@ void* pinned(ibip_ctx* ctx, size_t bytes);
 // ctx->done_host/done_dev with at least `words` words, zeroed; false on failure.
 bool done_records(ibip_ctx* ctx, size_t words);
 bool dims_ok(ibip_dims d);
+// Hardware queues that the process's streams share (HIP's own setting, 4 by default).
+int hw_queues();
 inline int64_t nvox(ibip_dims d) { return (int64_t)d.X * d.Y * d.Z; }
 
 // ---- launchers (each returns hipSuccess or the first launch error) ----

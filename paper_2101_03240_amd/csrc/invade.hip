@@ -1771,9 +1771,9 @@ double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R) {
 // 0.7 voxels (76 %) 36.5 and 19.3.
 bool tree_crowded(int64_t n_pore, uint32_t largest) { return 32 * (int64_t)largest > 27 * n_pore; }
 
-bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps) {
+bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps, double loops) {
     return n_pore > 0 && !tree_crowded(n_pore, largest) &&
-           loop_ms_expected(d, n_pore, R, max_steps) > tree_ms_expected(d, n_pore, R);
+           loop_ms_expected(d, n_pore, R, max_steps) > loops * tree_ms_expected(d, n_pore, R);
 }
 
 bool sizes_by_loop(ibip_dims d, int64_t max_steps) {
@@ -2992,16 +2992,20 @@ static ibip_status run_batch_loops(ibip_ctx* ctx, ibip_job* jobs, const std::vec
 }
 
 // Whether the step loops of a batch, side by side, are expected to end before the
-// groups' trees, by their sizes alone (see sizes_by_loop). Each job's setup and results take 0.135 ms with a loop and 0.08
-// without; the loops share the memory (20 planes 300^2 take 2 times as long as one, 64
-// images of 64^3 3 times, of 128^3 6 times, 256 of 64^3 10 times).
+// groups' trees, by their sizes alone (see sizes_by_loop). Each job's setup and results
+// take 0.135 ms with a loop and 0.08 without. The loops, in two launches, share the
+// memory and, with few hardware queues, one launch waits for the other: 20 planes
+// 300^2 take 2 times as long as one with 4 queues, 1.3 with 16; 64 images of 64^3 3
+// times, of 128^3 6 and 4 times, 256 of 64^3 10 times. ms by loops and by trees, with 4
+// queues: 20 planes 200^2 7.9, 8.7; 64 of 64^3 20.9, 22.5; 256 of 64^3 70, 64; 8 of 128^3
+// 33.8, 17.5; 256 of 16^3 34.7, 21.6; with 16: 6.6, 9.0; 19.9, 22.4; 77, 62; 33.6, 17.8; 41.6, 23.2.
 static bool batch_by_loops(const ibip_job* jobs, int32_t nj, const std::vector<Group>& groups) {
     double longest = 0, loops = 0.135 * nj, trees = 0.08 * nj;
     for (int32_t i = 0; i < nj; i++) {
         const ibip_dims d = jobs[i].dims;
         longest = std::max(longest, loop_ms_expected(d, (int64_t)(kGuessPore * (double)nvox(d)), kGuessRanks, jobs[i].max_steps));
     }
-    loops += longest * (1 + nj / 16.0);
+    loops += longest * (1 + nj / (hw_queues() >= 12 ? 32.0 : 16.0));
     for (const Group& g : groups) {
         int64_t n = 0;
         for (int32_t q : g.job) n += nvox(jobs[q].dims);

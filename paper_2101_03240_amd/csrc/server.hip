@@ -111,6 +111,7 @@ struct ibip_server {
     int device = 0;
     size_t budget = 0;
     int max_inflight = 0;
+    int queues = 4;  // hardware queues
     int lookahead = 0;
     uint8_t* pool_base = nullptr;
     ibip::Pool pool;
@@ -224,7 +225,13 @@ bool advance(ibip_server* S, int si, hipError_t* e, std::unique_lock<std::mutex>
             hs->err = !hs->solid_seen ? 2u : 3u;
             return false;
         }
-        if (tree_pays(jb.dims, hs->n_pore, hs->R, hs->largest, jb.max_steps)) {
+        // Step loops run side by side, as many as there are hardware queues; trees, a
+        // thousand launches each from this one thread, about three. With 4 queues that
+        // is the same within what is expected of either; with 16, and as many jobs, a tree
+        // has to be twice as fast (32 jobs of 64^3 21.6 ms by loops, 32.1 by trees, 16 of
+        // 100^3 25.8 and 22.1; with 4 queues 39.7 and 32, 51 and 24).
+        const int64_t side = std::min<int64_t>(S->stats.running + S->stats.pending, S->queues);
+        if (tree_pays(jb.dims, hs->n_pore, hs->R, hs->largest, jb.max_steps, std::max(1.0, 1.0 + (double)(side - 4) / 12))) {
             sl.tree = job_tree_args(b, *hs, h_off, jb.dims, jb.seq);
             const size_t bytes = align256(4 * tree_words(sl.tree));
             if (S->pool.alloc(bytes, &J.tree_off)) {
@@ -413,6 +420,7 @@ ibip_status ibip_server_create(ibip_server** out, int32_t device, const ibip_ser
     S->device = device;
     S->budget = (size_t)budget;
     S->max_inflight = inflight;
+    S->queues = hw_queues();
     S->lookahead = lookahead;
     int prev = -1;
     (void)hipGetDevice(&prev);

@@ -195,8 +195,9 @@ inline void tree_carve(TreeArgs& a, uint32_t* w) {
     a.kb = 32 - levels;
 }
 // Whether an invasion is expected to take less time by the tree than by the step loop
-// (largest: the voxels of the most frequent rank; max_steps 0: no limit).
-bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps);
+// (largest: the voxels of the most frequent rank; max_steps 0: no limit), `loops` loops
+// of other jobs running in the time of one tree beside it.
+bool tree_pays(ibip_dims d, int64_t n_pore, uint32_t R, uint32_t largest, int64_t max_steps, double loops = 1.0);
 // The same of an image of which nothing is known yet, taken as 60 % pore with 80 ranks.
 constexpr double kGuessPore = 0.6;
 constexpr uint32_t kGuessRanks = 80;
