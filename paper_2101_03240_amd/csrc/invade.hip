@@ -1753,13 +1753,13 @@ hipError_t launch_finalise(int32_t* seq, int64_t n, const uint32_t* M, uint32_t*
 // 2.83; 128^3 16.9, 6.0; plane 90^2 0.89, 1.48; 260^2 4.37, 2.01; 512^3 502, 54.6; 512^3
 // stopped after 5,000 steps 11.6, 54.6.
 double loop_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R, int64_t max_steps) {
-    const bool plane = d.X == 1 || d.Y == 1 || d.Z == 1;
+    const bool plane = is_plane(d);
     double steps = (plane ? 0.42 : 0.055) * (double)n_pore / std::cbrt((double)R);
     if (max_steps > 0) steps = std::min(steps, (double)max_steps);
     return 0.25 + (plane ? 0.97e-3 : 1.3e-3) * steps;
 }
 double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R) {
-    const bool plane = d.X == 1 || d.Y == 1 || d.Z == 1;
+    const bool plane = is_plane(d);
     return 0.5 + 0.011 * R + (plane ? 0.8e-3 : 0.3e-3) * std::pow((double)n_pore, 2.0 / 3.0);
 }
 
@@ -1883,7 +1883,7 @@ ibip_status run_invade(ibip_ctx* ctx, const uint8_t* image, const uint8_t* inlet
         if ((rc = hip_check(ctx, hipEventSynchronize(ctx->copy_ev), "sync")) != IBIP_OK) return rc;
         uint32_t lcap = 0;
         for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
-        tree_caps(ta, (uint32_t)n_pore, 1, lcap);
+        tree_caps(ta, (uint32_t)n_pore, 1, lcap, is_plane(d));
         tree_use.emplace(ctx);
         if (uint32_t* w = (uint32_t*)ensure(ctx, B_TREE, tree_words(ta) * sizeof(uint32_t))) {
             tree_carve(ta, w);
@@ -2280,7 +2280,7 @@ TreeArgs job_tree_args(const JobBufs& j, const LoopState& hs, const uint32_t* of
     ta.n = (uint32_t)nvox(d);
     uint32_t lcap = 0;
     for (uint32_t r = 1; r <= hs.R; r++) lcap = std::max(lcap, off_host[r + 1] - off_host[r]);
-    tree_caps(ta, hs.n_pore, 1, lcap);
+    tree_caps(ta, hs.n_pore, 1, lcap, is_plane(d));
     return ta;
 }
 
@@ -2624,7 +2624,9 @@ static ibip_status run_batch_group(ibip_ctx* ctx, ibip_job* jobs, const Group& g
     if ((rc = hip_check(ctx, hipStreamSynchronize(s), "sync")) != IBIP_OK) return rc;
     uint32_t lcap = 0;
     for (uint32_t r = 1; r <= R; r++) lcap = std::max(lcap, h_off[r + 1] - h_off[r]);
-    tree_caps(ta, n_pore, (uint32_t)m, lcap);
+    bool planes = false;
+    for (int32_t j = 0; j < m; j++) planes = planes || is_plane(dims(j));
+    tree_caps(ta, n_pore, (uint32_t)m, lcap, planes);
     // list, thread of each place (then the full balls), M; the tree's own
     const size_t pore_bytes = align256(4 * ((size_t)n_pore + 1));
     TreeUse tree_use(ctx);

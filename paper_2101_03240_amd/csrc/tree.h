@@ -208,18 +208,20 @@ double tree_ms_expected(ibip_dims d, int64_t n_pore, uint32_t R);
 // Levels of at most this many voxels are searched in one workgroup.
 constexpr uint32_t kTreeSmall = 2048;
 
-// The scratch's caps for n_pore pore voxels in njobs images, the largest level
-// of lcap voxels. More peaks, events or candidates than that and the tree gives
-// up. Pore voxels per peak: 130 to 260 in volumes of blurred noise or grains, 50
-// to 100 in such planes, 9 to 25 in noise of single voxels. Pore voxels per event
-// (step): 50 to 200 in volumes, but 9 to 16 in planes, 27 in plane noise of single
-// voxels. An image has no more of either than pore voxels; the 4,096 are its own.
-inline void tree_caps(TreeArgs& a, uint32_t n_pore, uint32_t njobs, uint32_t lcap) {
+inline bool is_plane(ibip_dims d) { return d.X == 1 || d.Y == 1 || d.Z == 1; }
+// The scratch's caps for n_pore pore voxels in njobs images (planes: one of them is
+// one), the largest level of lcap voxels. More peaks, events or candidates than that
+// and the tree gives up. Pore voxels per peak: 130 to 260 in volumes of blurred noise
+// or grains, 50 to 100 in such planes, 9 to 25 in noise of single voxels. Pore voxels
+// per event (step): 50 to 200 in volumes (16 and more in the smallest), but 9 to 16 in
+// planes, 27 in plane noise of single voxels. An image has no more of either than pore
+// voxels; the 4,096 are its own.
+inline void tree_caps(TreeArgs& a, uint32_t n_pore, uint32_t njobs, uint32_t lcap, bool planes) {
     a.n_pore = n_pore;
     a.njobs = njobs;
     const uint64_t own = 4096 * (uint64_t)njobs;
     a.pcap = (uint32_t)std::min<uint64_t>(n_pore, n_pore / 8 + own);
-    a.ecap = (uint32_t)std::min<uint64_t>(n_pore, n_pore / 4 + own) + njobs;
+    a.ecap = (uint32_t)std::min<uint64_t>(n_pore, n_pore / (planes ? 4 : 16) + own) + njobs;
     a.lcap = lcap;
     a.xcap = lcap + 4096;
     a.ncap = n_pore / 6;

@@ -429,3 +429,24 @@ def test_trapping_26_connected(dev, shape):
     t, r = ibip.trap(_put(dev, seq), _put(dev, out), connectivity=26), oracle.trap(seq, out, conn=26)
     assert np.array_equal(t["trapped"].cpu().numpy(), r["trapped"])
     assert np.array_equal(t["seq_trapped"].cpu().numpy(), r["seq_trapped"])
+
+
+def test_served_trees_wait_for_room(dev):
+    """A pool with room for three jobs' scratch and one tree: the trees follow one
+    another, and every ticket comes back."""
+    import oracle
+    import paper_2101_03240_amd as ibip
+
+    img = synth.blurred_noise((120, 130, 128), 3.0, 0.6, 3)
+    inl = synth.face_mask(img.shape, 0, 0)
+    ref = oracle.invade(img, inl)
+    n = img.size
+    d_img, d_inl = _put(dev, img), _put(dev, inl)
+    with ibip.Server(dev, hbm_budget_bytes=3 * 27 * n + 36 * n, max_inflight=4) as srv:
+        ts = [srv.submit(d_img, d_inl) for _ in range(7)]
+        res = [srv.wait(t) for t in ts]
+        st = srv.stats()
+    assert st["bytes_in_use"] == 0 and st["running"] == 0 and st["completed"] == 7
+    for b in res:
+        assert b["status"] == 0
+        _same(b, ref)
