@@ -226,22 +226,24 @@ ibip_status ibip_invade_resume(ibip_ctx* ctx, const uint8_t* image, const uint8_
 /*
  * ibip_invade_batch -- ibip_invade (Section 2.1) over many images of uneven
  * size in one call, with the same results as one ibip_invade per image.
- * Each job names its own device buffers, dims and step limit. The images share
- * one component tree (in groups of up to 2^29 voxels, the smaller ones padded
- * to the rows and planes of the largest), whose levels are searched for all of
- * them together; a batch whose jobs all stop after fewer than 1,024 steps runs
- * their step loops in one launch instead, one workgroup per job. A job's seq
- * also holds intermediate values while the call runs.
+ * Each job names its own device buffers, dims and step limit. Images of like rows
+ * and planes share a component tree (groups of up to 2^29 voxels, the images padded
+ * to the rows and planes of the largest, by 2^26 voxels or the group's own at most),
+ * whose levels are searched for all of them together. Where they are expected to
+ * end sooner (a few small images, jobs stopped after few steps), and for a group
+ * that the tree cannot take (more than 8192 distinct distance values together, one
+ * of them on almost all voxels, more peaks or steps than there is room for, no room
+ * for its scratch), the step loops of all jobs run in one launch instead, one
+ * workgroup per job. A job's seq also holds intermediate values while the call runs.
  * Per job: status receives the job's ibip_status (OK, ENOSOLID, ECAPACITY,
  * EDEVICE) and n_steps its K. M (uint32) and sat (double) are optional DEVICE
  * outputs of the per-step squared radius and saturation, each with capacity
  * for at least as many entries as the image has pore voxels.
- * Jobs that the batched paths cannot take (more than 8192 distinct distance
- * values in the pore space of a group, or more peaks or steps than its tree
- * has room for) run afterwards, alone, through the path of ibip_invade on the
- * context's stream (same results); that call replaces the context's per-step
- * arrays, so ibip_get_steps afterwards reports EINVAL until the next
- * ibip_invade.
+ * Jobs that neither can take (more than 8192 distinct distance values in one image,
+ * more than 2^29 voxels, no room for the loops' scratch) run afterwards, alone,
+ * through the path of ibip_invade on the context's stream (same results); that call
+ * replaces the context's per-step arrays, so ibip_get_steps afterwards reports EINVAL
+ * until the next ibip_invade.
  * Returns IBIP_OK when every job succeeded, else the first failing job's code.
  */
 typedef struct {

@@ -368,8 +368,9 @@ def invade(image, inlets, max_steps: int = 0, sigma: float = 1.0, theta_rad: flo
 
 def set_tuning(tuning: dict | None = None, device=None):
     """Launch parameters for the calling thread's context (ibip_ctx_set_tuning):
-    ``edt_tile_y`` (32 or 64), ``edt_tile_x`` (16 or 32), ``batch_wide`` (a
-    batch job's steps above it run over the whole GPU; negative: never).
+    ``edt_tile_y`` (32 or 64), ``edt_tile_x`` (16 or 32), ``batch_wide`` (where a
+    batch job runs its step loop, steps above it run over the whole GPU;
+    negative: never).
     Missing keys or None: defaults. Results never depend on them."""
     torch = _torch()
     ctx = _context(torch.device(device) if device is not None else torch.device("cuda", torch.cuda.current_device()))
@@ -392,9 +393,9 @@ def get_tuning(device=None) -> dict:
 
 def invade_batch(images, inlets, max_steps=0, rad2: bool = True, centre_step: bool = True, M: bool = True,
                  sat: bool = False, raise_on_error: bool = True, tuning: dict | None = None):
-    """ibip_invade over a list of images of uneven size in one call (the step
-    loops of all jobs run in one launch; a job's step above the wide
-    threshold continues over the whole GPU). ``inlets`` is a list of masks of
+    """ibip_invade over a list of images of uneven size in one call (by shared
+    component trees, or by the step loops of all jobs in one launch, where a
+    job's step above the wide threshold continues over the whole GPU). ``inlets`` is a list of masks of
     matching shapes; ``max_steps`` an int or a list. ``tuning`` (keys of
     ``set_tuning``) applies to this call only. Returns a list of dicts like
     ``invade`` (``seq``, ``rad2``, ``centre_step``, ``K``, ``M``, ``sat``)

@@ -1,5 +1,6 @@
-// The invasion loop of Section 2.1 (Figure 2(e)-(l)) and its per-step
-// post-processing (Sections 2.2.1-2.2.2).
+// The invasion of Section 2.1 (Figure 2(e)-(l)) by its step loop, the choice between
+// that and the component tree (tree.hip), and the per-step post-processing
+// (Sections 2.2.1-2.2.2).
 //
 // Data layout in HBM (N voxels, N_pore pore voxels, R distinct dt2 values):
 //   key[N]      uint32  bits 0..23: rank of dt2 among the distinct pore values
@@ -30,10 +31,10 @@
 // was painted): after the loop, seq[v] = min over centres c whose ball
 // B(c, M) = {|v - c|^2 < M} holds v of step(c), as an atomicMin per stamp --
 // this equals first-write-wins in step order. A centre c with a face
-// neighbour p that was a centre of an earlier step with a ball at least as
-// large stamps only the part of its ball outside B(p): the one-voxel cap
-// S = {o : |o|^2 < M <= |o - n|^2} (n = p - c), filtered by every other such
-// neighbour. This is exact: the smallest step covering a voxel always stamps
+// neighbour p that was a centre of an earlier step, or of the same step at a
+// smaller index, with a ball at least as large stamps only the part of its ball
+// outside B(p): voxels of the one-voxel cap {o : |o|^2 < M <= |o - n|^2} (n = p - c),
+// filtered by every other such neighbour. This is exact: the smallest step covering a voxel always stamps
 // it, since a ball it skipped is covered by an earlier ball.
 #include <chrono>
 #include <climits>

@@ -32,14 +32,15 @@
 //  1. The component tree: the voxels climb to their basins' tops, and Boruvka
 //     rounds on the basins leave the edges that hold their graph together (basin.hip);
 //     level by level from the highest rank down, a union-find joins the basins of
-//     the level's edges. The root of a component is its highest top (rank, then
-//     lowest index), its peak; a peak whose component joins a higher one at
-//     level t keeps (t, the other peak), so the label of a voxel's component
-//     at any level is found by walking from the voxel's peak.
+//     the level's edges. The root of a component is its highest top, its peak (of
+//     equal ones the larger basin's; no result depends on which); a peak whose
+//     component joins a higher one at level t keeps (t, the other peak), so the
+//     label of a voxel's component at any level is found by walking from the
+//     voxel's peak.
 //  2. The levels from the lowest rank up: the search above.
 //  3. The numbers, and the step of every voxel.
 // Levels of few voxels run in one workgroup, several levels per launch, the
-// others over the whole GPU.
+// others over the whole GPU until few are left (kTreeStall).
 #include <climits>
 
 #include "tree.h"
