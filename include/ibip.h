@@ -272,12 +272,10 @@ ibip_status ibip_invade_batch(ibip_ctx* ctx, ibip_job* jobs, int32_t n);
  * almost one rank), the step loop in one workgroup; sphere insertion and
  * finalisation. The tree's own scratch comes from the pool as well: 45 to 48 bytes
  * per pore voxel (51 to 54 in a plane), and at least 97 per voxel for images of up
- * to a million voxels, 12 to 17 for larger ones. A job whose tree does not fit then
- * waits for room, while others run that will give some back and where its step loop
- * would take three times as long, and no job is admitted meanwhile; else, and where
- * the tree gives up, the step loop runs. Admitted jobs overlap on the device. A job
- * behind one that does not fit yet may start first (within `lookahead` places), so
- * a huge job does not block the queue.
+ * to a million voxels, 12 to 17 for larger ones; without room for it when the job's
+ * pore voxels are known, and where it gives up, the step loop runs. Admitted jobs
+ * overlap on the device. A job behind one that does not fit yet may start first
+ * (within `lookahead` places), so a huge job does not block the queue.
  * A job's results are those of ibip_invade on the same inputs.
  * The job's input buffers must hold their data when it is submitted, and its
  * output buffers must stay valid until ibip_server_wait returns for it.

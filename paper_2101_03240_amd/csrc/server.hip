@@ -10,10 +10,10 @@
 // overlap on the device. Between the parts the worker, which polls each slot's
 // completion event, reads what the next one's launches depend on. The tree's
 // own scratch comes from the pool too, once the job's pore voxels are known; a
-// job that is small or stops after few steps, for which there is no room even
-// after a wait, or whose tree gives up runs its step loop in one workgroup
-// instead. At the end the worker returns the job's scratch to the pool and records
-// its latency from submission to completion.
+// job that is small or stops after few steps, for which there is no room then, or
+// whose tree gives up runs its step loop in one workgroup instead. At the end the
+// worker returns the job's scratch to the pool and records its latency from
+// submission to completion.
 #include <algorithm>
 #include <chrono>
 #include <condition_variable>
@@ -89,9 +89,8 @@ constexpr size_t kSlotSmall = 4096;  // LoopState + loop arguments of one slot
 constexpr size_t kSlotPinned = kSlotSmall + sizeof(uint32_t) * (kMaxRanks + 2);
 static_assert(sizeof(TreeCtl) + sizeof(TreeJob) <= 2048, "the tree's head fits beside the loop state");
 
-// What runs on a slot: setup, (nothing, while its tree waits for room in the pool,)
-// the component tree, the step loop, post-processing.
-enum Phase { P_SETUP = 1, P_WAIT, P_TREE, P_LOOP, P_POST };
+// What runs on a slot: setup, the component tree, the step loop, post-processing.
+enum Phase { P_SETUP = 1, P_TREE, P_LOOP, P_POST };
 
 struct Slot {
     hipStream_t stream = nullptr;
@@ -205,20 +204,6 @@ void release_tree(ibip_server* S, Job& J) {
     J.tree_bytes = 0;
 }
 
-// A job whose tree finds no room in the pool waits for it, with no job admitted
-// meanwhile, where its step loop would take this many times as long, and while another
-// job runs a part after which it gives room back (a step loop is not waited for). 64
-// requests of side 64 to 768 in a pool of 96 GB: 1.97 s with the largest in their
-// loops, 0.87 with this wait.
-constexpr double kWaitFactor = 3.0;
-bool frees_room_soon(const ibip_server* S, int si) {
-    for (size_t i = 0; i < S->slots.size(); i++) {
-        const Slot& o = S->slots[i];
-        if ((int)i != si && o.ticket >= 0 && o.phase != P_WAIT && o.phase != P_LOOP) return true;
-    }
-    return false;
-}
-
 // The slot's queued work ended (mu held through lk): queue the job's next
 // part. Returns false when the job is finished (or a launch failed: *e holds
 // the error).
@@ -236,7 +221,7 @@ bool advance(ibip_server* S, int si, hipError_t* e, std::unique_lock<std::mutex>
     const JobBufs b = job_bufs(S, J);
     hipError_t r = hipSuccess;
     bool state_back = true;  // the loop state is read back after this part
-    if (sl.phase == P_SETUP || sl.phase == P_WAIT) {
+    if (sl.phase == P_SETUP) {
         if (!hs->solid_seen || hs->R > (uint32_t)kMaxRanks) {
             hs->err = !hs->solid_seen ? 2u : 3u;
             return false;
@@ -254,10 +239,6 @@ bool advance(ibip_server* S, int si, hipError_t* e, std::unique_lock<std::mutex>
                 J.tree_bytes = bytes;
                 S->stats.bytes_in_use += (int64_t)bytes;
                 if (S->stats.bytes_in_use > S->stats.peak_bytes) S->stats.peak_bytes = S->stats.bytes_in_use;
-            } else if (J.bytes + bytes <= S->budget && frees_room_soon(S, si) &&
-                       tree_pays(jb.dims, hs->n_pore, hs->R, hs->largest, jb.max_steps, kWaitFactor)) {
-                sl.phase = P_WAIT;
-                return true;
             }
         }
         if (J.tree_bytes) {
@@ -350,12 +331,8 @@ void worker_main(ibip_server* S) {
             const hipError_t q = hipEventQuery(sl.done);
             if (q == hipErrorNotReady) continue;
             hipError_t e = q == hipSuccess ? hipSuccess : q;
-            const bool waited = sl.phase == P_WAIT;
-            if (advance(S, (int)si, &e, lk)) {
-                progressed = progressed || !waited || sl.phase != P_WAIT;
-                continue;
-            }
             progressed = true;
+            if (advance(S, (int)si, &e, lk)) continue;
             finish_job(S, (int)si, e);
         }
         if (progressed) S->cv_done.notify_all();
@@ -368,10 +345,6 @@ void worker_main(ibip_server* S) {
                     break;
                 }
             if (free_slot < 0 || S->pending.empty()) break;
-            // (room that is given back goes to a waiting job's tree first)
-            if (std::any_of(S->slots.begin(), S->slots.end(),
-                            [](const Slot& x) { return x.ticket >= 0 && x.phase == P_WAIT; }))
-                break;
             bool started = false;
             const size_t window = std::min<size_t>(S->pending.size(), (size_t)S->lookahead);
             for (size_t w = 0; w < window; w++) {

@@ -431,9 +431,9 @@ def test_trapping_26_connected(dev, shape):
     assert np.array_equal(t["seq_trapped"].cpu().numpy(), r["seq_trapped"])
 
 
-def test_served_trees_wait_for_room(dev):
-    """A pool with room for three jobs' scratch and one tree: the trees follow one
-    another, and every ticket comes back."""
+def test_served_trees_short_of_room(dev):
+    """A pool with room for three jobs' scratch and one tree: some jobs have a tree,
+    some run their loops, and every ticket comes back."""
     import oracle
     import paper_2101_03240_amd as ibip
 
